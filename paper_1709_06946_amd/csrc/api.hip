@@ -40,10 +40,11 @@ template <> GridSet<float> &grids<float>(Handle &h) { return h.g32; }
 // stride vstride).  Deformed lattices: x in lattice coordinates, the step
 // c A^-1 v taken there and wrapped; out in lattice coordinates (cartesian =
 // 0, the library's mid-point) or mapped back by A (cartesian = 1, the
-// caller's positions).
+// caller's positions).  order: out in the caller's order.
 __global__ void advance_kernel(const double *__restrict__ x, const double *__restrict__ v,
                                int vstride, double c, int64_t n, double L,
-                               double *__restrict__ out, Deform df, int cartesian) {
+                               double *__restrict__ out, Deform df, int cartesian,
+                               const int *__restrict__ order) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   double dv[3] = {v[i * vstride], v[i * vstride + 1], v[i * vstride + 2]};
@@ -60,8 +61,9 @@ __global__ void advance_kernel(const double *__restrict__ x, const double *__res
     if (t < 0) t = 0;
     y[d] = t;
   }
+  const int64_t o = order ? order[i] : i;
   for (int d = 0; d < 3; ++d)
-    out[3 * i + d] = (df.on && cartesian)
+    out[3 * o + d] = (df.on && cartesian)
                          ? df.A[3 * d] * y[0] + df.A[3 * d + 1] * y[1] + df.A[3 * d + 2] * y[2]
                          : y[d];
 }
@@ -87,12 +89,14 @@ __global__ void rhs_kernel(const double *__restrict__ slip, const double *__rest
     b[i * 5 + k] = -(slip[i * NC + 6 + k] + (m ? m[i * NC + 6 + k] : 0.0));
 }
 
-// moments (N x 11) = [FL | S]
+// moments (N x 11) = [FL | S], FL in the caller's order
 __global__ void moments_kernel(const double *__restrict__ FL, const double *__restrict__ S,
-                               int64_t n, double *__restrict__ q) {
+                               const int *__restrict__ order, int64_t n,
+                               double *__restrict__ q) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  for (int k = 0; k < 6; ++k) q[i * NC + k] = FL ? FL[i * 6 + k] : 0.0;
+  const int64_t f = order[i];
+  for (int k = 0; k < 6; ++k) q[i * NC + k] = FL ? FL[f * 6 + k] : 0.0;
   for (int k = 0; k < 5; ++k) q[i * NC + 6 + k] = S ? S[i * 5 + k] : 0.0;
 }
 
@@ -190,6 +194,22 @@ __global__ void f2d_kernel(const float2 *src, double2 *dst, size_t n) {
 }
 
 // ------------------------------------------------------------ operators --
+
+// Result rows to the caller's order; with check, non-finite numbers in the
+// caller's rows are reported.
+static void return_rows(Handle &h, const double *src, int w, int lo, int hi, double *out,
+                        bool check) {
+  if (!check) {
+    scatter_rows(h, src, w, lo, hi, out);
+    return;
+  }
+  int *flag = reinterpret_cast<int *>(h.small + h.small_len - 2), bad = 0;
+  fill_int(h, flag, 1, 0);
+  scatter_rows(h, src, w, lo, hi, out, flag);
+  PSE_HIP(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, h.stream));
+  PSE_HIP(hipStreamSynchronize(h.stream));
+  if (bad) throw Error{PSE_ERR_NONFINITE, "non-finite mobility product (non-finite input?)"};
+}
 
 template <typename T>
 static void wave_apply(Handle &h, const double *xw, const double *in, Layout lin,
@@ -378,9 +398,18 @@ static KrylovResult real_sqrt(Handle &h, const double *xw, const double *psi, do
                       &h.lz_prev);
 }
 
-static void prepare_positions(Handle &h, const double *x, double *xw) {
-  wrap_positions(h, x, xw);
-  build_cells(h, xw);
+// The product of the whole moments (or, es, of the constraint operator) at
+// the caller's positions: moments and velocities in the caller's order, the
+// velocities checked on request.
+static void product(Handle &h, const double *x, const double *in, double *out, unsigned parts,
+                    bool check) {
+  const bool real = parts & PSE_REAL, wave = parts & PSE_WAVE, es = parts & PSE_ES_BLOCK;
+  const CompSet all = comps_range(0, NC);
+  prepare_positions(h, x);
+  gather_rows(h, in, NC, h.v4);
+  if (es) es_apply(h, h.xw, real, wave, h.v4, FULL_LAYOUT, h.v5, FULL_LAYOUT, false);
+  else mobility(h, h.xw, real, wave, h.v4, FULL_LAYOUT, all, h.v5, FULL_LAYOUT, all, false);
+  return_rows(h, h.v5, NC, es ? 6 : 0, NC, out, check);
 }
 
 void clear_graphs(Handle &h) {
@@ -761,6 +790,7 @@ static void create(const pse_params &p, Handle &h) {
   handle_alloc(h, (void **)&h.cells.bcount, (size_t)h.cells.nc * h.cells.nc * h.cells.nc * sizeof(int));
   handle_alloc(h, (void **)&h.cells.bstart,
                ((size_t)h.cells.nc * h.cells.nc * h.cells.nc + 1) * sizeof(int));
+  handle_alloc(h, (void **)&h.order, n * sizeof(int));
   handle_alloc(h, (void **)&h.xw, 3 * n * sizeof(double));
   handle_alloc(h, (void **)&h.xh, 3 * n * sizeof(double));
   double **vs[6] = {&h.v0, &h.v1, &h.v2, &h.v3, &h.v4, &h.v5};
@@ -797,7 +827,7 @@ static void release(Handle &h) {
                   h.cells.scan_tmp, h.cells.of, h.cells.slot, h.cells.scat, h.cells.perm,
                   h.sbins.start, h.sbins.count, h.sbins.scan_tmp, h.sbins.of, h.sbins.slot,
                   h.sbins.scat, h.sbins.perm, h.cells.trav, h.cells.bcount, h.cells.bstart,
-                  h.xw, h.xh, h.v0, h.v1, h.v2, h.v3, h.v4, h.v5, h.es_b, h.es_x, h.es_r,
+                  h.order, h.xw, h.xh, h.v0, h.v1, h.v2, h.v3, h.v4, h.v5, h.es_b, h.es_x, h.es_r,
                   h.es_d, h.es_p, h.lz_V, h.gm_V, h.small, h.dots, h.ktab, h.pl_cnt,
                   h.pl_start, h.pl_scan, h.pl_nbr, h.pl_rec64, h.pl_rec32, h.tl_cnt, h.tl_start,
                   h.tl_scan, h.tl_rec, h.bad_pos, h.ktab32, h.dctl, h.dstats, h.dstep,
@@ -931,17 +961,7 @@ int pse_mobility_apply(pse_handle *hd, const double *x, const double *in, double
     return PSE_ERR_INVALID;
   }
   return guarded(hd, [&] {
-    Handle &h = hd->h;
-    const CompSet all = comps_range(0, NC);
-    prepare_positions(h, x, h.xw);
-    if (parts & PSE_ES_BLOCK)
-      es_apply(h, h.xw, parts & PSE_REAL, parts & PSE_WAVE, in, FULL_LAYOUT, out, FULL_LAYOUT,
-               false);
-    else
-      mobility(h, h.xw, parts & PSE_REAL, parts & PSE_WAVE, in, FULL_LAYOUT, all, out,
-               FULL_LAYOUT, all, false);
-    if (!h.async && check_finite(h, out, (size_t)h.n * NC))
-      throw Error{PSE_ERR_NONFINITE, "non-finite mobility product (non-finite input?)"};
+    product(hd->h, x, in, out, parts, !hd->h.async);
   });
 }
 
@@ -961,16 +981,7 @@ int pse_mobility_apply_noalloc(const pse_params *p, const double *x, const doubl
     h.arena = scratch_address();
     h.arena_size = kScratchBytes;
     create(q, h);
-    const CompSet all = comps_range(0, NC);
-    prepare_positions(h, x, h.xw);
-    if (parts & PSE_ES_BLOCK)
-      es_apply(h, h.xw, parts & PSE_REAL, parts & PSE_WAVE, in, FULL_LAYOUT, out, FULL_LAYOUT,
-               false);
-    else
-      mobility(h, h.xw, parts & PSE_REAL, parts & PSE_WAVE, in, FULL_LAYOUT, all, out,
-               FULL_LAYOUT, all, false);
-    if (check_finite(h, out, (size_t)h.n * NC))
-      throw Error{PSE_ERR_NONFINITE, "non-finite mobility product (non-finite input?)"};
+    product(h, x, in, out, parts, true);
   });
   RelaxedCaptureScope relaxed;
   (void)hipStreamSynchronize(h.stream);
@@ -1098,15 +1109,12 @@ int pse_brownian_sample(pse_handle *hd, const double *x, const double *psi_real,
       PSE_LAUNCH_CHECK();
     }
     // pair sums and interpolation only: no spreading tile lists
-    wrap_positions(h, x, h.xw);
-    build_cells(h, h.xw, false);
+    prepare_positions(h, x, false);
     if (out_real) {
-      const double *psi = psi_real;
-      if (!psi) {
-        real_noise(h, seed, counter, h.v2);
-        psi = h.v2;
-      }
-      KrylovResult r = real_sqrt(h, h.xw, psi, out_real);
+      if (psi_real) gather_rows(h, psi_real, NC, h.v2);
+      else real_noise(h, seed, counter, h.v2);
+      KrylovResult r = real_sqrt(h, h.xw, h.v2, h.v0);
+      scatter_rows(h, h.v0, NC, 0, NC, out_real);
       st.lanczos_iters = r.iters;
       st.lanczos_change = r.resid;
       if (!r.converged) {
@@ -1114,7 +1122,10 @@ int pse_brownian_sample(pse_handle *hd, const double *x, const double *psi_real,
         warn = PSE_WARN_NOT_CONVERGED;
       }
     }
-    if (out_wave) wave_sqrt(h, h.xw, psi_wave, seed, counter, out_wave, comps_range(0, NC));
+    if (out_wave) {
+      wave_sqrt(h, h.xw, psi_wave, seed, counter, h.v1, comps_range(0, NC));
+      scatter_rows(h, h.v1, NC, 0, NC, out_wave);
+    }
     if (h.async) {
       hipLaunchKernelGGL(stats_finish_kernel, dim3(1), dim3(1), 0, h.stream, h.dstats,
                          (const int *)(h.dctl + CTL_STATUS), stats);
@@ -1152,14 +1163,10 @@ int pse_constrained_step(pse_handle *hd, double *x, const double *FL, double dt,
     // 1. slip velocities at x_k: pair sums and the wave noise's
     // interpolation only (every spreading of the step runs at the mid-point),
     // so no spreading tile lists here
-    wrap_positions(h, x, h.xw);
-    build_cells(h, h.xw, false);
-    const double *psi = io ? io->psi_real : nullptr;
-    if (!psi) {
-      real_noise(h, seed, step, h.v2);
-      psi = h.v2;
-    }
-    KrylovResult lr = real_sqrt(h, h.xw, psi, h.v0);
+    prepare_positions(h, x, false);
+    if (io && io->psi_real) gather_rows(h, io->psi_real, NC, h.v2);
+    else real_noise(h, seed, step, h.v2);
+    KrylovResult lr = real_sqrt(h, h.xw, h.v2, h.v0);
     st.lanczos_iters = lr.iters;
     st.lanczos_change = lr.resid;
     converged = converged && lr.converged;
@@ -1174,14 +1181,14 @@ int pse_constrained_step(pse_handle *hd, double *x, const double *FL, double dt,
     PSE_LAUNCH_CHECK();
     // 2. mid-point
     hipLaunchKernelGGL(advance_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, h.xw,
-                       slip, NC, 0.5 * dt, n, h.p.box, h.xh, h.def, 0);
+                       slip, NC, 0.5 * dt, n, h.p.box, h.xh, h.def, 0, (const int *)nullptr);
     PSE_LAUNCH_CHECK();
     build_cells(h, h.xh);
     // 3. constraint at the mid-point: M_ES S = -E^B - M_EF F^P
     const CompSet fl = comps_range(0, 6), es = comps_range(6, 11);
     if (FL) {
       hipLaunchKernelGGL(moments_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, FL,
-                         (const double *)nullptr, n, h.v4);
+                         (const double *)nullptr, (const int *)h.order, n, h.v4);
       PSE_LAUNCH_CHECK();
       mobility(h, h.xh, true, true, h.v4, FULL_LAYOUT, fl, h.v5, FULL_LAYOUT, es, false);
     }
@@ -1191,7 +1198,7 @@ int pse_constrained_step(pse_handle *hd, double *x, const double *FL, double dt,
     stresslet_solve(h, h.xh, h.es_b, h.es_x, st, converged);
     // U = U^B + M_UF F^P + M_US S
     hipLaunchKernelGGL(moments_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, FL,
-                       (const double *)h.es_x, n, h.v4);
+                       (const double *)h.es_x, (const int *)h.order, n, h.v4);
     PSE_LAUNCH_CHECK();
     const CompSet u3 = comps_range(0, 3);
     // the right-hand side's product left the forces' (with moment gridding
@@ -1206,15 +1213,12 @@ int pse_constrained_step(pse_handle *hd, double *x, const double *FL, double dt,
     PSE_LAUNCH_CHECK();
     // 4. x_{k+1} = x_k + dt U
     hipLaunchKernelGGL(advance_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, h.xw,
-                       U, 3, dt, n, h.p.box, x, h.def, 1);
+                       U, 3, dt, n, h.p.box, x, h.def, 1, (const int *)h.order);
     PSE_LAUNCH_CHECK();
     if (io) {
-      if (io->slip) PSE_HIP(hipMemcpyAsync(io->slip, slip, NC * n * sizeof(double),
-                                           hipMemcpyDeviceToDevice, h.stream));
-      if (io->stresslet) PSE_HIP(hipMemcpyAsync(io->stresslet, h.es_x, 5 * n * sizeof(double),
-                                                hipMemcpyDeviceToDevice, h.stream));
-      if (io->velocity) PSE_HIP(hipMemcpyAsync(io->velocity, U, 3 * n * sizeof(double),
-                                               hipMemcpyDeviceToDevice, h.stream));
+      if (io->slip) scatter_rows(h, slip, NC, 0, NC, io->slip);
+      if (io->stresslet) scatter_rows(h, h.es_x, 5, 0, 5, io->stresslet);
+      if (io->velocity) scatter_rows(h, U, 3, 0, 3, io->velocity);
     }
     if (h.async) {
       if (dev_step) {
@@ -1251,11 +1255,11 @@ int pse_rpy_apply(pse_handle *hd, const double *x, const double *F, double *U,
   return guarded(hd, [&] {
     Handle &h = hd->h;
     const CompSet u3 = comps_range(0, 3);
-    prepare_positions(h, x, h.xw);
-    mobility(h, h.xw, parts & PSE_REAL, parts & PSE_WAVE, F, RPY_LAYOUT, u3, U, RPY_LAYOUT, u3,
-             false);
-    if (!h.async && check_finite(h, U, (size_t)h.n * 3))
-      throw Error{PSE_ERR_NONFINITE, "non-finite mobility product (non-finite input?)"};
+    prepare_positions(h, x);
+    gather_rows(h, F, 3, h.v4);
+    mobility(h, h.xw, parts & PSE_REAL, parts & PSE_WAVE, h.v4, RPY_LAYOUT, u3, h.v5, RPY_LAYOUT,
+             u3, false);
+    return_rows(h, h.v5, 3, 0, 3, U, !h.async);
   });
 }
 
@@ -1280,13 +1284,11 @@ int pse_rpy_step(pse_handle *hd, double *x, const double *F, double dt, uint64_t
                          h.dctl + CTL_STATUS);
       PSE_LAUNCH_CHECK();
     }
-    prepare_positions(h, x, h.xw);
+    prepare_positions(h, x);
     // (M_r)_UF^(1/2) psi1 by Lanczos on the UF block of the pair sum
-    const double *psi = io ? io->psi_real : nullptr;
-    if (!psi) {
-      real_noise(h, seed, step, h.v2, 3);
-      psi = h.v2;
-    }
+    if (io && io->psi_real) gather_rows(h, io->psi_real, 3, h.v2);
+    else real_noise(h, seed, step, h.v2, 3);
+    const double *psi = h.v2;
     Op A = [&](const double *in, double *o) {
       if (h.mixed) real_apply<float>(h, h.xw, in, RPY_LAYOUT, u3, o, RPY_LAYOUT, u3, false);
       else real_apply<double>(h, h.xw, in, RPY_LAYOUT, u3, o, RPY_LAYOUT, u3, false);
@@ -1302,20 +1304,21 @@ int pse_rpy_step(pse_handle *hd, double *x, const double *F, double dt, uint64_t
     // (M_w)_UF^(1/2) psi2: the wave sampler's velocity rows
     wave_sqrt(h, h.xw, io ? io->psi_wave : nullptr, seed, step, h.v1, u3, RPY_LAYOUT);
     // M_UF F at x_k
-    if (F) mobility(h, h.xw, true, true, F, RPY_LAYOUT, u3, h.v4, RPY_LAYOUT, u3, false);
+    if (F) {
+      gather_rows(h, F, 3, h.es_b);
+      mobility(h, h.xw, true, true, h.es_b, RPY_LAYOUT, u3, h.v4, RPY_LAYOUT, u3, false);
+    }
     double *slip = h.v3, *U = h.v5;
     hipLaunchKernelGGL(rpy_velocity_kernel, dim3(nblocks(3 * n, 256)), dim3(256), 0, h.stream,
                        h.v0, h.v1, F ? (const double *)h.v4 : nullptr,
                        std::sqrt(2.0 * h.p.kT / dt), 3 * n, slip, U);
     PSE_LAUNCH_CHECK();
     hipLaunchKernelGGL(advance_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, h.xw,
-                       U, 3, dt, n, h.p.box, x, h.def, 1);
+                       U, 3, dt, n, h.p.box, x, h.def, 1, (const int *)h.order);
     PSE_LAUNCH_CHECK();
     if (io) {
-      if (io->slip) PSE_HIP(hipMemcpyAsync(io->slip, slip, 3 * n * sizeof(double),
-                                           hipMemcpyDeviceToDevice, h.stream));
-      if (io->velocity) PSE_HIP(hipMemcpyAsync(io->velocity, U, 3 * n * sizeof(double),
-                                               hipMemcpyDeviceToDevice, h.stream));
+      if (io->slip) scatter_rows(h, slip, 3, 0, 3, io->slip);
+      if (io->velocity) scatter_rows(h, U, 3, 0, 3, io->velocity);
     }
     if (h.async) {
       if (dev_step) {
@@ -1393,16 +1396,17 @@ int pse_spread(pse_handle *hd, const double *x, const double *q, int ncomp, doub
   }
   return guarded(hd, [&] {
     Handle &h = hd->h;
-    prepare_positions(h, x, h.xw);
+    prepare_positions(h, x);
+    gather_rows(h, q, ncomp, h.v4);
     const CompSet cs = comps_range(0, ncomp);
     const size_t cnt = (size_t)ncomp * h.ngrid;
     if (h.mixed) {
       float *g = reinterpret_cast<float *>(h.g32.gin);
-      spread<float>(h, h.xw, q, Layout{ncomp, 0}, cs, g);
+      spread<float>(h, h.xw, h.v4, Layout{ncomp, 0}, cs, g);
       to_double<float>(h, g, cnt, out);
     } else {
       double *g = reinterpret_cast<double *>(h.g64.gin);
-      spread<double>(h, h.xw, q, Layout{ncomp, 0}, cs, g);
+      spread<double>(h, h.xw, h.v4, Layout{ncomp, 0}, cs, g);
       to_double<double>(h, g, cnt, out);
     }
     PSE_HIP(hipStreamSynchronize(h.stream));
@@ -1418,18 +1422,19 @@ int pse_interpolate(pse_handle *hd, const double *x, const double *g, int ncomp,
   }
   return guarded(hd, [&] {
     Handle &h = hd->h;
-    prepare_positions(h, x, h.xw);
+    prepare_positions(h, x);
     const CompSet cs = comps_range(0, ncomp);
     const size_t cnt = (size_t)ncomp * h.ngrid;
     if (h.mixed) {
       float *gg = reinterpret_cast<float *>(h.g32.gout);
       from_double<float>(h, g, cnt, gg);
-      interpolate<float>(h, h.xw, gg, cs, out, Layout{ncomp, 0}, false, 1.0);
+      interpolate<float>(h, h.xw, gg, cs, h.v5, Layout{ncomp, 0}, false, 1.0);
     } else {
       double *gg = reinterpret_cast<double *>(h.g64.gout);
       from_double<double>(h, g, cnt, gg);
-      interpolate<double>(h, h.xw, gg, cs, out, Layout{ncomp, 0}, false, 1.0);
+      interpolate<double>(h, h.xw, gg, cs, h.v5, Layout{ncomp, 0}, false, 1.0);
     }
+    scatter_rows(h, h.v5, ncomp, 0, ncomp, out);
     PSE_HIP(hipStreamSynchronize(h.stream));
   });
 }

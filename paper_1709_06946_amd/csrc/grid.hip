@@ -1309,12 +1309,13 @@ kspace_deformed_kernel(const cplx<T> *__restrict__ in, CompSet cin, cplx<T> *__r
 
 // Real-space noise psi1 ~ N(0, I), 11 per particle, from Philox.
 __global__ void real_noise_kernel(uint64_t seed, uint64_t counter, int64_t n, int ncomp,
-                                  double *__restrict__ out, const uint64_t *counter_dev) {
+                                  const int *__restrict__ order, double *__restrict__ out,
+                                  const uint64_t *counter_dev) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   if (counter_dev) counter = *counter_dev;
   double z[12];
-  philox_normals(seed, counter, STREAM_REAL, (uint32_t)i, 3, z);
+  philox_normals(seed, counter, STREAM_REAL, (uint32_t)order[i], 3, z);
   for (int c = 0; c < ncomp; ++c) out[i * ncomp + c] = z[c];
 }
 
@@ -1922,7 +1923,7 @@ void kspace_noise(Handle &h, const double *psi, uint64_t seed, uint64_t counter,
 
 void real_noise(Handle &h, uint64_t seed, uint64_t counter, double *out, int ncomp) {
   hipLaunchKernelGGL(real_noise_kernel, dim3(nblocks(h.n, 256)), dim3(256), 0,
-                     h.stream, seed, counter, h.n, ncomp, out, h.counter_dev);
+                     h.stream, seed, counter, h.n, ncomp, (const int *)h.order, out, h.counter_dev);
   PSE_LAUNCH_CHECK();
 }
 

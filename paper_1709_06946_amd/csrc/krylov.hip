@@ -215,11 +215,6 @@ __global__ void scatter_kernel(const double *__restrict__ src, CompSet cs,
   }
 }
 
-__global__ void finite_kernel(const double *v, size_t n, int *flag) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !isfinite(v[i])) atomicOr(flag, 1);
-}
-
 // ------------------------------------------------------------ host glue --
 
 void vzero(Handle &h, double *v, size_t n) {
@@ -297,18 +292,6 @@ void scatter_comps(Handle &h, const double *src, const CompSet &cs, double *dst,
   hipLaunchKernelGGL(scatter_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, src,
                      cs, dst, dstride, n, accumulate ? 1 : 0, alpha);
   PSE_LAUNCH_CHECK();
-}
-
-int check_finite(Handle &h, const double *v, size_t n) {
-  int *flag = reinterpret_cast<int *>(h.small + h.small_len - 2);
-  PSE_HIP(hipMemsetAsync(flag, 0, sizeof(int), h.stream));
-  hipLaunchKernelGGL(finite_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, v, n,
-                     flag);
-  PSE_LAUNCH_CHECK();
-  int hv = 0;
-  PSE_HIP(hipMemcpyAsync(&hv, flag, sizeof(int), hipMemcpyDeviceToHost, h.stream));
-  PSE_HIP(hipStreamSynchronize(h.stream));
-  return hv;
 }
 
 // ----------------------------------------------------- small dense work --

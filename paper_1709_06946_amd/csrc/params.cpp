@@ -238,6 +238,7 @@ size_t footprint(const pse_params &p, const pse_derived &d) {
   }
   bytes += (2 * (ncell3 + tiles3) + 4 + (ncell3 + tiles3) / 1024 + 16) * sizeof(int)
            + 8 * n * sizeof(int);
+  bytes += n * sizeof(int);   // the library's order of the particles
   bytes += (2 * 3 * n + 6 * NC * n + 5 * 5 * n) * sizeof(double);
   if (d.deriv_gridding == 2) bytes += 6 * n * sizeof(double);
   bytes += 12 * n * sizeof(double);   // packed moments of the pair sums

@@ -104,7 +104,8 @@ struct Bins {
   int *start = nullptr;      // nc^3 + 1: first slot of each bin in perm
   int *count = nullptr;      // nc^3
   int *of = nullptr;         // N: bin of each particle
-  int *slot = nullptr;       // N: arrival slot of the particle within its bin
+  int *slot = nullptr;       // N: arrival slot of the particle within its bin, then
+                             //    the bin of each position of perm
   int *scat = nullptr;       // N: particles by bin, in arrival order
   int *perm = nullptr;       // N: particles ordered by bin, by index within a bin
   int *scan_tmp = nullptr;   // block sums of the scan
@@ -174,6 +175,9 @@ struct Handle {
   int num_cu = 256;          // compute units of the device
 
   // particle work vectors (double, N x 11 each)
+  // (in the library's own order of the call: particle t is the caller's
+  // order[t], see sort_positions)
+  int *order = nullptr;      // N
   double *xw = nullptr;      // wrapped positions N x 3
   double *xh = nullptr;      // mid-point positions N x 3
   double *v0 = nullptr, *v1 = nullptr, *v2 = nullptr, *v3 = nullptr;
@@ -462,15 +466,23 @@ __device__ __forceinline__ int nbr27_slot(int idx, int first, int pre) {
 // ---- real.hip
 void build_tables(Handle &h);
 void exclusive_scan(Handle &h, const int *in, int *out, int *tmp, int n);
-// Cell list and pair list for wrapped positions xw, the spreading bins and
-// tile lists too unless spreading is false (positions where only pair sums
-// and interpolation run).
+// The caller's positions x wrapped and put in the library's order (h.order,
+// h.xw) with their cells; with lists, prepare_positions builds the pair list
+// too, and the spreading bins and tile lists unless spreading is false
+// (positions where only pair sums and interpolation run).
+void sort_positions(Handle &h, const double *x);
+void prepare_positions(Handle &h, const double *x, bool spreading = true);
+// Cells and lists for wrapped positions xw already in the library's order.
 void build_cells(Handle &h, const double *xw, bool spreading = true);
+// dst[t] = src[order[t]], and dst[order[t]] = src[t] for the components
+// [lo, hi) of rows of w numbers (bad: see scatter_rows_kernel).
+void gather_rows(Handle &h, const double *src, int w, double *dst);
+void scatter_rows(Handle &h, const double *src, int w, int lo, int hi, double *dst,
+                  int *bad = nullptr);
 template <typename T>
 void real_apply(Handle &h, const double *x, const double *in, Layout lin,
                 const CompSet &cin, double *out, Layout lout, const CompSet &cout,
                 bool accumulate);
-void wrap_positions(Handle &h, const double *x, double *xw);
 
 // ---- krylov.hip / blas
 void vzero(Handle &h, double *v, size_t n);
@@ -491,7 +503,6 @@ void gather_comps(Handle &h, const double *src, int sstride, const CompSet &cs,
 void scatter_comps(Handle &h, const double *src, const CompSet &cs,
                    double *dst, int dstride, size_t n, bool accumulate,
                    double alpha);
-int check_finite(Handle &h, const double *v, size_t n);
 
 struct KrylovResult {
   int iters;
@@ -515,7 +526,8 @@ void gmres_dev(Handle &h, const Op &A, const double *b, size_t n, double *x, int
 
 // ---- grid.hip (noise)
 // N x ncomp standard normals (the first ncomp of each particle's Philox
-// draws, so the F components agree for every ncomp).
+// draws, so the F components agree for every ncomp), keyed by the caller's
+// index of each particle.
 void real_noise(Handle &h, uint64_t seed, uint64_t counter, double *out, int ncomp = NC);
 
 inline CompSet comps_range(int lo, int hi) {
