@@ -331,8 +331,8 @@ static void mobility(Handle &h, const double *xw, bool want_real, bool want_wave
   const bool f32 = h.mixed && !fp64;
   bool acc = false;
   if (want_real) {
-    if (f32) real_apply<float>(h, xw, in, lin, cin, out, lout, cout, false);
-    else real_apply<double>(h, xw, in, lin, cin, out, lout, cout, false);
+    if (f32) real_apply<float>(h, xw, in, lin, cin, out, lout, cout);
+    else real_apply<double>(h, xw, in, lin, cin, out, lout, cout);
     acc = true;
   }
   if (want_wave) {
@@ -387,8 +387,8 @@ static void wave_sqrt(Handle &h, const double *xw, const double *psi, uint64_t s
 static KrylovResult real_sqrt(Handle &h, const double *xw, const double *psi, double *out) {
   const CompSet all = comps_range(0, NC);
   Op A = [&](const double *in, double *o) {
-    if (h.mixed) real_apply<float>(h, xw, in, FULL_LAYOUT, all, o, FULL_LAYOUT, all, false);
-    else real_apply<double>(h, xw, in, FULL_LAYOUT, all, o, FULL_LAYOUT, all, false);
+    if (h.mixed) real_apply<float>(h, xw, in, FULL_LAYOUT, all, o, FULL_LAYOUT, all);
+    else real_apply<double>(h, xw, in, FULL_LAYOUT, all, o, FULL_LAYOUT, all);
   };
   if (h.async) {
     lanczos_sqrt_dev(h, A, psi, (size_t)h.n * NC, out, h.lz_cap, h.d.lanczos_tol);
@@ -496,13 +496,11 @@ static void run_graphed(Handle &h, const void *in, const void *out, int kind, F 
 // S = P y, so its residual is the residual of M_ES S = b itself.  One
 // real-space pair sum per application, in the precision of the operator.
 static void es_precond(Handle &h, const double *xh, const double *v, double *out, bool fp64) {
-  const size_t n5 = (size_t)h.n * 5;
   const Layout l5{5, 6};
-  const CompSet es = comps_range(6, 11);
-  if (h.mixed && !fp64) real_apply<float>(h, xh, v, l5, es, out, l5, es, false);
-  else real_apply<double>(h, xh, v, l5, es, out, l5, es, false);
   const double a0 = h.es_self_total;
-  vaxpby(h, (1.0 + h.es_self_real / a0) / a0, v, -1.0 / (a0 * a0), out, n5);
+  const double alpha = (1.0 + h.es_self_real / a0) / a0, beta = -1.0 / (a0 * a0);
+  if (h.mixed && !fp64) real_es<float>(h, xh, v, l5, out, l5, alpha, beta);
+  else real_es<double>(h, xh, v, l5, out, l5, alpha, beta);
 }
 
 static void stresslet_solve(Handle &h, const double *xh, const double *b, double *S,
@@ -1290,8 +1288,8 @@ int pse_rpy_step(pse_handle *hd, double *x, const double *F, double dt, uint64_t
     else real_noise(h, seed, step, h.v2, 3);
     const double *psi = h.v2;
     Op A = [&](const double *in, double *o) {
-      if (h.mixed) real_apply<float>(h, h.xw, in, RPY_LAYOUT, u3, o, RPY_LAYOUT, u3, false);
-      else real_apply<double>(h, h.xw, in, RPY_LAYOUT, u3, o, RPY_LAYOUT, u3, false);
+      if (h.mixed) real_apply<float>(h, h.xw, in, RPY_LAYOUT, u3, o, RPY_LAYOUT, u3);
+      else real_apply<double>(h, h.xw, in, RPY_LAYOUT, u3, o, RPY_LAYOUT, u3);
     };
     KrylovResult lr{0, 0.0, true};
     if (h.async)

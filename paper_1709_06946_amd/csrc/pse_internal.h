@@ -393,7 +393,7 @@ inline size_t pair_entry_bytes(bool mixed) {
 inline size_t pair_capacity(const pse_params &p, const pse_derived &d) {
   const double dens = (double)p.n / (p.box * p.box * p.box);
   const double nb = 4.18879020478639098 * d.rcut * d.rcut * d.rcut * dens;
-  return (size_t)(2.0 * nb * (double)p.n) + 1024;
+  return ((size_t)(2.0 * nb * (double)p.n) + 1024 + 15) / 16 * 16;   // whole record blocks
 }
 
 // Most spreading tiles (S^3 points) one P-point stencil can meet.
@@ -481,8 +481,11 @@ void scatter_rows(Handle &h, const double *src, int w, int lo, int hi, double *d
                   int *bad = nullptr);
 template <typename T>
 void real_apply(Handle &h, const double *x, const double *in, Layout lin,
-                const CompSet &cin, double *out, Layout lout, const CompSet &cout,
-                bool accumulate);
+                const CompSet &cin, double *out, Layout lout, const CompSet &cout);
+// out = alpha in + beta M_r,ES in on the stresslet / strain components
+template <typename T>
+void real_es(Handle &h, const double *x, const double *in, Layout lin, double *out, Layout lout,
+             double alpha, double beta);
 
 // ---- krylov.hip / blas
 void vzero(Handle &h, double *v, size_t n);

@@ -564,10 +564,21 @@ __device__ __forceinline__ void pair_action(const T *co, const T *e, const T *F,
   }
 }
 
-// The moments of the particles packed for the pair sums: 12 numbers per
-// particle in the sum's precision, (F, L, s1..s5, 0), components absent
-// from the input mask zero, so that a neighbour's moments take three
-// 16-byte loads (FP32) or six (FP64) instead of one load per component.
+// Where a pair sum reads the partners' moments: the vector's own rows (double,
+// component c of particle j at v[j stride + c - off]), or (PACK) a packed copy
+// in the sum's precision, 12 numbers a particle (F, L, s1..s5, 0) read as
+// three 16-byte loads (FP32; FP64 six).  The copy costs a launch, which few
+// particles do not repay (N = 2*10^4, FP64: 29 + 5 us with it, 24 without).  A
+// copy by component instead, whose loads touch fewer cache lines, was slower
+// (N = 10^6, FP32, 11 components: 536 against 409 us).
+template <typename T> struct Moments {
+  const double *v;
+  Layout l;
+  const T *packed;
+};
+
+constexpr int64_t PACK_MIN = 32768;
+
 template <typename T>
 __global__ void __launch_bounds__(256)
 pack_moments_kernel(const double *__restrict__ in, Layout lin, int mask, int64_t n,
@@ -580,29 +591,52 @@ pack_moments_kernel(const double *__restrict__ in, Layout lin, int mask, int64_t
   out[t] = (c < NC && (mask & grp)) ? (T)in[p * lin.stride + c - lin.off] : (T)0;
 }
 
-template <typename T>
-__device__ __forceinline__ void load_packed(const T *__restrict__ m, int mask, T *F,
-                                            T (*C)[3]) {
+// Force F and couplet C (force index first) of particle j; groups absent
+// from the mask are zero and not read.
+template <typename T, bool PACK>
+__device__ __forceinline__ void load_moments(const Moments<T> &m, int j, int mask, T *F,
+                                             T (*C)[3]) {
   T v[12];
-  if constexpr (sizeof(T) == 4) {
-    const float4 *m4 = reinterpret_cast<const float4 *>(m);
+  if constexpr (PACK) {
+    const T *q = m.packed + (size_t)j * 12;
+    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float4 a = m4[k];
-      v[4 * k] = a.x; v[4 * k + 1] = a.y; v[4 * k + 2] = a.z; v[4 * k + 3] = a.w;
+      for (int k = 0; k < 3; ++k) {
+        const float4 a = reinterpret_cast<const float4 *>(q)[k];
+        v[4 * k] = a.x; v[4 * k + 1] = a.y; v[4 * k + 2] = a.z; v[4 * k + 3] = a.w;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const double2 a = reinterpret_cast<const double2 *>(q)[k];
+        v[2 * k] = a.x; v[2 * k + 1] = a.y;
+      }
     }
   } else {
-    const double2 *m2 = reinterpret_cast<const double2 *>(m);
+    const double *q = m.v + (size_t)j * m.l.stride - m.l.off;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const double2 a = m2[k];
-      v[2 * k] = a.x; v[2 * k + 1] = a.y;
+    for (int k = 0; k < NC; ++k) v[k] = (T)0;
+    if (mask == 7) {
+#pragma unroll
+      for (int k = 0; k < NC; ++k) v[k] = (T)q[k];
+    } else {
+      if (mask & 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] = (T)q[k];
+      if (mask & 2)
+#pragma unroll
+        for (int k = 3; k < 6; ++k) v[k] = (T)q[k];
+      if (mask & 4)
+#pragma unroll
+        for (int k = 6; k < NC; ++k) v[k] = (T)q[k];
     }
   }
   const T r2 = (T)0.70710678118654752440, r6 = (T)0.40824829046386301637;
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
     F[i] = v[i];
-    for (int j = 0; j < 3; ++j) C[i][j] = (T)0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) C[i][k] = (T)0;
   }
   if (mask & 2) {
     // C^A_mn = -1/2 eps_mnk L_k
@@ -612,13 +646,13 @@ __device__ __forceinline__ void load_packed(const T *__restrict__ m, int mask, T
     C[1][2] -= (T)0.5 * Lx; C[2][1] += (T)0.5 * Lx;
   }
   if (mask & 4) {
-    const T s1 = v[6], s2 = v[7], s3 = v[8], s4 = v[9], s5 = v[10];
-    C[0][1] += r2 * s1; C[1][0] += r2 * s1;
-    C[0][2] += r2 * s2; C[2][0] += r2 * s2;
-    C[1][2] += r2 * s3; C[2][1] += r2 * s3;
-    C[0][0] += r2 * s4 + r6 * s5;
-    C[1][1] += -r2 * s4 + r6 * s5;
-    C[2][2] += (T)(-2) * r6 * s5;
+    const T *q = v + 6;
+    C[0][1] += r2 * q[0]; C[1][0] += r2 * q[0];
+    C[0][2] += r2 * q[1]; C[2][0] += r2 * q[1];
+    C[1][2] += r2 * q[2]; C[2][1] += r2 * q[2];
+    C[0][0] += r2 * q[3] + r6 * q[4];
+    C[1][1] += -r2 * q[3] + r6 * q[4];
+    C[2][2] += (T)(-2) * r6 * q[4];
   }
 }
 
@@ -626,10 +660,25 @@ __device__ __forceinline__ void load_packed(const T *__restrict__ m, int mask, T
 // would leave most of the chip idle for N ~ 1e4.
 constexpr int GROUP = 16;
 
+// A group is one row of the wavefront, summed by rotations within it (an
+// add per step instead of a shuffle through LDS); every lane gets the sum.
+static_assert(GROUP == 16, "rows of 16 lanes");
+template <int R> __device__ __forceinline__ float row_rotate(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + R, 0xf, 0xf, true));
+}
+template <int R> __device__ __forceinline__ double row_rotate(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + R, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + R, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
 template <typename T>
 __device__ __forceinline__ T group_sum(T v) {
-#pragma unroll
-  for (int off = GROUP / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, GROUP);
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
   return v;
 }
 
@@ -645,7 +694,24 @@ __device__ __forceinline__ T group_sum(T v) {
 // FP32 sums).  A sum in the other precision (the FP64 residual of a mixed
 // handle, once per step) forms the data from the positions itself.
 
-constexpr int PAIR_REC = 10;   // co[7], e[3]
+// Records lie in blocks of REC_BLOCK entries, field by field within a block: a
+// lane reaches every field of its entry from one address, and the six fields
+// of the stresslet-strain sum are one contiguous run of a block (2*10^5
+// spheres, 111 neighbours each, FP32: 349 -> 305 us for the whole sum, 213 ->
+// 190 for that block, against one array per field; FP64 at 2*10^4: 26 -> 24).
+constexpr int PAIR_REC = 10;
+constexpr int REC_BLOCK = 16;
+// fields: d2 d3 d4, the unit vector, a b, c1 c2 (see the list of radial
+// coefficients above)
+enum { F_D2 = 0, F_D3, F_D4, F_E, F_A = F_E + 3, F_B, F_C1, F_C2 };
+
+// Entry s of the records: field f at [f].
+template <typename R> struct Entry {
+  R *p;
+  __device__ __forceinline__ Entry(R *rec, uint32_t s)
+      : p(rec + (size_t)(s / REC_BLOCK) * (PAIR_REC * REC_BLOCK) + s % REC_BLOCK) {}
+  __device__ __forceinline__ R &operator[](int f) const { return p[f * REC_BLOCK]; }
+};
 
 struct PairArgs {
   int64_t n;
@@ -747,21 +813,22 @@ pair_list_kernel(const double *__restrict__ xw, const int *__restrict__ perm,
       if (ok) {
         nbr[slot] = j;
         if (rec64 || rec32) {
-          // field-major: field k of entry s at rec[k * cap + s]; the unit
-          // vector now, the distance in field 0 for pair_coef_kernel (the
-          // table interpolation runs there on every lane, not on the few
-          // lanes of a candidate batch that found a neighbour)
+          // the unit vector now, the distance in field d2 for
+          // pair_coef_kernel (the table interpolation runs there on every
+          // lane, not on the few lanes of a candidate batch that found a
+          // neighbour)
           const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
           const double inv = r > 0 ? 1.0 / r : 0.0;
-          const size_t cap = (size_t)pa.cap;
           if (rec64) {
-            rec64[slot] = r;
+            const Entry<double> p(rec64, slot);
+            p[F_D2] = r;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) rec64[(NCOEF + k) * cap + slot] = d[k] * inv;
+            for (int k = 0; k < 3; ++k) p[F_E + k] = d[k] * inv;
           } else {
-            rec32[slot] = (float)r;
+            const Entry<float> p(rec32, slot);
+            p[F_D2] = (float)r;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) rec32[(NCOEF + k) * cap + slot] = (float)(d[k] * inv);
+            for (int k = 0; k < 3; ++k) p[F_E + k] = (float)(d[k] * inv);
           }
         }
       }
@@ -776,7 +843,7 @@ pair_list_kernel(const double *__restrict__ xw, const int *__restrict__ perm,
 }
 
 // The seven radial coefficients of every stored pair, interpolated from the
-// table at the distance the fill left in field 0 (entries up to the list's
+// table at the distance the fill left in field d2 (entries up to the list's
 // length, read on the device, and its capacity).
 // In the records' precision, from the table of that precision.
 template <typename R>
@@ -787,17 +854,18 @@ pair_coef_kernel(R *__restrict__ rec, const int *__restrict__ total, int64_t cap
   const int64_t len = min((int64_t)total[0], cap);
   if (s >= len) return;
   R co[NCOEF];
-  lookup<R>(tab, rec[s], (R)inv_dr, n2a, ntab, co);
+  const Entry<R> p(rec, (uint32_t)s);
+  lookup<R>(tab, p[F_D2], (R)inv_dr, n2a, ntab, co);
+  constexpr int field[NCOEF] = {F_A, F_B, F_C1, F_C2, F_D2, F_D3, F_D4};
 #pragma unroll
-  for (int k = 0; k < NCOEF; ++k) rec[(size_t)k * cap + s] = co[k];
+  for (int k = 0; k < NCOEF; ++k) p[field[k]] = co[k];
 }
 
 struct RealArgs {
   int64_t n;
   int in_mask;    // 1: F, 2: L, 4: S
   int out_mask;   // 1: U, 2: Omega, 4: E
-  int accumulate;
-  Layout lin, lout;
+  Layout lout;
   int64_t cap;    // pair-list capacity (entries beyond it were never written)
   double L;       // box; deformed lattice: separations mapped by A
   int def;
@@ -806,14 +874,30 @@ struct RealArgs {
   int n2a, ntab;
 };
 
+// The data of one pair formed from the positions (lists without records in
+// this precision).
+template <typename T>
+__device__ __forceinline__ void pair_data(const double *__restrict__ xw, double xi0, double xi1,
+                                          double xi2, int j, const RealArgs &ra,
+                                          const T *__restrict__ tab, T *co, T *e) {
+  double d[3];
+  separation(xw, xi0, xi1, xi2, j, ra.L, ra.def, ra.A, d);
+  const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+  const double inv = r > 0 ? 1.0 / r : 0.0;
+  lookup<T>(tab, (T)r, (T)ra.inv_dr, ra.n2a, ra.ntab, co);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) e[k] = (T)(d[k] * inv);
+}
+
 // M_r applied from the pair list: the self block (r = 0: only the isotropic
 // coefficients, table row 0) plus one pair block per stored neighbour.
 // UF, UC: forces / couplets among the inputs; OU, OD: velocity / gradient
 // outputs (from ra's masks); a stored entry's fields are read only when one
-// of the selected couplings uses them.
-template <typename T, bool UF, bool UC, bool OU, bool OD>
+// of the selected couplings uses them.  REC: the list holds records in this
+// precision (else the pair data are formed from the positions).
+template <typename T, bool REC, bool PACK, bool UF, bool UC, bool OU, bool OD>
 __global__ void __launch_bounds__(256)
-real_pair_kernel(const double *__restrict__ xw, const T *__restrict__ in,
+real_pair_kernel(const double *__restrict__ xw, Moments<T> in,
                  double *__restrict__ out, const int *__restrict__ perm,
                  const int *__restrict__ start, const int *__restrict__ nbr,
                  const T *__restrict__ rec, const T *__restrict__ tab, RealArgs ra) {
@@ -829,43 +913,62 @@ real_pair_kernel(const double *__restrict__ xw, const T *__restrict__ in,
     T co[NCOEF];
     for (int j = 0; j < NCOEF; ++j) co[j] = tab[j];
     const T e0[3] = {0, 0, 0};
-    load_packed<T>(in + (size_t)i * 12, ra.in_mask, F, C);
+    load_moments<T, PACK>(in, i, ra.in_mask, F, C);
     pair_action<T, UF, UC, OU, OD>(co, e0, F, C, U, D);
   }
   constexpr bool NEED_AB = UF && OU, NEED_C12 = (UF && OD) || (UC && OU), NEED_D = UC && OD;
   const int s1 = (int)min((int64_t)start[t + 1], ra.cap);
-  const double xi0 = xw[3 * i], xi1 = xw[3 * i + 1], xi2 = xw[3 * i + 2];
-  const size_t cap = (size_t)ra.cap;
-  for (int s = start[t] + lane; s < s1; s += GROUP) {
-    const int j = nbr[s];
-    T co[NCOEF] = {}, e[3];
-    if (rec) {
-      if constexpr (NEED_AB) {
-        co[0] = rec[s];
-        co[1] = rec[cap + s];
-      }
-      if constexpr (NEED_C12) {
-        co[2] = rec[2 * cap + s];
-        co[3] = rec[3 * cap + s];
-      }
-      if constexpr (NEED_D) {
-        co[4] = rec[4 * cap + s];
-        co[5] = rec[5 * cap + s];
-        co[6] = rec[6 * cap + s];
-      }
-#pragma unroll
-      for (int k = 0; k < 3; ++k) e[k] = rec[(NCOEF + k) * cap + s];
-    } else {
-      double d[3];
-      separation(xw, xi0, xi1, xi2, j, ra.L, ra.def, ra.A, d);
-      const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-      const double inv = r > 0 ? 1.0 / r : 0.0;
-      lookup<T>(tab, (T)r, (T)ra.inv_dr, ra.n2a, ra.ntab, co);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) e[k] = (T)(d[k] * inv);
+  const auto record = [&](int s, T *co, T *e) {
+    const Entry<const T> p(rec, (uint32_t)s);
+    if constexpr (NEED_AB) {
+      co[0] = p[F_A];
+      co[1] = p[F_B];
     }
-    load_packed<T>(in + (size_t)j * 12, ra.in_mask, F, C);
-    pair_action<T, UF, UC, OU, OD>(co, e, F, C, U, D);
+    if constexpr (NEED_C12) {
+      co[2] = p[F_C1];
+      co[3] = p[F_C2];
+    }
+    if constexpr (NEED_D) {
+      co[4] = p[F_D2];
+      co[5] = p[F_D3];
+      co[6] = p[F_D4];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) e[k] = p[F_E + k];
+  };
+  int s = start[t] + lane;
+  if constexpr (REC) {
+    // the next entry's index and record are in flight while the current
+    // neighbour's moments arrive
+    int jn = 0;
+    T con[NCOEF] = {}, en[3] = {};
+    if (s < s1) {
+      jn = nbr[s];
+      record(s, con, en);
+    }
+    for (; s < s1; s += GROUP) {
+      const int j = jn;
+      T co[NCOEF], e[3];
+#pragma unroll
+      for (int k = 0; k < NCOEF; ++k) co[k] = con[k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) e[k] = en[k];
+      load_moments<T, PACK>(in, j, ra.in_mask, F, C);
+      if (s + GROUP < s1) {
+        jn = nbr[s + GROUP];
+        record(s + GROUP, con, en);
+      }
+      pair_action<T, UF, UC, OU, OD>(co, e, F, C, U, D);
+    }
+  } else {
+    const double xi0 = xw[3 * i], xi1 = xw[3 * i + 1], xi2 = xw[3 * i + 2];
+    for (; s < s1; s += GROUP) {
+      const int j = nbr[s];
+      T co[NCOEF], e[3];
+      pair_data<T>(xw, xi0, xi1, xi2, j, ra, tab, co, e);
+      load_moments<T, PACK>(in, j, ra.in_mask, F, C);
+      pair_action<T, UF, UC, OU, OD>(co, e, F, C, U, D);
+    }
   }
   if constexpr (OU)
 #pragma unroll
@@ -881,21 +984,122 @@ real_pair_kernel(const double *__restrict__ xw, const T *__restrict__ in,
   auto O = [&](int c) -> double & { return out[row + c - ra.lout.off]; };
   const double r2 = 0.70710678118654752440, r6 = 0.40824829046386301637;
   if (ra.out_mask & 1) {
-    for (int k = 0; k < 3; ++k) O(k) = (ra.accumulate ? O(k) : 0.0) + (double)U[k];
+    for (int k = 0; k < 3; ++k) O(k) = (double)U[k];
   }
   if (ra.out_mask & 2) {
     // Omega = -1/2 eps : D
     const double om[3] = {-0.5 * ((double)D[1][2] - D[2][1]),
                           -0.5 * ((double)D[2][0] - D[0][2]),
                           -0.5 * ((double)D[0][1] - D[1][0])};
-    for (int k = 0; k < 3; ++k) O(3 + k) = (ra.accumulate ? O(3 + k) : 0.0) + om[k];
+    for (int k = 0; k < 3; ++k) O(3 + k) = om[k];
   }
   if (ra.out_mask & 4) {
     const double e5[5] = {r2 * ((double)D[0][1] + D[1][0]), r2 * ((double)D[0][2] + D[2][0]),
                           r2 * ((double)D[1][2] + D[2][1]), r2 * ((double)D[0][0] - D[1][1]),
                           r6 * ((double)D[0][0] + D[1][1] - 2.0 * D[2][2])};
-    for (int k = 0; k < 5; ++k) O(6 + k) = (ra.accumulate ? O(6 + k) : 0.0) + e5[k];
+    for (int k = 0; k < 5; ++k) O(6 + k) = e5[k];
   }
+}
+
+// The stresslet-strain block of M_r alone (the constraint operator and its
+// preconditioner): out = alpha in + beta M_r,ES in.  Stresslets and strains
+// are symmetric and traceless, so with S the partner's stresslet, w = S e and
+// x = e.w the pair action of pair_action<T, false, true, false, true>
+// reduces, in the Y_q components, to
+//   E_q = -9 [ f s_q + Y_q : (e m + m e) ],   m = (d4/2) x e + h w,
+//   f = -3 d2 - d3,  h = -(3 d3 + d4) / 2:
+// five numbers in and out instead of nine, read from the vectors' own rows.
+// Bound by the records, 28 bytes a pair (FP32) read once, and the arithmetic
+// per neighbour; the next entry's record is in flight while the current
+// neighbour's stresslet arrives.  N = 10^6, 28 neighbours: 276 + 36 (a packed
+// copy) -> 235 us; 2*10^5, 111 neighbours: 239 + 7 -> 190 us; 10^4 in FP64:
+// 9.4 + 4.2 -> 6.4 us.
+template <typename T>
+__device__ __forceinline__ void es_action(T d2, T d3, T d4, const T *e, const T *s, T *acc) {
+  const T r2 = (T)0.70710678118654752440, r6 = (T)0.40824829046386301637;
+  const T xy = r2 * s[0], xz = r2 * s[1], yz = r2 * s[2], a = r2 * s[3], b = r6 * s[4];
+  const T w[3] = {(b + a) * e[0] + xy * e[1] + xz * e[2], xy * e[0] + (b - a) * e[1] + yz * e[2],
+                  xz * e[0] + yz * e[1] - (T)2 * b * e[2]};
+  const T x = e[0] * w[0] + e[1] * w[1] + e[2] * w[2];
+  const T f = (T)-3 * d2 - d3, h = (T)-1.5 * d3 - (T)0.5 * d4, g = (T)0.5 * d4 * x;
+  T m[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) m[k] = g * e[k] + h * w[k];
+  const T c2 = (T)2 * r2, c6 = (T)2 * r6;
+  const T xx = e[0] * m[0], yy = e[1] * m[1], zz = e[2] * m[2];
+  acc[0] += f * s[0] + c2 * (e[0] * m[1] + e[1] * m[0]);
+  acc[1] += f * s[1] + c2 * (e[0] * m[2] + e[2] * m[0]);
+  acc[2] += f * s[2] + c2 * (e[1] * m[2] + e[2] * m[1]);
+  acc[3] += f * s[3] + c2 * (xx - yy);
+  acc[4] += f * s[4] + c6 * (xx + yy - (T)2 * zz);
+}
+
+template <typename T, bool REC>
+__global__ void __launch_bounds__(256)
+es_pair_kernel(const double *__restrict__ xw, const double *__restrict__ in, Layout lin,
+               double *__restrict__ out, const int *__restrict__ perm,
+               const int *__restrict__ start, const int *__restrict__ nbr,
+               const T *__restrict__ rec, const T *__restrict__ tab, RealArgs ra, double alpha,
+               double beta) {
+  const int64_t t =
+      ((int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) / GROUP;
+  const int lane = threadIdx.x % GROUP;
+  if (t >= ra.n) return;
+  const int i = perm[t];
+  const int s1 = (int)min((int64_t)start[t + 1], ra.cap);
+  T acc[5] = {}, m[5], e[3];
+  const double *in6 = in + 6 - lin.off;
+  const auto moments = [&](int j) {
+    const double *q = in6 + (size_t)j * lin.stride;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) m[k] = (T)q[k];
+  };
+  int s = start[t] + lane;
+  if constexpr (REC) {
+    int jn = 0;
+    T rn[6] = {};
+    const auto record = [&](int p) {
+      const Entry<const T> q(rec, (uint32_t)p);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) rn[k] = q[k];
+    };
+    if (s < s1) {
+      jn = nbr[s];
+      record(s);
+    }
+    for (; s < s1; s += GROUP) {
+      moments(jn);
+      const T d2 = rn[0], d3 = rn[1], d4 = rn[2];
+      e[0] = rn[3];
+      e[1] = rn[4];
+      e[2] = rn[5];
+      if (s + GROUP < s1) {
+        jn = nbr[s + GROUP];
+        record(s + GROUP);
+      }
+      es_action(d2, d3, d4, e, m, acc);
+    }
+  } else {
+    const double xi0 = xw[3 * i], xi1 = xw[3 * i + 1], xi2 = xw[3 * i + 2];
+    for (; s < s1; s += GROUP) {
+      const int j = nbr[s];
+      T co[NCOEF];
+      pair_data<T>(xw, xi0, xi1, xi2, j, ra, tab, co, e);
+      moments(j);
+      es_action(co[4], co[5], co[6], e, m, acc);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 5; ++k) acc[k] = group_sum(acc[k]);
+  if (lane >= 5) return;
+  // lane k finishes component k; the self block is f s at r = 0
+  T a = acc[0];
+#pragma unroll
+  for (int k = 1; k < 5; ++k) a = lane == k ? acc[k] : a;
+  const double v = in[(size_t)i * lin.stride + 6 - lin.off + lane];
+  const T f = (T)-3 * tab[4] - tab[5];
+  out[(size_t)i * ra.lout.stride + 6 - ra.lout.off + lane] =
+      alpha * v + beta * (double)((T)-9 * (a + f * (T)v));
 }
 
 // Second half of the pair-list fill: the coefficients of the stored pairs
@@ -967,7 +1171,7 @@ static void build_pair_list(Handle &h, const double *xw) {
     clear_graphs(h);   // captured real-space launches hold the old buffers
     const size_t cap = (size_t)total + total / 4 + 1024;
     pair_storage(h, cap, false);
-    pa.cap = (int64_t)cap;
+    pa.cap = (int64_t)h.pl_cap;
   }
   h.pl_pairs = (size_t)total;
   hipLaunchKernelGGL((pair_list_kernel<true>), dim3(nb), dim3(256), 0, h.stream, xw,
@@ -991,6 +1195,7 @@ void pair_storage(Handle &h, size_t cap, bool at_create) {
     if (at_create) handle_alloc(h, ptr, bytes);
     else dev_alloc(ptr, bytes);
   };
+  cap = (cap + REC_BLOCK - 1) / REC_BLOCK * REC_BLOCK;   // whole blocks
   alloc((void **)&h.pl_nbr, cap * sizeof(int));
   if (h.mixed) alloc((void **)&h.pl_rec32, cap * PAIR_REC * sizeof(float));
   else alloc((void **)&h.pl_rec64, cap * PAIR_REC * sizeof(double));
@@ -1084,26 +1289,21 @@ void scatter_rows(Handle &h, const double *src, int w, int lo, int hi, double *d
   PSE_LAUNCH_CHECK();
 }
 
-static int mask_of(const CompSet &cs, bool input) {
+static int mask_of(const CompSet &cs) {
   int m = 0;
   for (int k = 0; k < cs.n; ++k) {
     const int c = cs.idx[k];
     m |= c < 3 ? 1 : (c < 6 ? 2 : 4);
   }
-  (void)input;
   return m;
 }
 
-template <typename T>
-void real_apply(Handle &h, const double *xw, const double *in, Layout lin, const CompSet &cin,
-                double *out, Layout lout, const CompSet &cout, bool accumulate) {
+static RealArgs real_args(const Handle &h, int in_mask, Layout lout, int out_mask) {
   RealArgs ra;
   ra.n = h.n;
-  ra.lin = lin;
   ra.lout = lout;
-  ra.in_mask = mask_of(cin, true);
-  ra.out_mask = mask_of(cout, false);
-  ra.accumulate = accumulate ? 1 : 0;
+  ra.in_mask = in_mask;
+  ra.out_mask = out_mask;
   ra.cap = (int64_t)h.pl_cap;
   ra.L = h.p.box;
   ra.def = h.def.on;
@@ -1111,7 +1311,10 @@ void real_apply(Handle &h, const double *xw, const double *in, Layout lin, const
   ra.inv_dr = 1.0 / h.dr;
   ra.n2a = h.n2a;
   ra.ntab = h.ntab;
-  const T *tab, *rec;
+  return ra;
+}
+
+template <typename T> static void real_data(const Handle &h, const T *&tab, const T *&rec) {
   if constexpr (sizeof(T) == 8) {
     tab = h.g64.table;
     rec = h.pl_rec64;
@@ -1119,20 +1322,71 @@ void real_apply(Handle &h, const double *xw, const double *in, Layout lin, const
     tab = h.g32.table;
     rec = h.pl_rec32;
   }
+}
+
+// f(true_type) where the list holds records of T; FP32 sums run on mixed
+// handles only, whose records are FP32.
+template <typename T, typename F> static void with_records(const T *rec, F f) {
+  if constexpr (sizeof(T) == 8) {
+    if (rec) f(std::true_type());
+    else f(std::false_type());
+  } else {
+    if (!rec) throw Error{PSE_ERR_INVALID, "pair records missing"};
+    f(std::true_type());
+  }
+}
+
+template <typename T>
+void real_es(Handle &h, const double *xw, const double *in, Layout lin, double *out, Layout lout,
+             double alpha, double beta) {
+  const T *tab, *rec;
+  real_data<T>(h, tab, rec);
+  ProfScope ps(h, PK_REAL, (double)h.pl_pairs * (4.0 + (rec ? 6 * sizeof(T) : 0)) +
+                               (double)h.n * (5 * 8 * 2 + 8));
+  with_records<T>(rec, [&](auto R) {
+    hipLaunchKernelGGL((es_pair_kernel<T, decltype(R)::value>),
+                       dim3(nblocks((size_t)h.n * GROUP, 256)), dim3(256), 0, h.stream, xw, in,
+                       lin, out, h.cells.perm, h.pl_start, h.pl_nbr, rec, tab,
+                       real_args(h, 4, lout, 4), alpha, beta);
+  });
+  PSE_LAUNCH_CHECK();
+}
+
+template <typename T>
+void real_apply(Handle &h, const double *xw, const double *in, Layout lin, const CompSet &cin,
+                double *out, Layout lout, const CompSet &cout) {
+  const RealArgs ra = real_args(h, mask_of(cin), lout, mask_of(cout));
+  if (ra.in_mask == 4 && ra.out_mask == 4) {
+    real_es<T>(h, xw, in, lin, out, lout, 0.0, 1.0);
+    return;
+  }
+  const T *tab, *rec;
+  real_data<T>(h, tab, rec);
   ProfScope ps(h, PK_REAL, (double)h.pl_pairs * (4.0 + (rec ? PAIR_REC * sizeof(T) : 0)) +
                                (double)h.n * (NC * 8 * 2 + 8 + 24));
   const bool uf = ra.in_mask & 1, uc = (ra.in_mask & 6) != 0;
   const bool ou = ra.out_mask & 1, od = (ra.out_mask & 6) != 0;
-  T *mp = reinterpret_cast<T *>(h.mpack);
-  hipLaunchKernelGGL(pack_moments_kernel<T>, dim3(nblocks((size_t)h.n * 12, 256)), dim3(256),
-                     0, h.stream, in, lin, ra.in_mask, h.n, mp);
-  PSE_LAUNCH_CHECK();
+  Moments<T> m{in, lin, nullptr};
+  if (h.n >= PACK_MIN) {
+    T *mp = reinterpret_cast<T *>(h.mpack);
+    hipLaunchKernelGGL(pack_moments_kernel<T>, dim3(nblocks((size_t)h.n * 12, 256)), dim3(256),
+                       0, h.stream, in, lin, ra.in_mask, h.n, mp);
+    PSE_LAUNCH_CHECK();
+    m.packed = mp;
+  }
   const dim3 grid(nblocks((size_t)h.n * GROUP, 256)), block(256);
   const auto launch = [&](auto UF, auto UC, auto OU, auto OD) {
-    hipLaunchKernelGGL((real_pair_kernel<T, decltype(UF)::value, decltype(UC)::value,
-                                         decltype(OU)::value, decltype(OD)::value>),
-                       grid, block, 0, h.stream, xw, (const T *)mp, out, h.cells.perm,
-                       h.pl_start, h.pl_nbr, rec, tab, ra);
+    with_records<T>(rec, [&](auto R) {
+      const auto go = [&](auto P) {
+        hipLaunchKernelGGL((real_pair_kernel<T, decltype(R)::value, decltype(P)::value,
+                                             decltype(UF)::value, decltype(UC)::value,
+                                             decltype(OU)::value, decltype(OD)::value>),
+                           grid, block, 0, h.stream, xw, m, out, h.cells.perm, h.pl_start,
+                           h.pl_nbr, rec, tab, ra);
+      };
+      if (m.packed) go(std::true_type());
+      else go(std::false_type());
+    });
   };
   using Y = std::true_type;
   using N = std::false_type;
@@ -1152,9 +1406,13 @@ void real_apply(Handle &h, const double *xw, const double *in, Layout lin, const
   PSE_LAUNCH_CHECK();
 }
 
+template void real_es<double>(Handle &, const double *, const double *, Layout, double *, Layout,
+                              double, double);
+template void real_es<float>(Handle &, const double *, const double *, Layout, double *, Layout,
+                             double, double);
 template void real_apply<double>(Handle &, const double *, const double *, Layout,
-                                 const CompSet &, double *, Layout, const CompSet &, bool);
+                                 const CompSet &, double *, Layout, const CompSet &);
 template void real_apply<float>(Handle &, const double *, const double *, Layout,
-                                const CompSet &, double *, Layout, const CompSet &, bool);
+                                const CompSet &, double *, Layout, const CompSet &);
 
 }  // namespace pse
