@@ -522,10 +522,10 @@ static void stresslet_solve(Handle &h, const double *xh, const double *b, double
       });
     });
   };
-  // S = P y in place (y in v, tmp a scratch vector)
-  auto unprecondition = [&](double *v) {
-    es_precond(h, xh, v, h.es_p, !h.mixed);
-    vcopy(h, v, h.es_p, n5);
+  // the correction y of a pass to S: S = P y, or S += P y after the first
+  auto correct = [&](int pass) {
+    es_precond(h, xh, h.es_d, pass ? h.es_p : S, false);
+    if (pass) vaxpby(h, 1.0, h.es_p, 1.0, S, n5);
   };
   if (h.async) {
     // device-checked: GMRES of exactly gmres_maxit iterations; mixed handles
@@ -533,24 +533,21 @@ static void stresslet_solve(Handle &h, const double *xh, const double *b, double
     // FP64 residual (statistics on the device)
     const int K = h.gm_cap;
     if (!h.mixed) {
-      gmres_dev(h, make_op(true, true), b, n5, S, K, h.d.gmres_tol);
-      unprecondition(S);
+      gmres_dev(h, make_op(true, true), b, n5, h.es_d, K, h.d.gmres_tol);
+      es_precond(h, xh, h.es_d, S, true);
       hipLaunchKernelGGL(gmres_as_fp64_kernel, dim3(1), dim3(1), 0, h.stream, h.dstats);
       PSE_LAUNCH_CHECK();
       return;
     }
     Op A32 = make_op(false, true), A64 = make_op(true, false);
     double *b2 = h.small + h.small_len - 4, *r2 = b2 + 1;
-    vzero(h, S, n5);
-    vcopy(h, h.es_r, b, n5);
-    multi_dot(h, b, n5, 1, b, n5, b2);
+    norm2_dev(h, b, n5, b2);
     for (int pass = 0; pass < h.ref_cap; ++pass) {
-      gmres_dev(h, A32, h.es_r, n5, h.es_d, K, h.d.gmres_tol);
-      unprecondition(h.es_d);
-      vaxpby(h, 1.0, h.es_d, 1.0, S, n5);
+      gmres_dev(h, A32, pass ? h.es_r : b, n5, h.es_d, K, h.d.gmres_tol);
+      correct(pass);
       A64(S, h.es_r);
       vaxpby(h, 1.0, b, -1.0, h.es_r, n5);
-      multi_dot(h, h.es_r, n5, 1, h.es_r, n5, r2);
+      norm2_dev(h, h.es_r, n5, r2);
       hipLaunchKernelGGL(refine_stats_kernel, dim3(1), dim3(1), 0, h.stream,
                          (const double *)b2, (const double *)r2, pass,
                          pass + 1 == h.ref_cap ? 1 : 0, h.d.gmres_tol, h.dstats);
@@ -559,9 +556,9 @@ static void stresslet_solve(Handle &h, const double *xh, const double *b, double
     return;
   }
   if (!h.mixed) {
-    KrylovResult r = gmres(h, make_op(true, true), b, n5, S, h.d.gmres_restart,
+    KrylovResult r = gmres(h, make_op(true, true), b, n5, h.es_d, h.d.gmres_restart,
                            h.d.gmres_maxit, h.d.gmres_tol, &h.gm_prev[0]);
-    unprecondition(S);
+    es_precond(h, xh, h.es_d, S, true);   // S = P y
     st.gmres_iters += r.iters;
     st.gmres_residual = r.resid;
     st.fp64_residual = r.resid;
@@ -569,34 +566,28 @@ static void stresslet_solve(Handle &h, const double *xh, const double *b, double
     return;
   }
   Op A32 = make_op(false, true), A64 = make_op(true, false);
-  vzero(h, S, n5);
-  vcopy(h, h.es_r, b, n5);
-  double bnorm2 = 0.0;
-  {
-    double *tmp = h.small + h.small_len - 4;
-    multi_dot(h, b, n5, 1, b, n5, tmp);
-    PSE_HIP(hipMemcpyAsync(&bnorm2, tmp, sizeof(double), hipMemcpyDeviceToHost, h.stream));
-    PSE_HIP(hipStreamSynchronize(h.stream));
-  }
-  const double bnorm = std::sqrt(bnorm2);
-  if (!(bnorm > 0)) {
-    st.fp64_residual = 0.0;
-    return;
-  }
+  double bnorm = 0.0;
   bool ok = false;
   for (int pass = 0; pass < h.d.refine_passes; ++pass) {
-    KrylovResult r = gmres(h, A32, h.es_r, n5, h.es_d, h.d.gmres_restart, h.d.gmres_maxit,
-                           h.d.gmres_tol, pass == 0 ? &h.gm_prev[1] : nullptr);
+    KrylovResult r = gmres(h, A32, pass ? h.es_r : b, n5, h.es_d, h.d.gmres_restart,
+                           h.d.gmres_maxit, h.d.gmres_tol, pass == 0 ? &h.gm_prev[1] : nullptr);
+    if (pass == 0) {
+      bnorm = r.bnorm;
+      if (!(bnorm > 0)) {
+        vzero(h, S, n5);
+        st.fp64_residual = 0.0;
+        return;
+      }
+    }
     st.gmres_iters += r.iters;
     st.gmres_residual = r.resid;
     st.refine_passes = pass + 1;
-    unprecondition(h.es_d);
-    vaxpby(h, 1.0, h.es_d, 1.0, S, n5);
+    correct(pass);
     A64(S, h.es_r);
     vaxpby(h, 1.0, b, -1.0, h.es_r, n5);
     double rn2 = 0.0;
     double *tmp = h.small + h.small_len - 4;
-    multi_dot(h, h.es_r, n5, 1, h.es_r, n5, tmp);
+    norm2_dev(h, h.es_r, n5, tmp);
     PSE_HIP(hipMemcpyAsync(&rn2, tmp, sizeof(double), hipMemcpyDeviceToHost, h.stream));
     PSE_HIP(hipStreamSynchronize(h.stream));
     st.fp64_residual = std::sqrt(rn2) / bnorm;
@@ -669,6 +660,19 @@ void dev_free(void *p) {
   if (!p) return;
   std::unique_lock<std::shared_mutex> lk(capture_gate());
   (void)hipFree(p);
+}
+
+void *host_alloc(size_t bytes) {
+  std::unique_lock<std::shared_mutex> lk(capture_gate());
+  void *p = nullptr;
+  PSE_HIP(hipHostMalloc(&p, bytes));
+  return p;
+}
+
+void host_free(void *p) {
+  if (!p) return;
+  std::unique_lock<std::shared_mutex> lk(capture_gate());
+  (void)hipHostFree(p);
 }
 
 hipError_t dev_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind) {
@@ -798,10 +802,11 @@ static void create(const pse_params &p, Handle &h) {
   handle_alloc(h, (void **)&h.lz_V, (size_t)(h.d.lanczos_maxit + 1) * NC * n * sizeof(double));
   handle_alloc(h, (void **)&h.gm_V, (size_t)(h.d.gmres_restart + 1) * 5 * n * sizeof(double));
   const size_t M = h.d.lanczos_maxit, R = h.d.gmres_restart;
-  h.small_len = std::max((M + 1) * 10 + (M + 3) * (M + 1), (R + 1) * (R + 1) + 8 * (R + 2)) + 64;
+  h.small_len = std::max((M + 1) * 11 + (M + 3) * (M + 1), (R + 1) * (R + 1) + 8 * (R + 2)) + 64;
   handle_alloc(h, (void **)&h.small, h.small_len * sizeof(double));
   h.dots_len = 1024 * (std::max(M, R) + 2);
   handle_alloc(h, (void **)&h.dots, h.dots_len * sizeof(double));
+  if (!h.arena) h.kry = (double *)host_alloc((2 * (std::max(M, R) + 2) + 2) * sizeof(double));
   handle_alloc(h, (void **)&h.dctl, CTL_WORDS * sizeof(int));
   handle_alloc(h, (void **)&h.dstats, sizeof(pse_stats));
   handle_alloc(h, (void **)&h.dstep, sizeof(uint64_t));
@@ -832,6 +837,7 @@ static void release(Handle &h) {
                   h.dg_mu, h.mpack, h.kdg, h.kdg32};
   if (!h.arena)
     for (void *p : ptrs) dev_free(p);
+  host_free(h.kry);
   clear_graphs(h);
   for (hipEvent_t e : h.prof.pool) (void)hipEventDestroy(e);
   h.prof.pool.clear();

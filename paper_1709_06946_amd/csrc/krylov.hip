@@ -1,26 +1,21 @@
 // FP64 vector kernels and small dense solvers of the Krylov iterations:
 // the Lanczos square root of M_r (Sec. III.B, Chow & Saad) and GMRES on the
 // stresslet constraint M_ES S = b (Eq. rigidconstraint).  All scalars stay
-// on the device; the host only reads a few numbers back per iteration to
-// decide when to stop.
+// on the device; kernels also write the few numbers that decide when to stop
+// to host memory, which the host reads after waiting for the stream.
+#include <algorithm>
 #include <cmath>
-#include <vector>
+#include <type_traits>
 
 #include "pse_internal.h"
 
 namespace pse {
 
 constexpr int RED_BLOCKS = 1024;   // partial-sum blocks of a reduction
-constexpr int MAX_DOTS = 128;      // dot products of one fused subtraction pass
 
 __global__ void zero_kernel_d(double *v, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) v[i] = 0.0;
-}
-
-__global__ void fill_kernel_d(double *v, size_t n, double value) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) v[i] = value;
 }
 
 __global__ void fill_kernel_i(int *v, size_t n, int value) {
@@ -28,150 +23,466 @@ __global__ void fill_kernel_i(int *v, size_t n, int value) {
   if (i < n) v[i] = value;
 }
 
-__global__ void copy_kernel_d(double *dst, const double *src, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
-
 __global__ void axpby_kernel(double a, const double *x, double b, double *y, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = a * x[i] + b * y[i];
 }
 
-// Sum over a 256-thread block: within each wave by shuffles, then the four
-// wave sums in a fixed order (valid in thread 0).
-__device__ __forceinline__ double block_sum256(double v, double *s4) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+__device__ __forceinline__ double lane_d(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
 }
 
-// partial[j * nb + blk] = sum over the block's share of V_j . w
+// Sum over a wavefront (every lane gets it; all lanes active): rotations
+// within the rows of 16 lanes, then the four rows' sums (shuffles go through
+// LDS, six of them one after the other).
+template <int R> __device__ __forceinline__ double row_rotated(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + R, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + R, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += row_rotated<8>(v);
+  v += row_rotated<4>(v);
+  v += row_rotated<2>(v);
+  v += row_rotated<1>(v);
+  return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
+}
+
+// One Gram-Schmidt step of a Krylov method (two classical passes, CGS2) takes
+// w = V_m against V_0..V_{m-1}:
+//   h1_j = V_j . w;  w -= sum_j h1_j V_j;
+//   h2_j = V_j . w (j < m), h2_m = w . w;
+//   w = (w - sum_j h2_j V_j) / nn,  nn = sqrt(h2_m - |h2_0..m-1|^2)
+// and gives the method its column (Column below).  Three kernels -- dots, sub
+// and dots, finish -- whose sums go from one to the next as block partials.
+// How a step is launched depends on the vectors' length n alone (plan_of):
+//  * ONE: one workgroup does the whole step (krylov_one_kernel).  A launch
+//    takes 5 to 7 us of the stream whatever it does, and vectors this short
+//    are read in less (n = 1100: one launch of 7 us instead of six of 2 to 6;
+//    at n = 7655 it takes 25 us against 14 for the three).
+//  * FEW: the three kernels on at most 64 workgroups, so that each consumer
+//    adds up the 64 partials of a sum itself, one per lane (n = 110000: 20 us
+//    a step against 32 with the sums in launches of their own).
+//  * MANY: up to 1024 workgroups for the bandwidth, the partials added up by
+//    launches of their own (each consumer reading 1024 of them would cost
+//    more than the launch).
+struct Plan {
+  enum Kind { ONE, FEW, MANY } kind;
+  int nb;   // workgroups of a sum
+};
+
+constexpr size_t ONE_MAX = 2048;
+constexpr size_t FEW_MAX = size_t(1) << 18;
+
+static Plan plan_of(size_t n) {
+  const int nb = std::max(1, (int)std::min<size_t>(RED_BLOCKS, (n + 255) / 256));
+  if (n <= ONE_MAX) return {Plan::ONE, 1};
+  if (n <= FEW_MAX) return {Plan::FEW, std::min(nb, 64)};
+  return {Plan::MANY, nb};
+}
+
+// h[j] = the sum of the nb <= 64 partials of sum j < cnt, by the block's
+// wavefronts.
+__device__ __forceinline__ void sum_partials(const double *__restrict__ partial, int nb, int cnt,
+                                             double *h) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  for (int j = wv; j < cnt; j += nw) {
+    const double v = wave_sum(lane < nb ? partial[(size_t)j * nb + lane] : 0.0);
+    if (lane == 0) h[j] = v;
+  }
+}
+
+// Sums of NW wavefronts' accumulators: acc[k] into out[k], k < cnt <= 8
+// (s: NW x 8 doubles; all threads call it, with a barrier after).
+template <int NW>
+__device__ __forceinline__ void block_sums8(const double *acc, int cnt, double (*s)[8],
+                                            double *out, int stride) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    if (k >= cnt) break;
+    const double v = wave_sum(acc[k]);
+    if (lane == 0) s[wv][k] = v;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < cnt) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v += s[w][threadIdx.x];
+    out[(size_t)threadIdx.x * stride] = v;
+  }
+  __syncthreads();
+}
+
+// f(integral_constant<int, k>) for k = cnt in 1..8: loops over a fixed number
+// of vectors, so that all loads of an element are issued together.
+template <typename F> __device__ __forceinline__ void fixed_count(int cnt, F f) {
+  switch (cnt) {
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    case 5: f(std::integral_constant<int, 5>()); break;
+    case 6: f(std::integral_constant<int, 6>()); break;
+    case 7: f(std::integral_constant<int, 7>()); break;
+    default: f(std::integral_constant<int, 8>()); break;
+  }
+}
+
+// w = (w - sum_{j<m} coef_j V_j) f over this thread's elements.
+__device__ __forceinline__ void sub_of(double *w, const double *V, size_t ldv, int m,
+                                       const double *coef, double f, size_t n, size_t i0,
+                                       size_t step) {
+  for (int j0 = 0; j0 < m; j0 += 8) {
+    const int cnt = min(8, m - j0);
+    const double *v0 = V + (size_t)j0 * ldv;
+    const double fk = j0 + 8 >= m ? f : 1.0;
+    fixed_count(cnt, [&](auto c) {
+      constexpr int K = decltype(c)::value;
+      double cf[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) cf[k] = coef[j0 + k];
+#pragma unroll 4
+      for (size_t i = i0; i < n; i += step) {
+        double v[K], a = w[i];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = v0[(size_t)k * ldv + i];
+#pragma unroll
+        for (int k = 0; k < K; ++k) a -= cf[k] * v[k];
+        w[i] = a * fk;
+      }
+    });
+  }
+}
+
+// Dots of w with V_0..V_{m-1} over this thread's elements i0, i0 + step, ...:
+// eight vectors at a time, so w is read once per eight.
+template <int NW>
+__device__ __forceinline__ void dots_of(const double *V, size_t ldv, int m, const double *w,
+                                        size_t n, size_t i0, size_t step, double (*s)[8],
+                                        double *out, int stride) {
+  for (int j0 = 0; j0 < m; j0 += 8) {
+    const int cnt = min(8, m - j0);
+    double acc[8] = {};
+    const double *v0 = V + (size_t)j0 * ldv;
+    fixed_count(cnt, [&](auto c) {
+      constexpr int K = decltype(c)::value;
+#pragma unroll 4
+      for (size_t i = i0; i < n; i += step) {
+        const double wi = w[i];
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[k] += v0[(size_t)k * ldv + i] * wi;
+      }
+    });
+    block_sums8<NW>(acc, cnt, s, out + (size_t)j0 * stride, stride);
+  }
+}
+
+// w -= sum_{j<m} coef_j V_j (coef in LDS), then the dots of the new w with
+// V_0..V_{m-1} and itself.  Up to seven vectors every element is visited
+// once; more take a pass for the update and one per eight dots.
+template <int NW>
+__device__ __forceinline__ void sub_dots_of(double *w, const double *V, size_t ldv, int m,
+                                            const double *coef, size_t n, size_t i0, size_t step,
+                                            double (*s)[8], double *out, int stride) {
+  if (m <= 7) {
+    double acc[8] = {};
+    fixed_count(m, [&](auto c) {
+      constexpr int K = decltype(c)::value < 8 ? decltype(c)::value : 7;
+      double cf[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) cf[k] = coef[k];
+#pragma unroll 4
+      for (size_t i = i0; i < n; i += step) {
+        double v[K], wn = w[i];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = V[(size_t)k * ldv + i];
+#pragma unroll
+        for (int k = 0; k < K; ++k) wn -= cf[k] * v[k];
+        w[i] = wn;
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[k] += v[k] * wn;
+        acc[K] += wn * wn;
+      }
+    });
+    block_sums8<NW>(acc, m + 1, s, out, stride);
+    return;
+  }
+  sub_of(w, V, ldv, m, coef, 1.0, n, i0, step);
+  // V_m is w itself
+  dots_of<NW>(V, ldv, m + 1, w, n, i0, step, s, out, stride);
+}
+
+// Where a Krylov column goes.  GMRES (H not NULL): H[i][j] = h1_i + h2_i, the
+// previous Givens rotations and a new one, g updated, |g_{j+1}| the residual.
+// Lanczos: alpha_j = h1_j + h2_j and beta_j = nn.  vn_hist and res_hist keep
+// nn and the residual per column on the device; host (may be NULL) is memory
+// the host reads after a synchronisation: nn at [1 + j], the residual at
+// [1 + hcap + j].
+// Device-checked GMRES (sel not NULL): sel[0] is set at the first column whose
+// residual met tol |b| or whose new vector vanished (nn <= 1e-15 |b|), sel[1]
+// = its column count k (0 for b = 0); at the last column (last != 0) without
+// one, k = j + 1 and sel[2] = 1 (not converged).
+struct Column {
+  double *H;
+  int ldh;
+  double *cs, *sn, *g, *res_hist;
+  double *alpha, *beta;
+  double *vn_hist;
+  double *host;
+  int hcap;
+  int *sel;
+  const double *bn;
+  double tol;
+  int last;
+};
+
+// One wavefront forms column j from h1[0..j] and h2[0..j+1] (LDS) and nn; cl,
+// cs_l, sn_l: LDS scratch of j + 1 doubles each.
+__device__ __forceinline__ void finish_column(const Column &c, int j, const double *h1,
+                                              const double *h2, double nn, double *cl,
+                                              double *cs_l, double *sn_l) {
+  const int lane = threadIdx.x & 63;
+  if (!c.H) {
+    if (lane != 0) return;
+    c.alpha[j] = h1[j] + h2[j];
+    c.beta[j] = nn;
+    c.vn_hist[j] = nn;
+    if (c.host) c.host[1 + j] = nn;
+    return;
+  }
+  for (int i = lane; i <= j; i += 64) cl[i] = h1[i] + h2[i];
+  for (int i = lane; i < j; i += 64) {
+    cs_l[i] = c.cs[i];
+    sn_l[i] = c.sn[i];
+  }
+  // one wavefront: its LDS accesses are in order
+  __builtin_amdgcn_wave_barrier();
+  if (lane != 0) return;
+  double *col = c.H + (size_t)j * c.ldh;
+  double a = cl[0];
+  for (int i = 0; i < j; ++i) {   // (cl[j] is the column's last entry)
+    const double b = cl[i + 1];
+    col[i] = cs_l[i] * a + sn_l[i] * b;
+    a = -sn_l[i] * a + cs_l[i] * b;
+  }
+  const double r = hypot(a, nn);
+  const double cn = r > 0 ? a / r : 1.0, sj = r > 0 ? nn / r : 0.0;
+  c.cs[j] = cn;
+  c.sn[j] = sj;
+  col[j] = r;
+  col[j + 1] = 0.0;
+  const double gj = c.g[j], gn = -sj * gj, res = fabs(gn);
+  c.g[j + 1] = gn;
+  c.g[j] = cn * gj;
+  c.vn_hist[j] = nn;
+  c.res_hist[j] = res;
+  if (c.host) {
+    c.host[1 + j] = nn;
+    c.host[1 + c.hcap + j] = res;
+  }
+  if (!c.sel || c.sel[0]) return;
+  const double bn = *c.bn;
+  const bool done = res < c.tol * bn || nn <= 1e-15 * bn;
+  if (done || c.last) {
+    c.sel[0] = 1;
+    c.sel[1] = bn > 0.0 ? j + 1 : 0;
+    c.sel[2] = done ? 0 : 1;
+  }
+}
+
+// nn of the twice-orthogonalised w from h2[0..m] (LDS), by every wavefront.
+__device__ __forceinline__ double new_norm(const double *h2, int m) {
+  double p2 = 0.0;
+  for (int i = threadIdx.x & 63; i < m; i += 64) p2 += h2[i] * h2[i];
+  return sqrt(fmax(h2[m] - wave_sum(p2), 0.0));
+}
+
+// FEW and MANY: the first pass's dots, partial[j nb + blk].
 __global__ void __launch_bounds__(256)
-multi_dot_partial(const double *__restrict__ V, size_t ldv, const double *__restrict__ w,
-                  size_t n, double *__restrict__ partial) {
-  __shared__ double s[4];
-  const int j = blockIdx.y;
-  const double *v = V + (size_t)j * ldv;
-  double acc = 0.0;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
-    acc += v[i] * w[i];
-  acc = block_sum256(acc, s);
-  if (threadIdx.x == 0) partial[(size_t)j * gridDim.x + blockIdx.x] = acc;
+dots_kernel(const double *V, size_t ldv, int m, const double *w, size_t n,
+            double *__restrict__ partial) {
+  __shared__ double s[4][8];
+  dots_of<4>(V, ldv, m, w, n, (size_t)blockIdx.x * 256 + threadIdx.x, (size_t)gridDim.x * 256, s,
+             partial + blockIdx.x, gridDim.x);
 }
 
 __global__ void __launch_bounds__(256)
 reduce_partial(const double *__restrict__ partial, int nb, double *__restrict__ out) {
-  __shared__ double s[4];
-  const int j = blockIdx.x;
+  __shared__ double s[4][8];
   double acc = 0.0;
-  for (int b = threadIdx.x; b < nb; b += 256) acc += partial[(size_t)j * nb + b];
-  acc = block_sum256(acc, s);
-  if (threadIdx.x == 0) out[j] = acc;
+  for (int b = threadIdx.x; b < nb; b += 256) acc += partial[(size_t)blockIdx.x * nb + b];
+  block_sums8<4>(&acc, 1, s, out + blockIdx.x, 1);
 }
 
-// The second Gram-Schmidt pass's subtraction fused with the dot products
-// that follow it: w -= sum_{j<m} coef_j V_j, then partial[j nb + blk] =
-// V_j . w for j <= m over the block's share (V_m is w itself, so the last
-// entry is w . w).  Each thread updates and then reads back only its own
-// elements, in the grid-stride order of multi_dot_partial, so the sums are
-// those of a separate subtraction and multi_dot_partial bit for bit.
+// The first pass's subtraction and the second pass's dots; nb1 > 0: h1 from
+// nb1 partials each (kept in h1 by the first workgroup), else h1 given.
 __global__ void __launch_bounds__(256)
-sub_dot_partial(double *w, const double *V, size_t ldv, int m, const double *__restrict__ coef,
-                size_t n, double *__restrict__ partial) {
-  __shared__ double s[4][MAX_DOTS];
-  const int nb = gridDim.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)nb * 256;
-  for (size_t i = i0; i < n; i += step) {
-    double acc = 0.0;
-    for (int j = 0; j < m; ++j) acc += coef[j] * V[(size_t)j * ldv + i];
-    w[i] -= acc;
-  }
-#pragma unroll 4
-  for (int j = 0; j <= m; ++j) {
-    const double *v = V + (size_t)j * ldv;
-    double acc = 0.0;
-    for (size_t i = i0; i < n; i += step) acc += v[i] * w[i];
+sub_dots_kernel(double *w, const double *V, size_t ldv, int m, size_t n,
+                const double *__restrict__ partial1, int nb1, double *__restrict__ h1,
+                double *__restrict__ partial2) {
+  __shared__ double s[4][8];
+  extern __shared__ double h[];   // m
+  if (nb1 > 0) sum_partials(partial1, nb1, m, h);
+  else
+    for (int j = threadIdx.x; j < m; j += 256) h[j] = h1[j];
+  __syncthreads();
+  if (nb1 > 0 && blockIdx.x == 0)
+    for (int j = threadIdx.x; j < m; j += 256) h1[j] = h[j];
+  sub_dots_of<4>(w, V, ldv, m, h, n, (size_t)blockIdx.x * 256 + threadIdx.x,
+                 (size_t)gridDim.x * 256, s, partial2 + blockIdx.x, gridDim.x);
+}
+
+// The second subtraction, the scaling and (first workgroup) the column;
+// nb2 > 0: h2 from nb2 partials each, else h2 given.
+__global__ void __launch_bounds__(256)
+finish_kernel(double *w, const double *V, size_t ldv, int m, size_t n,
+              const double *__restrict__ h1, const double *__restrict__ partial2, int nb2,
+              const double *__restrict__ h2, Column c) {
+  extern __shared__ double h[];   // m + 1, then four times m + 1
+  double *h1l = h + m + 1, *cl = h1l + m + 1, *cs = cl + m + 1, *sn = cs + m + 1;
+  if (nb2 > 0) sum_partials(partial2, nb2, m + 1, h);
+  else
+    for (int j = threadIdx.x; j <= m; j += 256) h[j] = h2[j];
+  __syncthreads();
+  const double nn = new_norm(h, m), f = nn > 0.0 ? 1.0 / nn : 0.0;
+  sub_of(w, V, ldv, m, h, f, n, (size_t)blockIdx.x * 256 + threadIdx.x,
+         (size_t)gridDim.x * 256);
+  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
+  for (int j = threadIdx.x; j < m; j += 64) h1l[j] = h1[j];
+  __builtin_amdgcn_wave_barrier();
+  finish_column(c, m - 1, h1l, h, nn, cl, cs, sn);
+}
+
+// ONE: the whole step by one workgroup, w and up to eight vectors in
+// registers (a thread holds ONE_E elements of each), more vectors read in
+// chunks of eight for each phase.  A launch is one short chain -- two rounds of
+// sums between barriers -- so the sums go over few wavefronts and the code is
+// small (a version with loops unrolled per vector count spent its time
+// fetching instructions).
+constexpr int ONE_T = 512, ONE_E = (int)(ONE_MAX / ONE_T);
+static_assert(ONE_E * ONE_T == ONE_MAX, "elements per thread");
+
+__global__ void __launch_bounds__(ONE_T)
+krylov_one_kernel(double *w, const double *V, size_t ldv, int m, int n, Column c) {
+  __shared__ double s[ONE_T / 64][9];
+  extern __shared__ double h1[];   // five times m + 1
+  double *h2 = h1 + m + 1, *cl = h2 + m + 1, *cs = cl + m + 1, *sn = cs + m + 1;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double x[ONE_E], v[8][ONE_E];
+  const auto load = [&](int j0) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) s[wv][j] = acc;
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+      for (int e = 0; e < ONE_E; ++e) {
+        const int i = tid + e * ONE_T;
+        v[k][e] = (j0 + k < m && i < n) ? V[(size_t)(j0 + k) * ldv + i] : 0.0;
+      }
+  };
+  // sums of the chunk's dots (and x . x with the last chunk) into out[j0 ..]
+  const auto sums = [&](int j0, double *out, bool norm) {
+    double a[9];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      a[k] = 0.0;
+#pragma unroll
+      for (int e = 0; e < ONE_E; ++e) a[k] += v[k][e] * x[e];
+      a[k] = wave_sum(a[k]);
+    }
+    a[8] = 0.0;
+    if (norm) {
+#pragma unroll
+      for (int e = 0; e < ONE_E; ++e) a[8] += x[e] * x[e];
+      a[8] = wave_sum(a[8]);
+    }
+    if (lane == 0)
+#pragma unroll
+      for (int k = 0; k < 9; ++k) s[wv][k] = a[k];
+    __syncthreads();
+    if (tid < 9) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < ONE_T / 64; ++k) t += s[k][tid];
+      if (tid < 8 && j0 + tid < m) out[j0 + tid] = t;
+      if (tid == 8 && norm) out[m] = t;
+    }
+    __syncthreads();
+  };
+  const auto subtract = [&](int j0, const double *h) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const double hk = j0 + k < m ? h[j0 + k] : 0.0;
+#pragma unroll
+      for (int e = 0; e < ONE_E; ++e) x[e] -= hk * v[k][e];
+    }
+  };
+#pragma unroll
+  for (int e = 0; e < ONE_E; ++e) {
+    const int i = tid + e * ONE_T;
+    x[e] = i < n ? w[i] : 0.0;
+  }
+  const bool hold = m <= 8;
+  if (hold) load(0);
+  for (int j0 = 0; j0 < m; j0 += 8) {
+    if (!hold) load(j0);
+    sums(j0, h1, false);
+  }
+  for (int j0 = 0; j0 < m; j0 += 8) {
+    if (!hold) load(j0);
+    subtract(j0, h1);
+  }
+  for (int j0 = 0; j0 < m; j0 += 8) {
+    if (!hold) load(j0);
+    sums(j0, h2, j0 + 8 >= m);
+  }
+  for (int j0 = 0; j0 < m; j0 += 8) {
+    if (!hold) load(j0);
+    subtract(j0, h2);
+  }
+  const double nn = new_norm(h2, m), f = nn > 0.0 ? 1.0 / nn : 0.0;
+#pragma unroll
+  for (int e = 0; e < ONE_E; ++e) {
+    const int i = tid + e * ONE_T;
+    if (i < n) w[i] = x[e] * f;
+  }
+  if (tid < 64) finish_column(c, m - 1, h1, h2, nn, cl, cs, sn);
+}
+
+// The start of a solve: bn = |b|, v = b / bn (0 for b = 0; v may be b), g =
+// (bn, 0, ...) and, when given, clear0 and clear1 (len numbers) and sel (3)
+// cleared.  nb > 0: |b|^2 from nb <= 64 partials; 0: given in norm2; -1:
+// formed here (one workgroup).
+__global__ void __launch_bounds__(1024)
+krylov_start_kernel(const double *b, double *v, size_t n,
+                    const double *__restrict__ partial, int nb, const double *norm2,
+                    double *__restrict__ bn_out, double *__restrict__ g, int glen,
+                    double *__restrict__ clear0, double *__restrict__ clear1, int len,
+                    int *__restrict__ sel, double *__restrict__ host) {
+  __shared__ double s[16][8];
+  __shared__ double b2;
+  if (nb > 0) sum_partials(partial, nb, 1, &b2);
+  else if (nb == 0) {
+    if (threadIdx.x == 0) b2 = norm2[0];
+  } else {
+    double acc = 0.0;
+    for (size_t i = threadIdx.x; i < n; i += blockDim.x) acc += b[i] * b[i];
+    block_sums8<16>(&acc, 1, s, &b2, 1);
   }
   __syncthreads();
-  for (int j = threadIdx.x; j <= m; j += 256)
-    partial[(size_t)j * nb + blockIdx.x] = (s[0][j] + s[1][j]) + (s[2][j] + s[3][j]);
-}
-
-// The same in one pass over the elements when m + 1 <= SDF: a thread loads
-// V_0..V_{m-1} at each of its elements once, subtracts, stores w and adds
-// the products into the m + 1 sums from the loaded values, so each vector
-// is read once instead of twice.  The per-thread order of every sum and the
-// reduction are those of sub_dot_partial, so the results agree bit for bit.
-constexpr int SDF = 8;
-
-__global__ void __launch_bounds__(256)
-sub_dot_partial1(double *w, const double *V, size_t ldv, int m, const double *__restrict__ coef,
-                 size_t n, double *__restrict__ partial) {
-  __shared__ double s[4][SDF];
-  const int nb = gridDim.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)nb * 256;
-  double cf[SDF - 1], acc[SDF];
-#pragma unroll
-  for (int j = 0; j < SDF - 1; ++j) cf[j] = j < m ? coef[j] : 0.0;
-#pragma unroll
-  for (int j = 0; j < SDF; ++j) acc[j] = 0.0;
-  for (size_t i = i0; i < n; i += step) {
-    double v[SDF - 1];
-#pragma unroll
-    for (int j = 0; j < SDF - 1; ++j) v[j] = j < m ? V[(size_t)j * ldv + i] : 0.0;
-    double a = 0.0;
-#pragma unroll
-    for (int j = 0; j < SDF - 1; ++j)
-      if (j < m) a += cf[j] * v[j];
-    const double wn = w[i] - a;
-    w[i] = wn;
-#pragma unroll
-    for (int j = 0; j < SDF - 1; ++j)
-      if (j < m) acc[j] += v[j] * wn;
-#pragma unroll
-    for (int j = 0; j < SDF; ++j)
-      if (j == m) acc[j] += wn * wn;
+  const double bn = sqrt(fmax(b2, 0.0)), f = bn != 0.0 ? 1.0 / bn : 0.0;
+  const size_t step = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step)
+    v[i] = b[i] * f;
+  if (blockIdx.x != 0) return;
+  if (threadIdx.x == 0) {
+    *bn_out = bn;
+    if (host) host[0] = bn;
   }
-#pragma unroll
-  for (int j = 0; j < SDF; ++j) {
-    if (j > m) break;
-    double a = acc[j];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if (lane == 0) s[wv][j] = a;
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j <= m; j += 256)
-    partial[(size_t)j * nb + blockIdx.x] = (s[0][j] + s[1][j]) + (s[2][j] + s[3][j]);
-}
-
-// w -= sum_j coef_j V_j
-__global__ void sub_multi_kernel(double *__restrict__ w, const double *__restrict__ V,
-                                 size_t ldv, int m, const double *__restrict__ coef,
-                                 size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double acc = 0.0;
-  for (int j = 0; j < m; ++j) acc += coef[j] * V[(size_t)j * ldv + i];
-  w[i] -= acc;
-}
-
-// w = (w - sum_{j<m} coef_j V_j) / s with s a device scalar (0 if s <= 0)
-__global__ void sub_scale_kernel(double *__restrict__ w, const double *__restrict__ V,
-                                 size_t ldv, int m, const double *__restrict__ coef,
-                                 const double *__restrict__ s, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double acc = 0.0;
-  for (int j = 0; j < m; ++j) acc += coef[j] * V[(size_t)j * ldv + i];
-  const double f = s[0] > 0.0 ? 1.0 / s[0] : 0.0;
-  w[i] = (w[i] - acc) * f;
+  for (int i = threadIdx.x; i < glen; i += blockDim.x) g[i] = i == 0 ? bn : 0.0;
+  for (int i = threadIdx.x; i < len; i += blockDim.x) clear0[i] = clear1[i] = 0.0;
+  if (sel && threadIdx.x < 3) sel[threadIdx.x] = 0;
 }
 
 // y = (acc ? y : 0) + alpha sum_j coef_j V_j (m from m_dev when given)
@@ -187,32 +498,44 @@ __global__ void gemv_small_kernel(const double *__restrict__ V, size_t ldv, int 
   y[i] = (accumulate ? y[i] : 0.0) + alpha * acc;
 }
 
-// dst = src * s or src / s with s a device scalar (dst may equal src)
-__global__ void scale_dev_kernel(double *dst, const double *src, const double *s,
-                                 int invert, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double f = invert ? (*s != 0.0 ? 1.0 / *s : 0.0) : *s;
-  dst[i] = src[i] * f;
-}
+// y = (acc ? y : 0) + V c with R c = g, R the k x k upper triangle of the
+// columns H (k from k_dev when given): every workgroup solves the triangle
+// itself (one launch instead of two, and the columns wait in LDS instead of a
+// chain of global loads: 4.6 to 17 us for the solve alone).
+constexpr int TRI_MAX = 48;   // columns staged in LDS
 
-__global__ void gather_kernel(const double *__restrict__ src, int sstride, CompSet cs,
-                              double *__restrict__ dst, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int k = 0; k < cs.n; ++k) dst[i * cs.n + k] = src[i * sstride + cs.idx[k]];
-}
-
-__global__ void scatter_kernel(const double *__restrict__ src, CompSet cs,
-                               double *__restrict__ dst, int dstride, size_t n,
-                               int accumulate, double alpha) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int k = 0; k < cs.n; ++k) {
-    double *o = dst + i * dstride + cs.idx[k];
-    const double v = alpha * src[i * cs.n + k];
-    *o = accumulate ? *o + v : v;
+__global__ void __launch_bounds__(256)
+solve_gemv_kernel(const double *__restrict__ V, size_t ldv, int k, const double *__restrict__ H,
+                  int ldh, const double *__restrict__ g, double *__restrict__ y, size_t n,
+                  int accumulate, const int *__restrict__ k_dev) {
+  __shared__ double R[TRI_MAX * (TRI_MAX + 1) / 2];
+  extern __shared__ double c[];   // the largest k
+  if (k_dev) k = *k_dev;
+  const bool staged = k <= TRI_MAX;
+  if (staged)
+    for (int e = threadIdx.x; e < k * k; e += 256) {
+      const int j = e / k, i = e % k;
+      if (i <= j) R[j * (j + 1) / 2 + i] = H[(size_t)j * ldh + i];
+    }
+  for (int i = threadIdx.x; i < k; i += 256) c[i] = g[i];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    // columns from the last: c_j = g_j / R_jj, then g_i -= R_ij c_j for i < j
+    for (int j = k - 1; j >= 0; --j) {
+      const double *col = staged ? R + j * (j + 1) / 2 : H + (size_t)j * ldh;
+      const double cj = c[j] / col[j];
+      __builtin_amdgcn_wave_barrier();
+      for (int i = threadIdx.x; i < j; i += 64) c[i] -= col[i] * cj;
+      if (threadIdx.x == 0) c[j] = cj;
+      __builtin_amdgcn_wave_barrier();
+    }
   }
+  __syncthreads();
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  double acc = accumulate ? y[i] : 0.0;
+  for (int j = 0; j < k; ++j) acc += c[j] * V[(size_t)j * ldv + i];
+  y[i] = acc;
 }
 
 // ------------------------------------------------------------ host glue --
@@ -227,41 +550,9 @@ void fill_int(Handle &h, int *v, size_t n, int value) {
   PSE_LAUNCH_CHECK();
 }
 
-static void fill_double(Handle &h, double *v, size_t n, double value) {
-  hipLaunchKernelGGL(fill_kernel_d, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, v, n,
-                     value);
-  PSE_LAUNCH_CHECK();
-}
-
-void vcopy(Handle &h, double *dst, const double *src, size_t n) {
-  hipLaunchKernelGGL(copy_kernel_d, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, dst,
-                     src, n);
-  PSE_LAUNCH_CHECK();
-}
 void vaxpby(Handle &h, double a, const double *x, double b, double *y, size_t n) {
   hipLaunchKernelGGL(axpby_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, a, x,
                      b, y, n);
-  PSE_LAUNCH_CHECK();
-}
-
-void multi_dot(Handle &h, const double *V, size_t ldv, int m, const double *w,
-               size_t n, double *dev_out) {
-  int nb = (int)std::min<size_t>(RED_BLOCKS, (n + 255) / 256);
-  if (nb < 1) nb = 1;
-  if ((size_t)nb * m > h.dots_len) throw Error{PSE_ERR_INVALID, "reduction scratch too small"};
-  ProfScope ps(h, PK_KRYLOV, (double)(m + 1) * n * 8);
-  hipLaunchKernelGGL(multi_dot_partial, dim3(nb, m), dim3(256), 0, h.stream, V, ldv, w, n,
-                     h.dots);
-  PSE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(reduce_partial, dim3(m), dim3(256), 0, h.stream, h.dots, nb, dev_out);
-  PSE_LAUNCH_CHECK();
-}
-
-void vsub_multi(Handle &h, double *w, const double *V, size_t ldv, int m,
-                const double *coef_dev, size_t n) {
-  ProfScope ps(h, PK_KRYLOV, (double)(m + 2) * n * 8);
-  hipLaunchKernelGGL(sub_multi_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, w,
-                     V, ldv, m, coef_dev, n);
   PSE_LAUNCH_CHECK();
 }
 
@@ -270,27 +561,6 @@ void gemv_small(Handle &h, const double *V, size_t ldv, int m, const double *coe
   ProfScope ps(h, PK_KRYLOV, (double)(m + 1 + (accumulate ? 1 : 0)) * n * 8);
   hipLaunchKernelGGL(gemv_small_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, V,
                      ldv, m, coef_dev, y, n, alpha, accumulate ? 1 : 0, m_dev);
-  PSE_LAUNCH_CHECK();
-}
-
-void vscale_dev(Handle &h, double *dst, const double *src, const double *s_dev,
-                bool invert, size_t n) {
-  hipLaunchKernelGGL(scale_dev_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream,
-                     dst, src, s_dev, invert ? 1 : 0, n);
-  PSE_LAUNCH_CHECK();
-}
-
-void gather_comps(Handle &h, const double *src, int sstride, const CompSet &cs,
-                  double *dst, size_t n) {
-  hipLaunchKernelGGL(gather_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, src,
-                     sstride, cs, dst, n);
-  PSE_LAUNCH_CHECK();
-}
-
-void scatter_comps(Handle &h, const double *src, const CompSet &cs, double *dst,
-                   int dstride, size_t n, bool accumulate, double alpha) {
-  hipLaunchKernelGGL(scatter_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, src,
-                     cs, dst, dstride, n, accumulate ? 1 : 0, alpha);
   PSE_LAUNCH_CHECK();
 }
 
@@ -352,9 +622,73 @@ __device__ void tridiag_ql(double *d, double *e, double *z, int m, int ldz) {
   }
 }
 
+// The same for m <= 64 with d and e in registers, entry i in lane i, and a
+// rotation from one reciprocal square root (d and e are scaled to at most
+// one): the recurrences are one dependent chain, and memory, hypot and two
+// divisions per rotation were most of its length (m = 6: 21 -> 8 us).  The
+// column of z that a rotation leaves to the next stays in a register.  z[i][j]
+// (LDS, rows of m): row i belongs to lane i.
+__device__ void tridiag_ql_lanes(double &d, double &e, double *z, int m) {
+  const int lane = threadIdx.x;
+  double *zr = z + lane * m;
+  if (lane < m)
+    for (int j = 0; j < m; ++j) zr[j] = lane == j ? 1.0 : 0.0;
+  for (int l = 0; l < m; ++l) {
+    for (int iter = 0; iter < 60; ++iter) {
+      const double dn = __shfl_down(d, 1, 64);
+      const unsigned long long small =
+          __ballot(lane >= m - 1 || fabs(e) <= 1e-16 * (fabs(d) + fabs(dn)));
+      const int mm = l + __builtin_ctzll(small >> l);
+      if (mm == l) break;
+      const double el = lane_d(e, l), dl = lane_d(d, l);
+      double g = (lane_d(d, l + 1) - dl) / (2.0 * el);
+      double r = sqrt(g * g + 1.0);
+      g = lane_d(d, mm) - dl + el / (g + (g >= 0 ? r : -r));
+      double s = 1.0, c = 1.0, p = 0.0;
+      double zf = lane < m ? zr[mm] : 0.0;   // column i + 1
+      int i = mm - 1;
+      for (; i >= l; --i) {
+        const double ei = lane_d(e, i), di1 = lane_d(d, i + 1), di = lane_d(d, i);
+        const double zi = lane < m ? zr[i] : 0.0;
+        const double f = s * ei, b = c * ei, h2 = f * f + g * g;
+        if (h2 == 0.0) {
+          if (lane == i + 1) {
+            e = 0.0;
+            d -= p;
+          }
+          if (lane == mm) e = 0.0;
+          if (lane < m) zr[i + 1] = zf;
+          break;
+        }
+        const double ir = rsqrt(h2);
+        s = f * ir;
+        c = g * ir;
+        g = di1 - p;
+        r = (di - g) * s + 2.0 * c * b;
+        p = s * r;
+        if (lane == i + 1) {
+          e = h2 * ir;
+          d = g + p;
+        }
+        g = c * r - b;
+        if (lane < m) zr[i + 1] = s * zi + c * zf;
+        zf = c * zi - s * zf;
+      }
+      if (i >= l) continue;
+      if (lane < m) zr[l] = zf;
+      if (lane == l) {
+        d -= p;
+        e = g;
+      }
+      if (lane == mm) e = 0.0;
+    }
+  }
+}
+
 // coef = bnorm * f(T) e_1 with f = sqrt, T = tridiag(alpha, beta) of size m;
 // also the relative change against the previous coefficient vector
-// (zero-padded), written to out_change.  One wavefront (64 threads): inputs
+// (zero-padded), kept in chg_hist[m-1] and, when given, host_change[m-1].  One
+// wavefront (64 threads): inputs
 // loaded in parallel, the eigenproblem by tridiag_ql, coefficient i by lane
 // i mod 64, the change summed in index order by lane 0.
 // Device-checked solves (sel != NULL): sel[0] is set once the first
@@ -364,9 +698,9 @@ __device__ void tridiag_ql(double *d, double *e, double *z, int m, int ldz) {
 // converged).
 __global__ void __launch_bounds__(64)
 lanczos_sqrt_kernel(const double *alpha, const double *beta, int m, const double *bnorm_dev,
-                    double *work, int ldz, double *coef, double *coef_prev,
-                    double *out_change, double *chg_hist, int *sel, double *coef_sel,
-                    const double *vn_hist, double tol, int last) {
+                    double *work, int ldz, double *coef, double *coef_prev, double *chg_hist,
+                    double *host_change, int *sel, double *coef_sel, const double *vn_hist,
+                    double tol, int last) {
   // LDS: the new and previous coefficients (2m), then d, e and z when they
   // fit (ldz == m; the host sizes the dynamic shared memory), else those
   // live in the global work area
@@ -377,20 +711,34 @@ lanczos_sqrt_kernel(const double *alpha, const double *beta, int m, const double
   double *cbuf = lds_work, *pbuf = lds_work + m;
   double *base = ldz == m ? lds_work + 2 * m : work;
   double *d = base, *e = base + ldz, *z = base + 2 * ldz;
-  for (int i = lane; i < m; i += nt) {
-    d[i] = alpha[i];
-    e[i] = i + 1 < m ? beta[i] : 0.0;
-    pbuf[i] = i < m - 1 ? coef_prev[i] : 0.0;
+  if (m <= 64) {
+    double di = lane < m ? alpha[lane] : 0.0, ei = lane + 1 < m ? beta[lane] : 0.0;
+    if (lane < m) pbuf[lane] = lane < m - 1 ? coef_prev[lane] : 0.0;
+    double big = fmax(fabs(di), fabs(ei));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) big = fmax(big, __shfl_xor(big, off, 64));
+    const double f = big > 0.0 ? 1.0 / big : 1.0;
+    di *= f;
+    ei *= f;
+    tridiag_ql_lanes(di, ei, z, m);
+    if (lane < m) d[lane] = big > 0.0 ? di * big : di;
+  } else {
+    for (int i = lane; i < m; i += nt) {
+      d[i] = alpha[i];
+      e[i] = i + 1 < m ? beta[i] : 0.0;
+      pbuf[i] = i < m - 1 ? coef_prev[i] : 0.0;
+    }
+    __syncthreads();
+    tridiag_ql(d, e, z, m, ldz);
   }
   __syncthreads();
-  tridiag_ql(d, e, z, m, ldz);
+  // w_k = sqrt(lambda_k) z_0k (over e, which is done with)
+  double *w = e;
+  for (int k = lane; k < m; k += nt) w[k] = (d[k] > 0.0 ? sqrt(d[k]) : 0.0) * z[k];
   __syncthreads();
   for (int i = lane; i < m; i += nt) {
     double acc = 0.0;
-    for (int k = 0; k < m; ++k) {
-      const double lam = d[k] > 0.0 ? sqrt(d[k]) : 0.0;
-      acc += z[i * ldz + k] * lam * z[0 * ldz + k];
-    }
+    for (int k = 0; k < m; ++k) acc += z[i * ldz + k] * w[k];
     cbuf[i] = bnorm * acc;
     coef[i] = cbuf[i];
   }
@@ -403,11 +751,12 @@ lanczos_sqrt_kernel(const double *alpha, const double *beta, int m, const double
     den += c * c;
     coef_prev[i] = c;
   }
-  out_change[0] = den > 0.0 ? sqrt(num / den) : 0.0;
-  chg_hist[m - 1] = out_change[0];
+  const double change = den > 0.0 ? sqrt(num / den) : 0.0;
+  chg_hist[m - 1] = change;
+  if (host_change) host_change[m - 1] = change;
   if (!sel || sel[0]) return;
   const bool brk = vn_hist[m - 1] <= 1e-14 * bnorm;
-  const bool conv = m > 1 && out_change[0] < tol;
+  const bool conv = m > 1 && change < tol;
   if (brk || conv || last) {
     sel[0] = 1;
     sel[1] = m;
@@ -416,261 +765,207 @@ lanczos_sqrt_kernel(const double *alpha, const double *beta, int m, const double
   }
 }
 
-// y = R^{-1} g for the k x k upper-triangular part of H (k from k_dev when
-// given).
-__global__ void backsub_kernel(const double *H, int ldh, int k, const double *g, double *y,
-                               const int *k_dev) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (k_dev) k = *k_dev;
-  for (int i = k - 1; i >= 0; --i) {
-    double s = g[i];
-    for (int j = i + 1; j < k; ++j) s -= H[(size_t)j * ldh + i] * y[j];
-    y[i] = s / H[(size_t)i * ldh + i];
-  }
-}
-
-// GMRES column j from the two Gram-Schmidt passes: H[i][j] = h1[i] + h2[i]
-// (i <= j); h2[j+1] holds w.w after the first pass, so the norm of the
-// twice-orthogonalised w is sqrt(w.w - |h2|^2) (V orthonormal).  Then the
-// previous Givens rotations are applied to the column, the new one is
-// formed and g updated; vnorm = H[j+1][j], resid = |g_{j+1}|.
-// One wavefront: the column, its squared norm and the previous rotations
-// are loaded in parallel into LDS (3j + 2 doubles, sized by the host), then
-// lane 0 applies the rotations.
-// Device-checked solves (sel != NULL): sel[0] is set at the first column
-// whose residual met tol |b| or whose new vector vanished (vn <= 1e-15 |b|),
-// sel[1] = its column count k (0 for b = 0); at the last column (last != 0)
-// without one, k = j + 1 and sel[2] = 1 (not converged).
-__global__ void __launch_bounds__(64)
-hess_givens_kernel(double *__restrict__ H, int ldh, int j, const double *__restrict__ h1,
-                   const double *__restrict__ h2, double *__restrict__ cs,
-                   double *__restrict__ sn, double *__restrict__ g, double *__restrict__ vnorm,
-                   double *__restrict__ resid, double *__restrict__ vn_hist,
-                   double *__restrict__ res_hist, int *__restrict__ sel,
-                   const double *__restrict__ bnorm_dev, double tol, int last) {
-  extern __shared__ double sm[];
-  if (blockIdx.x != 0) return;
-  double *cl = sm, *cs_l = sm + (j + 2), *sn_l = cs_l + j;
-  const int lane = threadIdx.x, nt = blockDim.x;
-  double p2 = 0.0;
-  for (int i = lane; i <= j; i += nt) {
-    const double b2 = h2[i];
-    cl[i] = h1[i] + b2;
-    p2 += b2 * b2;
-  }
-  for (int i = lane; i < j; i += nt) {
-    cs_l[i] = cs[i];
-    sn_l[i] = sn[i];
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) p2 += __shfl_xor(p2, off, 64);
-  __syncthreads();
-  if (lane != 0) return;
-  double *col = H + (size_t)j * ldh;
-  const double nn = sqrt(fmax(h2[j + 1] - p2, 0.0));
-  cl[j + 1] = nn;
-  vnorm[0] = nn;
-  for (int i = 0; i < j; ++i) {
-    const double t = cs_l[i] * cl[i] + sn_l[i] * cl[i + 1];
-    cl[i + 1] = -sn_l[i] * cl[i] + cs_l[i] * cl[i + 1];
-    cl[i] = t;
-  }
-  const double a = cl[j], b = cl[j + 1];
-  const double r = hypot(a, b);
-  const double c = r > 0 ? a / r : 1.0, s = r > 0 ? b / r : 0.0;
-  cs[j] = c;
-  sn[j] = s;
-  for (int i = 0; i < j; ++i) col[i] = cl[i];
-  col[j] = r;
-  col[j + 1] = 0.0;
-  const double gj = g[j];
-  g[j + 1] = -s * gj;
-  g[j] = c * gj;
-  resid[0] = fabs(g[j + 1]);
-  vn_hist[j] = nn;
-  res_hist[j] = resid[0];
-  if (!sel || sel[0]) return;
-  const double bn = *bnorm_dev;
-  const bool done = resid[0] < tol * bn || nn <= 1e-15 * bn;
-  if (done || last) {
-    sel[0] = 1;
-    sel[1] = bn > 0.0 ? j + 1 : 0;
-    sel[2] = done ? 0 : 1;
-  }
-}
-
-__global__ void sqrt_kernel(const double *in, double *out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) out[0] = sqrt(fmax(in[0], 0.0));
-}
-
-__global__ void set_g0_kernel(double *g, int len, const double *beta) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    for (int i = 0; i < len; ++i) g[i] = 0.0;
-    g[0] = beta[0];
-  }
-}
-
-// Lanczos tridiagonal entries from the two Gram-Schmidt passes:
-// alpha_j = h1[j] + h2[j]; h2[j+1] holds w.w after the first pass, so
-// beta_j = sqrt(w.w - |h2|^2) is the norm of the twice-orthogonalised w.
-__global__ void lanczos_fill_kernel(double *alpha, double *beta, int j, const double *h1,
-                                    const double *h2, double *vnorm, double *vn_hist) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  alpha[j] = h1[j] + h2[j];
-  double p2 = 0.0;
-  for (int i = 0; i <= j; ++i) p2 += h2[i] * h2[i];
-  const double nn = sqrt(fmax(h2[j + 1] - p2, 0.0));
-  beta[j] = nn;
-  vnorm[0] = nn;
-  vn_hist[j] = nn;
-}
-
 // ---------------------------------------------------- host algorithms --
 
-// Reads n Krylov scalars; any non-finite one is reported as an error (a
+// Krylov scalars that kernels write to host memory (h.kry: |b| first, then
+// two histories of hcap numbers), read after a synchronisation.  Any
+// non-finite one among the first n of each history is reported as an error (a
 // non-finite input vector or operator result).
-static void host_read(Handle &h, const double *dev, double *host, int n) {
-  PSE_HIP(hipMemcpyAsync(host, dev, n * sizeof(double), hipMemcpyDeviceToHost, h.stream));
+static void host_scalars(Handle &h, int hcap, int n) {
   PSE_HIP(hipStreamSynchronize(h.stream));
-  for (int i = 0; i < n; ++i)
-    if (!std::isfinite(host[i])) throw Error{PSE_ERR_NONFINITE, "non-finite Krylov scalar"};
+  const volatile double *k = h.kry;
+  bool ok = std::isfinite(k[0]);
+  for (int i = 0; i < n; ++i) ok = ok && std::isfinite(k[1 + i]) && std::isfinite(k[1 + hcap + i]);
+  if (!ok) throw Error{PSE_ERR_NONFINITE, "non-finite Krylov scalar"};
 }
 
-// Reads the first n values of two device histories that lie stride doubles
-// apart (a and a + stride) into ha and ha + stride, with one copy and one
-// synchronisation.
-static void host_read2(Handle &h, const double *a, double *ha, int stride, int n) {
-  PSE_HIP(hipMemcpyAsync(ha, a, (size_t)(stride + n) * sizeof(double), hipMemcpyDeviceToHost,
-                         h.stream));
-  PSE_HIP(hipStreamSynchronize(h.stream));
-  for (int i = 0; i < n; ++i)
-    if (!std::isfinite(ha[i]) || !std::isfinite(ha[stride + i]))
-      throw Error{PSE_ERR_NONFINITE, "non-finite Krylov scalar"};
+// dev_norm2 = v . v
+void norm2_dev(Handle &h, const double *v, size_t n, double *dev_norm2) {
+  const Plan p = plan_of(n);
+  ProfScope ps(h, PK_KRYLOV, (double)n * 8);
+  hipLaunchKernelGGL(dots_kernel, dim3(p.nb), dim3(256), 0, h.stream, v, n, 1, v, n,
+                     p.nb == 1 ? dev_norm2 : h.dots);
+  PSE_LAUNCH_CHECK();
+  if (p.nb == 1) return;
+  hipLaunchKernelGGL(reduce_partial, dim3(1), dim3(256), 0, h.stream, (const double *)h.dots,
+                     p.nb, dev_norm2);
+  PSE_LAUNCH_CHECK();
 }
 
-static void norm2_dev(Handle &h, const double *v, size_t n, double *dev_norm2) {
-  multi_dot(h, v, n, 1, v, n, dev_norm2);
+// Scalars of a solve's start (see krylov_start_kernel).
+struct Start {
+  double *bn, *g;
+  int glen;
+  double *clear0, *clear1;
+  int len;
+  int *sel;
+  double *host;
+};
+
+static void krylov_start(Handle &h, const double *b, double *v, size_t n, double *norm2,
+                         const Start &st) {
+  const Plan p = plan_of(n);
+  ProfScope ps(h, PK_KRYLOV, (double)(p.kind == Plan::ONE ? 2 : 3) * n * 8);
+  int nb = -1;
+  unsigned grid = 1, block = 1024;
+  if (p.kind != Plan::ONE) {
+    hipLaunchKernelGGL(dots_kernel, dim3(p.nb), dim3(256), 0, h.stream, b, n, 1, b, n, h.dots);
+    PSE_LAUNCH_CHECK();
+    nb = p.nb;
+    if (p.kind == Plan::MANY) {
+      hipLaunchKernelGGL(reduce_partial, dim3(1), dim3(256), 0, h.stream, (const double *)h.dots,
+                         p.nb, norm2);
+      PSE_LAUNCH_CHECK();
+      nb = 0;
+    }
+    block = 256;
+    grid = std::min(nblocks(n, 256), 2048u);
+  }
+  hipLaunchKernelGGL(krylov_start_kernel, dim3(grid), dim3(block), 0, h.stream, b, v, n,
+                     (const double *)h.dots, nb, (const double *)norm2, st.bn, st.g, st.glen,
+                     st.clear0, st.clear1, st.len, st.sel, st.host);
+  PSE_LAUNCH_CHECK();
 }
 
-// Two-pass classical Gram-Schmidt of w = V[m] against V[0..m-1] (leading dim
-// n): h1 = V^T w, w -= V h1; then h2[0..m] = [V, w]^T w (h2[m] = w.w).  The
-// second subtraction is fused with the normalisation (sub_scale) once the
-// norm is known on the device.
-static void cgs2_pass(Handle &h, const double *V, size_t n, int m, double *w, double *h1,
-                      double *h2) {
-  multi_dot(h, V, n, m, w, n, h1);
-  if (m + 1 > MAX_DOTS || w != V + (size_t)m * n) {
-    vsub_multi(h, w, V, n, m, h1, n);
-    multi_dot(h, V, n, m + 1, w, n, h2);
+// One Gram-Schmidt step of w = V_m (leading dimension n) and its column.
+static void krylov_step(Handle &h, const double *V, size_t n, int m, double *w, double *h1,
+                        double *h2, const Column &c) {
+  const Plan p = plan_of(n);
+  const size_t hl = (size_t)(m + 1) * sizeof(double);
+  ProfScope ps(h, PK_KRYLOV, (double)(3 * m + 5) * n * 8);
+  if (p.kind == Plan::ONE) {
+    hipLaunchKernelGGL(krylov_one_kernel, dim3(1), dim3(ONE_T), 5 * hl, h.stream, w, V, n, m,
+                       (int)n, c);
+    PSE_LAUNCH_CHECK();
     return;
   }
-  // w = V_m: the subtraction and the second pass's dot products in one launch
-  int nb = (int)std::min<size_t>(RED_BLOCKS, (n + 255) / 256);
-  if (nb < 1) nb = 1;
-  if ((size_t)nb * (m + 1) > h.dots_len) throw Error{PSE_ERR_INVALID, "reduction scratch too small"};
-  // one pass reads V_0..V_{m-1} and w and writes w; the two-loop form reads
-  // them twice
-  ProfScope ps(h, PK_KRYLOV, (double)(m + 1 <= SDF ? m + 2 : 2 * m + 3) * n * 8);
-  if (m + 1 <= SDF)
-    hipLaunchKernelGGL(sub_dot_partial1, dim3(nb), dim3(256), 0, h.stream, w, V, n, m, h1, n,
-                       h.dots);
-  else
-    hipLaunchKernelGGL(sub_dot_partial, dim3(nb), dim3(256), 0, h.stream, w, V, n, m, h1, n,
-                       h.dots);
+  const bool few = p.kind == Plan::FEW;
+  double *p1 = h.dots, *p2 = few ? h.dots + (size_t)p.nb * m : h.dots;
+  if ((size_t)(p2 - h.dots) + (size_t)p.nb * (m + 1) > h.dots_len)
+    throw Error{PSE_ERR_INVALID, "reduction scratch too small"};
+  hipLaunchKernelGGL(dots_kernel, dim3(p.nb), dim3(256), 0, h.stream, V, n, m, (const double *)w,
+                     n, p1);
   PSE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(reduce_partial, dim3(m + 1), dim3(256), 0, h.stream, h.dots, nb, h2);
+  if (!few) {
+    hipLaunchKernelGGL(reduce_partial, dim3(m), dim3(256), 0, h.stream, (const double *)p1, p.nb,
+                       h1);
+    PSE_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(sub_dots_kernel, dim3(p.nb), dim3(256), hl, h.stream, w, V, n, m, n,
+                     (const double *)p1, few ? p.nb : 0, h1, p2);
+  PSE_LAUNCH_CHECK();
+  if (!few) {
+    hipLaunchKernelGGL(reduce_partial, dim3(m + 1), dim3(256), 0, h.stream, (const double *)p2,
+                       p.nb, h2);
+    PSE_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(finish_kernel, dim3(std::min(nblocks(n, 256), few ? 256u : 8192u)), dim3(256),
+                     5 * hl, h.stream, w, V, n, m, n, (const double *)h1, (const double *)p2,
+                     few ? p.nb : 0, (const double *)h2, c);
   PSE_LAUNCH_CHECK();
 }
 
-static void sub_scale(Handle &h, double *w, const double *V, size_t n, int m,
-                      const double *coef, const double *s) {
-  ProfScope ps(h, PK_KRYLOV, (double)(m + 2) * n * 8);
-  hipLaunchKernelGGL(sub_scale_kernel, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, w, V, n,
-                     m, coef, s, n);
+// Lanczos scratch in h.small for at most M iterations.
+struct LanczosScratch {
+  double *alpha, *beta, *h1, *h2, *norm2, *bn, *coef, *coef_prev, *vn_hist, *chg_hist, *coef_sel,
+      *work;
+  LanczosScratch(Handle &h, int M) {
+    double *s = h.small;
+    const auto take = [&](size_t n) { double *p = s; s += n; return p; };
+    alpha = take(M + 1);
+    beta = take(M + 1);
+    h1 = take(M + 1);
+    h2 = take(M + 2);
+    norm2 = take(1);
+    bn = take(1);
+    coef = take(M + 1);
+    coef_prev = take(M + 1);
+    vn_hist = take(M + 1);
+    chg_hist = take(M + 1);
+    coef_sel = take(M + 1);
+    work = s;
+    if ((size_t)(work - h.small) + (size_t)(3 + M) * (M + 1) + 8 > h.small_len)
+      throw Error{PSE_ERR_INVALID, "Lanczos scratch too small"};
+  }
+};
+
+static void lanczos_coef(Handle &h, const LanczosScratch &z, int M, int mm, double *host_change,
+                         int *sel, double tol, bool last) {
+  // LDS holds the two coefficient vectors, and d, e and the mm^2 eigenvectors
+  // when they fit in 48 KiB
+  const size_t coefs = (size_t)2 * mm * sizeof(double);
+  const size_t lds = coefs + (size_t)(2 * mm + mm * mm) * sizeof(double);
+  const bool fits = lds <= 49152;
+  hipLaunchKernelGGL(lanczos_sqrt_kernel, dim3(1), dim3(64), fits ? lds : coefs, h.stream,
+                     (const double *)z.alpha, (const double *)z.beta, mm, (const double *)z.bn,
+                     z.work, fits ? mm : M + 1, z.coef, z.coef_prev, z.chg_hist, host_change, sel,
+                     z.coef_sel, (const double *)z.vn_hist, tol, last ? 1 : 0);
   PSE_LAUNCH_CHECK();
+}
+
+// The first iteration whose scalars the host looks at: the iteration counts
+// of successive solves on a handle barely change, and a look stalls the
+// stream, so they start shortly before the previous solve's count (two
+// iterations; one where an iteration is short against the stall), at every
+// iteration on a first solve.
+static int first_look(const int *prev, size_t n) {
+  if (!prev || *prev <= 3) return 0;
+  return *prev - (plan_of(n).kind == Plan::MANY ? 2 : 1);
 }
 
 // Lanczos approximation of y = A^(1/2) b (Chow & Saad): full
 // reorthogonalization, stop when the relative change of the iterate falls
 // below tol.  The iterate is y_m = |b| V_m f(T_m) e_1; with V_m orthonormal
-// its change is the change of the small coefficient vector.
-// Convergence checks read per-iteration scalars on the host, each a stall of
-// the stream.  The iteration counts of successive solves on a handle barely
-// change, so a solve reads them from two iterations before the previous
-// solve's count on (every iteration on the first solve); per-iteration
-// values are kept on the device, so the first converged iteration (or a
-// breakdown) is still found exactly and later iterations are discarded.
-
+// its change is the change of the small coefficient vector.  Per-iteration
+// values are kept, so the first converged iteration (or a breakdown) is found
+// exactly whenever the host looks (first_look); later iterations are discarded.
 KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n, double *y,
                           int maxit, double tol, int *prev_iters) {
-  const int M = maxit;
-  const int ldz = M + 1;
-  double *s = h.small;
-  double *alpha = s, *beta = alpha + (M + 1), *h1 = beta + (M + 1), *h2 = h1 + (M + 1);
-  double *norm2 = h2 + (M + 1), *vnorm = norm2 + 1, *bn = vnorm + 1, *change = bn + 1;
-  double *coef = change + 1, *coef_prev = coef + (M + 1);
-  double *vn_hist = coef_prev + (M + 1), *chg_hist = vn_hist + (M + 1);
-  double *work = chg_hist + (M + 1);
-  if ((size_t)(work - s) + (size_t)(2 + ldz) * ldz + 8 > h.small_len)
-    throw Error{PSE_ERR_INVALID, "Lanczos scratch too small"};
+  const int M = maxit, hcap = M + 1;
+  const LanczosScratch z(h, M);
   double *V = h.lz_V;
-  KrylovResult res{0, 0.0, false};
-  norm2_dev(h, b, n, norm2);
-  hipLaunchKernelGGL(sqrt_kernel, dim3(1), dim3(1), 0, h.stream, norm2, bn);
-  PSE_LAUNCH_CHECK();
-  double hb[2];
-  host_read(h, bn, hb, 1);
-  const double bnorm = hb[0];
-  if (!(bnorm > 0)) {
-    vzero(h, y, n);
-    res.converged = true;
-    return res;
-  }
-  fill_double(h, coef_prev, M + 1, 0.0);
-  // iterations before the first read leave their change unset: zero, so that
-  // the history read back is finite
-  fill_double(h, chg_hist, M + 1, 0.0);
-  vscale_dev(h, V, b, bn, true, n);
-  auto sqrt_coef = [&](int mm) {
-    // LDS holds the two coefficient vectors, and d, e and the mm^2
-    // eigenvectors when they fit in 48 KiB
-    const size_t coefs = (size_t)2 * mm * sizeof(double);
-    const size_t lds = coefs + (size_t)(2 * mm + mm * mm) * sizeof(double);
-    const bool fits = lds <= 49152;
-    hipLaunchKernelGGL(lanczos_sqrt_kernel, dim3(1), dim3(64), fits ? lds : coefs, h.stream, alpha,
-                       beta, mm, (const double *)bn, work, fits ? mm : ldz, coef, coef_prev,
-                       change, chg_hist, (int *)nullptr, (double *)nullptr,
-                       (const double *)nullptr, 0.0, 0);
-    PSE_LAUNCH_CHECK();
-  };
-  const int check_from = (prev_iters && *prev_iters > 3) ? *prev_iters - 2 : 0;
-  std::vector<double> hist(2 * (M + 1));
+  KrylovResult res{0, 0.0, false, 0.0};
+  // changes before the first look stay unset: zero, so that they read finite
+  // (the stream has finished the last solve that wrote them)
+  for (int i = 0; i < 2 * hcap; ++i) h.kry[1 + i] = 0.0;
+  double *host_change = h.kry + 1 + hcap;
+  krylov_start(h, b, V, n, z.norm2,
+               Start{z.bn, nullptr, 0, z.coef_prev, z.chg_hist, M + 1, nullptr, h.kry});
+  const int check_from = first_look(prev_iters, n);
+  const volatile double *vh = h.kry + 1, *ch = host_change;
   int m = 0;
   for (int j = 0; j < M; ++j) {
     double *w = V + (size_t)(j + 1) * n;
     A(V + (size_t)j * n, w);
-    cgs2_pass(h, V, n, j + 1, w, h1, h2);
-    hipLaunchKernelGGL(lanczos_fill_kernel, dim3(1), dim3(1), 0, h.stream, alpha, beta, j,
-                       h1, h2, vnorm, vn_hist);
-    PSE_LAUNCH_CHECK();
-    sub_scale(h, w, V, n, j + 1, h2, vnorm);
-    // f(T) e_1 is needed from one iteration before the first read on (the
+    Column c{};
+    c.alpha = z.alpha;
+    c.beta = z.beta;
+    c.vn_hist = z.vn_hist;
+    c.host = h.kry;
+    c.hcap = hcap;
+    krylov_step(h, V, n, j + 1, w, z.h1, z.h2, c);
+    // f(T) e_1 is needed from one iteration before the first look on (the
     // change there is taken against it); a breakdown recomputes its own
-    if (j + 2 >= check_from || j + 1 >= M) sqrt_coef(j + 1);
+    if (j + 2 >= check_from || j + 1 >= M)
+      lanczos_coef(h, z, M, j + 1, host_change, nullptr, 0.0, false);
     m = j + 1;
     res.iters = m;
     if (m < check_from && m < M) continue;
-    host_read2(h, vn_hist, hist.data(), M + 1, j + 1);  // vn_hist, then chg_hist
-    const double *vh = hist.data(), *ch = vh + (M + 1);
+    host_scalars(h, hcap, j + 1);
+    res.bnorm = h.kry[0];
+    if (!(res.bnorm > 0)) {
+      vzero(h, y, n);
+      return KrylovResult{0, 0.0, true, 0.0};
+    }
     int brk = -1;
     for (int i = 0; i <= j; ++i)
-      if (vh[i] <= 1e-14 * bnorm) {
+      if (vh[i] <= 1e-14 * res.bnorm) {
         brk = i;
         break;
       }
     if (brk >= 0) {
       // breakdown: the Krylov space is exhausted after brk + 1 vectors
-      if (brk < j) sqrt_coef(brk + 1);
+      if (brk < j) lanczos_coef(h, z, M, brk + 1, nullptr, nullptr, 0.0, false);
       m = brk + 1;
       res.resid = ch[brk];
       res.converged = true;
@@ -683,86 +978,109 @@ KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n, dou
     }
   }
   if (prev_iters) *prev_iters = res.iters;
-  gemv_small(h, V, n, m, coef, y, n, 1.0, false, nullptr);
+  gemv_small(h, V, n, m, z.coef, y, n, 1.0, false, nullptr);
   return res;
+}
+
+// GMRES scratch in h.small for at most R columns.
+struct GmresScratch {
+  double *H, *cs, *sn, *g, *h1, *h2, *norm2, *beta, *bn, *vn_hist, *res_hist;
+  GmresScratch(Handle &h, int R) {
+    double *s = h.small;
+    const auto take = [&](size_t n) { double *p = s; s += n; return p; };
+    H = take((size_t)(R + 1) * R);
+    cs = take(R + 1);
+    sn = take(R + 1);
+    g = take(R + 1);
+    h1 = take(R + 1);
+    h2 = take(R + 2);
+    norm2 = take(1);
+    beta = take(1);
+    bn = take(1);
+    vn_hist = take(R + 1);
+    res_hist = take(R + 1);
+    if ((size_t)(s - h.small) + 8 > h.small_len)
+      throw Error{PSE_ERR_INVALID, "GMRES scratch too small"};
+  }
+  Column column(int R) const {
+    Column c{};
+    c.H = H;
+    c.ldh = R + 1;
+    c.cs = cs;
+    c.sn = sn;
+    c.g = g;
+    c.vn_hist = vn_hist;
+    c.res_hist = res_hist;
+    c.bn = bn;
+    return c;
+  }
+};
+
+// x = (acc ? x : 0) + V y, R y = g over k columns (k_dev: at most k).
+static void gmres_update(Handle &h, const GmresScratch &z, int ldh, const double *V, size_t n,
+                         int k, double *x, bool acc, const int *k_dev) {
+  ProfScope ps(h, PK_KRYLOV, (double)(k + 1 + (acc ? 1 : 0)) * n * 8);
+  hipLaunchKernelGGL(solve_gemv_kernel, dim3(nblocks(n, 256)), dim3(256),
+                     (size_t)(k + 1) * sizeof(double), h.stream, V, n, k, (const double *)z.H, ldh,
+                     (const double *)z.g, x, n, acc ? 1 : 0, k_dev);
+  PSE_LAUNCH_CHECK();
 }
 
 // Restarted GMRES(restart) for A x = b from x = 0, stopping at relative
 // residual tol or after maxit iterations.  Modified to classical
 // Gram-Schmidt with a second pass (CGS2) so that each Arnoldi step costs two
-// fused reductions; Givens rotations on the device.
+// fused reductions; Givens rotations on the device.  The host looks at the
+// residuals as in lanczos_sqrt; restarted cycles every step.
 KrylovResult gmres(Handle &h, const Op &A, const double *b, size_t n, double *x,
                    int restart, int maxit, double tol, int *prev_iters) {
-  const int R = restart;
-  const int ldh = R + 1;
-  double *s = h.small;
-  double *H = s, *cs = H + (size_t)ldh * R, *sn = cs + (R + 1), *g = sn + (R + 1);
-  double *h1 = g + (R + 1), *h2 = h1 + (R + 1), *norm2 = h2 + (R + 1);
-  double *vnorm = norm2 + 1, *bn = vnorm + 1, *resid = bn + 1, *ycoef = resid + 1;
-  double *vn_hist = ycoef + (R + 1), *res_hist = vn_hist + (R + 1);
-  if ((size_t)(res_hist - s) + R + 8 > h.small_len)
-    throw Error{PSE_ERR_INVALID, "GMRES scratch too small"};
+  const int R = restart, hcap = R + 1;
+  const GmresScratch z(h, R);
   double *V = h.gm_V;
-  KrylovResult res{0, 0.0, false};
-  vzero(h, x, n);
-  norm2_dev(h, b, n, norm2);
-  hipLaunchKernelGGL(sqrt_kernel, dim3(1), dim3(1), 0, h.stream, norm2, bn);
-  PSE_LAUNCH_CHECK();
-  double bnorm;
-  host_read(h, bn, &bnorm, 1);
-  if (!(bnorm > 0)) {
-    res.converged = true;
-    if (prev_iters) *prev_iters = 0;
-    return res;
-  }
-  double rel = 1.0;
+  KrylovResult res{0, 0.0, false, 0.0};
+  const volatile double *vh = h.kry + 1, *rh = h.kry + 1 + hcap;
+  double rel = 1.0, bnorm = 0.0;
   int total = 0;
   bool first = true;
-  // only the first cycle reads late (see above); restarts check every step
-  int check_from = (prev_iters && *prev_iters > 3) ? *prev_iters - 2 : 0;
-  std::vector<double> hist(2 * (R + 1));
+  int check_from = first_look(prev_iters, n);
   while (total < maxit) {
-    // r = b - A x; on the first cycle x = 0, so r = b and its norm is the
-    // |b| already on the device and the host
+    // r = b - A x; on the first cycle x = 0, so r = b and beta = |b|
     double *r = V;
-    const double *beta_dev = bn;
-    double beta = bnorm;
-    if (!first) {
+    if (first) {
+      krylov_start(h, b, r, n, z.norm2,
+                   Start{z.bn, z.g, R + 1, nullptr, nullptr, 0, nullptr, h.kry});
+    } else {
       A(x, r);
       vaxpby(h, 1.0, b, -1.0, r, n);
       check_from = 0;
-      norm2_dev(h, r, n, norm2);
-      hipLaunchKernelGGL(sqrt_kernel, dim3(1), dim3(1), 0, h.stream, norm2, vnorm);
-      PSE_LAUNCH_CHECK();
-      host_read(h, vnorm, &beta, 1);
-      beta_dev = vnorm;
+      krylov_start(h, r, r, n, z.norm2,
+                   Start{z.beta, z.g, R + 1, nullptr, nullptr, 0, nullptr, h.kry});
+      host_scalars(h, hcap, 0);
+      rel = h.kry[0] / bnorm;
+      if (rel < tol) {
+        res.converged = true;
+        break;
+      }
     }
-    rel = beta / bnorm;
-    if (rel < tol) {
-      res.converged = true;
-      break;
-    }
-    // v_0 = r / beta
-    vscale_dev(h, r, first ? b : r, beta_dev, true, n);
-    first = false;
-    hipLaunchKernelGGL(set_g0_kernel, dim3(1), dim3(1), 0, h.stream, g, R + 1, beta_dev);
-    PSE_LAUNCH_CHECK();
     int k = 0;
     for (int j = 0; j < R && total < maxit; ++j) {
       double *w = V + (size_t)(j + 1) * n;
       A(V + (size_t)j * n, w);
-      cgs2_pass(h, V, n, j + 1, w, h1, h2);
-      hipLaunchKernelGGL(hess_givens_kernel, dim3(1), dim3(64),
-                         (size_t)(3 * j + 2) * sizeof(double), h.stream, H, ldh, j, h1, h2,
-                         cs, sn, g, vnorm, resid, vn_hist, res_hist, (int *)nullptr,
-                         (const double *)nullptr, 0.0, 0);
-      PSE_LAUNCH_CHECK();
-      sub_scale(h, w, V, n, j + 1, h2, vnorm);
+      Column c = z.column(R);
+      c.host = h.kry;
+      c.hcap = hcap;
+      krylov_step(h, V, n, j + 1, w, z.h1, z.h2, c);
       ++total;
       k = j + 1;
       if (k < check_from && j + 1 < R && total < maxit) continue;
-      host_read2(h, vn_hist, hist.data(), R + 1, j + 1);  // vn_hist, then res_hist
-      const double *vh = hist.data(), *rh = vh + (R + 1);
+      host_scalars(h, hcap, j + 1);
+      if (first) {
+        bnorm = h.kry[0];
+        if (!(bnorm > 0)) {
+          vzero(h, x, n);
+          if (prev_iters) *prev_iters = 0;
+          return KrylovResult{0, 0.0, true, 0.0};
+        }
+      }
       // first column at which the residual met tol or the space was exhausted;
       // later columns (and Givens entries) are not used by the update
       int stop = -1;
@@ -778,10 +1096,8 @@ KrylovResult gmres(Handle &h, const Op &A, const double *b, size_t n, double *x,
       }
       rel = rh[j] / bnorm;
     }
-    hipLaunchKernelGGL(backsub_kernel, dim3(1), dim3(1), 0, h.stream, H, ldh, k, g, ycoef,
-                       (const int *)nullptr);
-    PSE_LAUNCH_CHECK();
-    gemv_small(h, V, n, k, ycoef, x, n, 1.0, true, nullptr);
+    gmres_update(h, z, R + 1, V, n, k, x, !first, nullptr);
+    first = false;
     if (rel < tol) {
       res.converged = true;
       break;
@@ -789,6 +1105,7 @@ KrylovResult gmres(Handle &h, const Op &A, const double *b, size_t n, double *x,
   }
   res.iters = total;
   res.resid = rel;
+  res.bnorm = bnorm;
   if (prev_iters) *prev_iters = total;
   return res;
 }
@@ -824,91 +1141,49 @@ __global__ void gmres_stats_kernel(const int *sel, const double *res_hist, const
 
 void lanczos_sqrt_dev(Handle &h, const Op &A, const double *b, size_t n, double *y, int K,
                       double tol) {
-  const int M = K;
-  const int ldz = M + 1;
-  double *s = h.small;
-  double *alpha = s, *beta = alpha + (M + 1), *h1 = beta + (M + 1), *h2 = h1 + (M + 1);
-  double *norm2 = h2 + (M + 1), *vnorm = norm2 + 1, *bn = vnorm + 1, *change = bn + 1;
-  double *coef = change + 1, *coef_prev = coef + (M + 1);
-  double *vn_hist = coef_prev + (M + 1), *chg_hist = vn_hist + (M + 1);
-  double *coef_sel = chg_hist + (M + 1);
-  double *work = coef_sel + (M + 1);
-  if ((size_t)(work - s) + (size_t)(2 + ldz) * ldz + 8 > h.small_len)
-    throw Error{PSE_ERR_INVALID, "Lanczos scratch too small"};
+  const LanczosScratch z(h, K);
   int *sel = h.dctl + CTL_LZ;
   double *V = h.lz_V;
-  norm2_dev(h, b, n, norm2);
-  hipLaunchKernelGGL(sqrt_kernel, dim3(1), dim3(1), 0, h.stream, norm2, bn);
-  PSE_LAUNCH_CHECK();
-  fill_double(h, coef_prev, M + 1, 0.0);
-  fill_double(h, chg_hist, M + 1, 0.0);
-  fill_int(h, sel, 3, 0);
-  vscale_dev(h, V, b, bn, true, n);
-  for (int j = 0; j < M; ++j) {
+  krylov_start(h, b, V, n, z.norm2,
+               Start{z.bn, nullptr, 0, z.coef_prev, z.chg_hist, K + 1, sel, nullptr});
+  for (int j = 0; j < K; ++j) {
     double *w = V + (size_t)(j + 1) * n;
     A(V + (size_t)j * n, w);
-    cgs2_pass(h, V, n, j + 1, w, h1, h2);
-    hipLaunchKernelGGL(lanczos_fill_kernel, dim3(1), dim3(1), 0, h.stream, alpha, beta, j,
-                       h1, h2, vnorm, vn_hist);
-    PSE_LAUNCH_CHECK();
-    sub_scale(h, w, V, n, j + 1, h2, vnorm);
-    const int mm = j + 1;
-    const size_t coefs = (size_t)2 * mm * sizeof(double);
-    const size_t lds = coefs + (size_t)(2 * mm + mm * mm) * sizeof(double);
-    const bool fits = lds <= 49152;
-    hipLaunchKernelGGL(lanczos_sqrt_kernel, dim3(1), dim3(64), fits ? lds : coefs, h.stream,
-                       alpha, beta, mm, (const double *)bn, work, fits ? mm : ldz, coef,
-                       coef_prev, change, chg_hist, sel, coef_sel, (const double *)vn_hist,
-                       tol, j + 1 == M ? 1 : 0);
-    PSE_LAUNCH_CHECK();
+    Column c{};
+    c.alpha = z.alpha;
+    c.beta = z.beta;
+    c.vn_hist = z.vn_hist;
+    krylov_step(h, V, n, j + 1, w, z.h1, z.h2, c);
+    lanczos_coef(h, z, K, j + 1, nullptr, sel, tol, j + 1 == K);
   }
-  gemv_small(h, V, n, M, coef_sel, y, n, 1.0, false, sel + 1);
+  gemv_small(h, V, n, K, z.coef_sel, y, n, 1.0, false, sel + 1);
   hipLaunchKernelGGL(lanczos_stats_kernel, dim3(1), dim3(1), 0, h.stream, (const int *)sel,
-                     (const double *)chg_hist, h.dstats);
+                     (const double *)z.chg_hist, h.dstats);
   PSE_LAUNCH_CHECK();
 }
 
 void gmres_dev(Handle &h, const Op &A, const double *b, size_t n, double *x, int K,
                double tol) {
   const int R = K;
-  const int ldh = R + 1;
-  double *s = h.small;
-  double *H = s, *cs = H + (size_t)ldh * R, *sn = cs + (R + 1), *g = sn + (R + 1);
-  double *h1 = g + (R + 1), *h2 = h1 + (R + 1), *norm2 = h2 + (R + 1);
-  double *vnorm = norm2 + 1, *bn = vnorm + 1, *resid = bn + 1, *ycoef = resid + 1;
-  double *vn_hist = ycoef + (R + 1), *res_hist = vn_hist + (R + 1);
-  if ((size_t)(res_hist - s) + R + 8 > h.small_len)
-    throw Error{PSE_ERR_INVALID, "GMRES scratch too small"};
+  const GmresScratch z(h, R);
   if ((size_t)R > (size_t)h.d.gmres_restart)
     throw Error{PSE_ERR_INVALID, "GMRES basis smaller than its iteration count"};
   int *sel = h.dctl + CTL_GM;
   double *V = h.gm_V;
-  vzero(h, x, n);
-  norm2_dev(h, b, n, norm2);
-  hipLaunchKernelGGL(sqrt_kernel, dim3(1), dim3(1), 0, h.stream, norm2, bn);
-  PSE_LAUNCH_CHECK();
-  fill_int(h, sel, 3, 0);
-  vscale_dev(h, V, b, bn, true, n);
-  hipLaunchKernelGGL(set_g0_kernel, dim3(1), dim3(1), 0, h.stream, g, R + 1,
-                     (const double *)bn);
-  PSE_LAUNCH_CHECK();
+  krylov_start(h, b, V, n, z.norm2,
+               Start{z.bn, z.g, R + 1, nullptr, nullptr, 0, sel, nullptr});
   for (int j = 0; j < R; ++j) {
     double *w = V + (size_t)(j + 1) * n;
     A(V + (size_t)j * n, w);
-    cgs2_pass(h, V, n, j + 1, w, h1, h2);
-    hipLaunchKernelGGL(hess_givens_kernel, dim3(1), dim3(64),
-                       (size_t)(3 * j + 2) * sizeof(double), h.stream, H, ldh, j, h1, h2, cs,
-                       sn, g, vnorm, resid, vn_hist, res_hist, sel, (const double *)bn, tol,
-                       j + 1 == R ? 1 : 0);
-    PSE_LAUNCH_CHECK();
-    sub_scale(h, w, V, n, j + 1, h2, vnorm);
+    Column c = z.column(R);
+    c.sel = sel;
+    c.tol = tol;
+    c.last = j + 1 == R ? 1 : 0;
+    krylov_step(h, V, n, j + 1, w, z.h1, z.h2, c);
   }
-  hipLaunchKernelGGL(backsub_kernel, dim3(1), dim3(1), 0, h.stream, H, ldh, R, g, ycoef,
-                     (const int *)(sel + 1));
-  PSE_LAUNCH_CHECK();
-  gemv_small(h, V, n, R, ycoef, x, n, 1.0, true, sel + 1);
+  gmres_update(h, z, R + 1, V, n, R, x, false, sel + 1);
   hipLaunchKernelGGL(gmres_stats_kernel, dim3(1), dim3(1), 0, h.stream, (const int *)sel,
-                     (const double *)res_hist, (const double *)bn, h.dstats);
+                     (const double *)z.res_hist, (const double *)z.bn, h.dstats);
   PSE_LAUNCH_CHECK();
 }
 

@@ -214,6 +214,9 @@ struct Handle {
   size_t small_len;
   double *dots = nullptr;    // partial sums for reductions
   size_t dots_len;
+  // host memory that the Krylov kernels of synchronous solves write their
+  // scalars to (not in handles with an arena, which run no solve)
+  double *kry = nullptr;
 
   Profiler prof;
 
@@ -270,6 +273,8 @@ void clear_graphs(Handle &h);
 std::shared_mutex &capture_gate();
 void dev_alloc(void **p, size_t bytes);          // hipMalloc; throws on failure
 void dev_free(void *p);                          // hipFree of a non-null pointer
+void *host_alloc(size_t bytes);                  // pinned host memory; throws on failure
+void host_free(void *p);
 hipError_t dev_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind);
 
 // Sets the calling thread's stream-capture interaction mode to relaxed for
@@ -490,31 +495,21 @@ void real_es(Handle &h, const double *x, const double *in, Layout lin, double *o
 // ---- krylov.hip / blas
 void vzero(Handle &h, double *v, size_t n);
 void fill_int(Handle &h, int *v, size_t n, int value);   // kernel, not a memset node
-void vcopy(Handle &h, double *dst, const double *src, size_t n);
 void vaxpby(Handle &h, double a, const double *x, double b, double *y, size_t n);
-void multi_dot(Handle &h, const double *V, size_t ldv, int m, const double *w,
-               size_t n, double *dev_out);
-void vsub_multi(Handle &h, double *w, const double *V, size_t ldv, int m,
-                const double *coef_dev, size_t n);
+void norm2_dev(Handle &h, const double *v, size_t n, double *dev_norm2);   // v . v
 void gemv_small(Handle &h, const double *V, size_t ldv, int m,
                 const double *coef_dev, double *y, size_t n, double alpha,
                 bool accumulate, const int *m_dev = nullptr);
-void vscale_dev(Handle &h, double *dst, const double *src, const double *s_dev,
-                bool invert, size_t n);
-void gather_comps(Handle &h, const double *src, int sstride, const CompSet &cs,
-                  double *dst, size_t n);
-void scatter_comps(Handle &h, const double *src, const CompSet &cs,
-                   double *dst, int dstride, size_t n, bool accumulate,
-                   double alpha);
 
 struct KrylovResult {
   int iters;
   double resid;      // Lanczos: last relative change; GMRES: relative residual
   bool converged;
+  double bnorm;      // |b| (0: the result is zero)
 };
 using Op = std::function<void(const double *in, double *out)>;
 // prev_iters (may be null): the previous solve's iteration count, read and
-// updated; the convergence checks start two iterations before it.
+// updated; the convergence checks start shortly before it.
 KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n,
                           double *y, int maxit, double tol, int *prev_iters);
 KrylovResult gmres(Handle &h, const Op &A, const double *b, size_t n, double *x,
