@@ -195,6 +195,12 @@ __global__ void f2d_kernel(const float2 *src, double2 *dst, size_t n) {
 
 // ------------------------------------------------------------ operators --
 
+// End of a synchronous call.
+static void finish(Handle &h) {
+  PSE_HIP(hipStreamSynchronize(h.stream));
+  verify_lists(h);
+}
+
 // Result rows to the caller's order; with check, non-finite numbers in the
 // caller's rows are reported.
 static void return_rows(Handle &h, const double *src, int w, int lo, int hi, double *out,
@@ -203,11 +209,16 @@ static void return_rows(Handle &h, const double *src, int w, int lo, int hi, dou
     scatter_rows(h, src, w, lo, hi, out);
     return;
   }
-  int *flag = reinterpret_cast<int *>(h.small + h.small_len - 2), bad = 0;
-  fill_int(h, flag, 1, 0);
+  // (asynchronous handles reach here from the allocation-free product only)
+  int *flag = h.info + INFO_FINITE, bad = 0;
+  if (!h.arena) *(volatile int *)flag = 0;
+  else if (h.async) fill_int(h, flag, 1, 0);
   scatter_rows(h, src, w, lo, hi, out, flag);
-  PSE_HIP(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, h.stream));
+  if (h.arena)
+    PSE_HIP(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, h.stream));
   PSE_HIP(hipStreamSynchronize(h.stream));
+  verify_lists(h);
+  if (!h.arena) bad = *(volatile int *)flag;
   if (bad) throw Error{PSE_ERR_NONFINITE, "non-finite mobility product (non-finite input?)"};
 }
 
@@ -308,10 +319,7 @@ static void wave_apply_dg(Handle &h, const DGPlan &d, const double *xw, const do
   if (hc) {
     // couplets onto the next three grids (measured faster than spreading
     // forces and couplets in one launch: 1.4 + 1.4 against 3.9 ms at 512^3)
-    CompSet cc{};
-    for (int k = 0; k < cin.n; ++k)
-      if (cin.idx[k] >= 3) cc.idx[cc.n++] = cin.idx[k];
-    spread_deriv<T>(h, in, lin, cc, false, d.hL, d.hS, gc);
+    spread_deriv<T>(h, in, lin, d.hL, d.hS, gc);
   }
   if (d.hf && !reuse_forces) rfft_xy<T>(h, gin, G.twiddle, d.gin.n, -1);
   else if (hc) rfft_xy<T>(h, gc, G.twiddle, 3, -1);
@@ -757,7 +765,8 @@ static void create(const pse_params &p, Handle &h) {
     handle_alloc(h, (void **)&h.kdg, (size_t)ktable_len(ng) * sizeof(double));
     if (h.mixed) handle_alloc(h, (void **)&h.kdg32, (size_t)ktable_len(ng) * sizeof(float));
   }
-  handle_alloc(h, (void **)&h.bad_pos, 64);
+  if (h.arena) handle_alloc(h, (void **)&h.info, INFO_WORDS * sizeof(int));
+  else h.info = (int *)host_alloc(INFO_WORDS * sizeof(int));
   build_ktable(h);
   if (h.stile) {
     const size_t ntile = (size_t)h.sbins.nc * h.sbins.nc * h.sbins.nc;
@@ -765,7 +774,10 @@ static void create(const pse_params &p, Handle &h) {
     handle_alloc(h, (void **)&h.tl_start, (ntile + 1) * sizeof(int));
     handle_alloc(h, (void **)&h.tl_scan, ((ntile + 1023) / 1024 + 8) * sizeof(int));
     h.tl_cap = n * tiles_per_particle(h.d.support, h.stile);
-    handle_alloc(h, (void **)&h.tl_rec, h.tl_cap * tile_record_bytes(h.stile) + 256);
+    handle_alloc(h, (void **)&h.tl_rec, h.tl_cap * sizeof(TileRec));
+    const size_t entries = 3 * n * (size_t)weight_row(h.d.support, h.stile) * (h.deriv ? 2 : 1);
+    handle_alloc(h, (void **)&h.wt64, entries * sizeof(double));
+    if (h.mixed) handle_alloc(h, (void **)&h.wt32, entries * sizeof(float));
   }
   handle_alloc(h, (void **)&h.pl_cnt, n * sizeof(int));
   handle_alloc(h, (void **)&h.pl_start, (n + 1) * sizeof(int));
@@ -833,11 +845,12 @@ static void release(Handle &h) {
                   h.order, h.xw, h.xh, h.v0, h.v1, h.v2, h.v3, h.v4, h.v5, h.es_b, h.es_x, h.es_r,
                   h.es_d, h.es_p, h.lz_V, h.gm_V, h.small, h.dots, h.ktab, h.pl_cnt,
                   h.pl_start, h.pl_scan, h.pl_nbr, h.pl_rec64, h.pl_rec32, h.tl_cnt, h.tl_start,
-                  h.tl_scan, h.tl_rec, h.bad_pos, h.ktab32, h.dctl, h.dstats, h.dstep,
+                  h.tl_scan, h.tl_rec, h.wt64, h.wt32, h.ktab32, h.dctl, h.dstats, h.dstep,
                   h.dg_mu, h.mpack, h.kdg, h.kdg32};
   if (!h.arena)
     for (void *p : ptrs) dev_free(p);
   host_free(h.kry);
+  if (!h.arena) host_free(h.info);
   clear_graphs(h);
   for (hipEvent_t e : h.prof.pool) (void)hipEventDestroy(e);
   h.prof.pool.clear();
@@ -847,12 +860,25 @@ static void release(Handle &h) {
   }
 }
 
+// Runs f, an entry point's work, and turns what it throws into a status.  A
+// pair list beyond its capacity (Regrow) grows and f starts over: results are
+// handed over only after the lists they depend on were verified, so a run that
+// stops there has left the caller's state as it was.
 template <typename F> static int guarded(pse_handle *hd, F &&f) {
   RelaxedCaptureScope relaxed;
   // an error left by the caller's own runtime calls is not this call's
   (void)hipGetLastError();
   try {
-    f();
+    for (bool done = false; !done;) {
+      try {
+        f();
+        done = true;
+      } catch (const Regrow &r) {
+        if (!hd) throw Error{PSE_ERR_NOMEM, "pair list beyond its capacity"};
+        PSE_HIP(hipStreamSynchronize(hd->h.stream));
+        regrow_pairs(hd->h, r.total);
+      }
+    }
     if (hd && !hd->h.prof.pending.empty()) {
       PSE_HIP(hipStreamSynchronize(hd->h.stream));
       prof_resolve(hd->h);
@@ -1104,6 +1130,7 @@ int pse_brownian_sample(pse_handle *hd, const double *x, const double *psi_real,
   int warn = PSE_OK;
   const int rc = guarded(hd, [&] {
     Handle &h = hd->h;
+    warn = PSE_OK;
     pse_stats st{};
     st.converged = 1;
     st.fp64_residual = -1;
@@ -1136,7 +1163,7 @@ int pse_brownian_sample(pse_handle *hd, const double *x, const double *psi_real,
       PSE_LAUNCH_CHECK();
       return;
     }
-    PSE_HIP(hipStreamSynchronize(h.stream));
+    finish(h);
     if (stats) *stats = st;
   });
   return rc != PSE_OK ? rc : warn;
@@ -1154,6 +1181,7 @@ int pse_constrained_step(pse_handle *hd, double *x, const double *FL, double dt,
   const int rc = guarded(hd, [&] {
     Handle &h = hd->h;
     const int64_t n = h.n;
+    warn = PSE_OK;
     pse_stats st{};
     st.fp64_residual = -1;
     bool converged = true;
@@ -1235,7 +1263,7 @@ int pse_constrained_step(pse_handle *hd, double *x, const double *FL, double dt,
       PSE_LAUNCH_CHECK();
       return;
     }
-    PSE_HIP(hipStreamSynchronize(h.stream));
+    finish(h);
     st.converged = converged ? 1 : 0;
     if (!converged) warn = PSE_WARN_NOT_CONVERGED;
     if (stats) *stats = st;
@@ -1279,6 +1307,7 @@ int pse_rpy_step(pse_handle *hd, double *x, const double *F, double dt, uint64_t
     Handle &h = hd->h;
     const int64_t n = h.n;
     const CompSet u3 = comps_range(0, 3);
+    warn = PSE_OK;
     pse_stats st{};
     st.fp64_residual = -1;
     const bool dev_step = h.async && step == PSE_STEP_DEVICE;
@@ -1335,7 +1364,7 @@ int pse_rpy_step(pse_handle *hd, double *x, const double *F, double dt, uint64_t
       PSE_LAUNCH_CHECK();
       return;
     }
-    PSE_HIP(hipStreamSynchronize(h.stream));
+    finish(h);
     st.converged = lr.converged ? 1 : 0;
     if (!lr.converged) warn = PSE_WARN_NOT_CONVERGED;
     if (stats) *stats = st;
@@ -1413,7 +1442,7 @@ int pse_spread(pse_handle *hd, const double *x, const double *q, int ncomp, doub
       spread<double>(h, h.xw, h.v4, Layout{ncomp, 0}, cs, g);
       to_double<double>(h, g, cnt, out);
     }
-    PSE_HIP(hipStreamSynchronize(h.stream));
+    finish(h);
   });
 }
 
@@ -1439,7 +1468,7 @@ int pse_interpolate(pse_handle *hd, const double *x, const double *g, int ncomp,
       interpolate<double>(h, h.xw, gg, cs, h.v5, Layout{ncomp, 0}, false, 1.0);
     }
     scatter_rows(h, h.v5, ncomp, 0, ncomp, out);
-    PSE_HIP(hipStreamSynchronize(h.stream));
+    finish(h);
   });
 }
 

@@ -15,21 +15,11 @@
 #include <type_traits>
 
 #include "fftreg.h"
+#include "stencil.h"
 
 namespace pse {
 
 // ---------------------------------------------------------------- helpers --
-
-__device__ __forceinline__ int wrapi(int i, int n) {
-  i %= n;
-  return i < 0 ? i + n : i;
-}
-
-// First stencil index and the grid offset of a particle coordinate.
-__device__ __forceinline__ int stencil_start(double xc, double h, int P) {
-  const double f = xc / h;
-  return (P & 1) ? (int)floor(f + 0.5) - (P - 1) / 2 : (int)floor(f) - P / 2 + 1;
-}
 
 template <typename T> __device__ __forceinline__ T &part(cplx<T> &z, int k) {
   return (k & 1) ? z.y : z.x;
@@ -73,207 +63,133 @@ spread_kernel(const double *__restrict__ x, const double *__restrict__ q,
   }
 }
 
-// Whether a stencil starting at grid index st (P points) meets the tile
-// starting at t0 (S points) on a periodic axis of ng points.
-__device__ __forceinline__ bool stencil_meets(int st, int t0, int P, int S, int ng) {
-  int a = (t0 - st) % ng;
-  a += a < 0 ? ng : 0;
-  return a < P || a > ng - S;
-}
+// Gather form of the spreading sum: one wavefront per tile of S^3 grid points
+// goes through the tile's candidates (TileRec: a particle and where the tile's
+// window lies in its weight rows).  The Gaussian factorises over the axes, and
+// a lane owns one z-column of an 8^3 tile (ZPT of its points; on grids below
+// 24, tiles of 4^3 points, one point).  TCH candidates at a time are staged in
+// the wavefront's own part of LDS -- their windows by half a wavefront each,
+// their moments by one lane each -- with all loads in flight together, so a
+// tile pays the memory's latency once per chunk, and no barrier.  (Loads by
+// scalar instructions one candidate ahead were bound by that latency: 1.45
+// against 1.01 ms per gradient spreading at 512^3, N = 10^6, and 1.33 for
+// records of weights written per tile and candidate.)  z planes that the
+// stencil does not reach are skipped, four of eight on average at support 8.
+// Every grid point is written exactly once: no atomics and no zeroing pass.
+// Neighbouring tiles, in blocks of 4^3, run on one XCD, whose L2 they share
+// their particles' rows and complete their cache lines in.
+constexpr int TCH = 16;
 
-// The candidate lists hold one record per (tile, particle) pair: the
-// particle index (rp) and REC_W(S) doubles (rw): the one-dimensional Gaussian
-// weights at the tile's S grid positions along x, y and z (zero outside the
-// stencil), then per axis the offset d0 such that d0 + i h is the distance
-// from the particle to tile position i wherever the weight is nonzero (the
-// gradient weights of derivative gridding are -2 kcoef (d0 + i h) w_i).  They
-// depend on the positions only, so they are formed once per position update,
-// when the lists are built.
-struct TileRecs {
-  int *p;
-  double *w;
+template <int S, int ZPT> struct TileLane {
+  int tile, tc[3], lx, ly, z0;    // z0: first z point; S = 4: the lane's own
+  __device__ __forceinline__ TileLane(int nb) {
+    constexpr int PARTS = S == 8 ? 8 / ZPT : 1;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int unit = (int)xcd_block(blockIdx.x, gridDim.x) * 4 + wave;
+    const int lane = threadIdx.x & 63, u = unit / PARTS;
+    if (nb % 4 == 0) {
+      const int b = u / 64, i = u % 64, n4 = nb / 4;
+      tc[0] = (b % n4) * 4 + i % 4;
+      tc[1] = (b / n4) % n4 * 4 + i / 4 % 4;
+      tc[2] = b / (n4 * n4) * 4 + i / 16;
+    } else {
+      tc[0] = u % nb;
+      tc[1] = u / nb % nb;
+      tc[2] = u / (nb * nb);
+    }
+    tile = (tc[2] * nb + tc[1]) * nb + tc[0];
+    lx = lane % S;
+    ly = (lane / S) % S;
+    z0 = S == 8 ? (unit % PARTS) * ZPT : lane / (S * S);
+  }
+  __device__ __forceinline__ size_t point(int ng, int z) const {
+    return ((size_t)(tc[2] * S + z0 + z) * ng + tc[1] * S + ly) * ng + tc[0] * S + lx;
+  }
 };
 
-// FILL = false: count each tile's candidates; true: write their records from
-// start[tile] on, in bin order and ranked with a ballot.  One wavefront per
-// tile enumerates the particles of the 27 bins around it 64 at a time (bins
-// are tiles; a stencil reaches at most one tile beyond its particle's).
-template <bool FILL>
+// Stages up to TCH candidates rec[0..cnt): item i of candidate c's windows
+// (axis i / S, position i % S) at items[c * 3 S + i], W = entry(row index).
+// Two candidates per step, half a wavefront each.
+template <typename W, int S, typename Entry>
+__device__ __forceinline__ void stage_windows(const TileRec &r, int cnt, int rw, W *items,
+                                              Entry entry) {
+  constexpr int NI = 3 * S;
+  const int lane = threadIdx.x & 63, i = lane & 31, axis = min(i / S, 2);
+  const bool upper = lane >= 32;
+  W v[TCH / 2];
+#pragma unroll
+  for (int k = 0; k < TCH / 2; ++k) {
+    if (2 * k >= cnt) break;
+    const int c1 = min(2 * k + 1, cnt - 1);
+    const int p0 = __builtin_amdgcn_readlane(r.p, 2 * k), p1 = __builtin_amdgcn_readlane(r.p, c1);
+    const int w0 = __builtin_amdgcn_readlane(r.win, 2 * k),
+              w1 = __builtin_amdgcn_readlane(r.win, c1);
+    const int p = upper ? p1 : p0, win = upper ? w1 : w0;
+    // (lanes past the items read a window's entry too and drop it)
+    v[k] = entry((size_t)p * (3 * rw) + axis * rw + ((win >> (8 * axis)) & 255) + i % S);
+  }
+  if (i >= NI) return;
+#pragma unroll
+  for (int k = 0; k < TCH / 2; ++k) {
+    if (2 * k >= cnt) break;
+    items[(2 * k + (lane >> 5)) * NI + i] = v[k];
+  }
+}
+
+// Moments: component k of grid k is sum_b q_bk K(x_n - x_b).
+template <typename T, int E, int S, int NCM, int ZPT>
 __global__ void __launch_bounds__(256)
-tile_list_kernel(const double *__restrict__ x, GridGeom g, int S, int nb,
-                 const int *__restrict__ bstart, const int *__restrict__ bperm,
-                 int *__restrict__ cnt, const int *__restrict__ start, TileRecs rec) {
-  const int tile = blockIdx.x * 4 + threadIdx.x / 64;
-  const int lane = threadIdx.x % 64;
-  if (tile >= nb * nb * nb) return;
-  const int tc[3] = {tile % nb, (tile / nb) % nb, tile / (nb * nb)};
-  const int P = g.P, ng = g.ng;
-  int first, pre, total;
-  nbr27_setup(lane, tc[0], tc[1], tc[2], nb, bstart, first, pre, total);
-  int pos = FILL ? start[tile] : 0;
-  int count = 0;
-  for (int base = 0; base < total; base += 64) {
-    const int idx = base + lane;
-    const int s = nbr27_slot(idx, first, pre);
-    bool ok = false;
-    int p = 0, st[3] = {0, 0, 0};
-    if (idx < total) {
-      p = bperm[s];
-      ok = true;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        st[d] = stencil_start(x[3 * p + d], g.h, P);
-        ok = ok && stencil_meets(st[d], tc[d] * S, P, S, ng);
-      }
-    }
-    if (!FILL) {
-      count += ok ? 1 : 0;
-    } else {
-      const unsigned long long m = __ballot(ok);
-      if (ok) {
-        // the record's particle and, in its first offset slot, the tile's
-        // index; tile_weights_kernel forms the weights and offsets (on every
-        // lane, not on the lanes of a candidate batch that met the tile)
-        const int e = pos + __popcll(m & ((1ull << lane) - 1ull));
-        rec.p[e] = p;
-        rec.w[(size_t)e * (3 * S + 3) + 3 * S] = (double)tile;
-      }
-      pos += __popcll(m);
-    }
-  }
-  if (!FILL) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off, 64);
-    if (lane == 0) cnt[tile] = count;
-  }
-}
-
-// Second half of the tile-list fill: for every record, the S
-// one-dimensional weights of its particle at the tile's grid positions along
-// each axis (zero outside its stencil) and the offset d0 of the first
-// stencil point inside the tile from that position.  A workgroup takes
-// TW_RECS records, one thread per (record, axis), forms their 3 S + 3
-// numbers in LDS and writes them back as one contiguous block, so the stores
-// are coalesced (written in place, each record's numbers stride 3 S + 3
-// apart across the threads).
-constexpr int TW_RECS = 64;
-
-__global__ void __launch_bounds__(3 * TW_RECS)
-tile_weights_kernel(const double *__restrict__ x, GridGeom g, int S, int nb,
-                    const int *__restrict__ total, int64_t cap, TileRecs rec) {
-  extern __shared__ double tw_block[];   // TW_RECS records of 3 S + 3
-  const int RW = 3 * S + 3;
-  const int64_t len = min((int64_t)total[0], cap);
-  const int64_t e0 = (int64_t)blockIdx.x * TW_RECS;
-  if (e0 >= len) return;
-  const int nrec = (int)min((int64_t)TW_RECS, len - e0);
-  const int tid = threadIdx.x;
-  const int j = tid / 3, d = tid % 3;
-  if (j < nrec) {
-    const int64_t e = e0 + j;
-    const int P = g.P, ng = g.ng;
-    const int p = rec.p[e];
-    // the tile's first grid index along the axis, from the tile index the
-    // list fill left in the record
-    const int tile = (int)rec.w[(size_t)e * RW + 3 * S];
-    const int t0 = (d == 0 ? tile % nb : (d == 1 ? (tile / nb) % nb : tile / (nb * nb))) * S;
-    const double xd = x[3 * p + d];
-    const int st = stencil_start(xd, g.h, P);
-    double d0 = 0.0;
-    for (int i = 0; i < S; ++i) {
-      int a = (t0 + i - st) % ng;
-      a += a < 0 ? ng : 0;
-      double wi = 0.0;
-      if (a < P) {
-        const double dx = (st + a) * g.h - xd;
-        wi = g.knorm * exp(-g.kcoef * dx * dx);
-        d0 = dx - i * g.h;
-      }
-      tw_block[j * RW + d * S + i] = wi;
-    }
-    tw_block[j * RW + 3 * S + d] = d0;
-  }
-  __syncthreads();
-  double *dst = rec.w + (size_t)e0 * RW;
-  for (int k = tid; k < nrec * RW; k += blockDim.x) dst[k] = tw_block[k];
-}
-
-// Gather form of the spreading sum: one workgroup per tile of S^3 grid
-// points reads the tile's candidate records.  The Gaussian factorises over
-// the axes, K = w_x w_y w_z, and the records carry the 1D weights, so a chunk
-// of candidates is staged in LDS with one coalesced read of its weights and
-// one gather of its moments.  Each thread owns ZPT points of one z-column of
-// the tile and, per candidate, forms w_x w_y once and reads the moments once
-// for all of them.  Every grid point is written exactly once: no atomics and
-// no zeroing pass.
-constexpr int GMAXC = 32;
-
-template <typename T, int S, int NCM, int ZPT>
-__global__ void __launch_bounds__(S * S * S / ZPT)
-spread_list_kernel(const double *__restrict__ q, Layout lq, CompSet cs, GridGeom g, int nb,
-                   const int *__restrict__ tstart, TileRecs rec, T *__restrict__ grids,
-                   size_t ngrid) {
-  constexpr int NT = S * S * S / ZPT;
-  constexpr int RW = 3 * S + 3;
-  constexpr int WPT = (GMAXC * RW + NT - 1) / NT;
-  constexpr int NCMP = NCM + (NCM & 1);
-  static_assert(GMAXC <= NT, "one candidate per thread in the moment gather");
-  __shared__ T wts[GMAXC * RW];
-  __shared__ T cq[GMAXC * NCMP];
-  const int tile = blockIdx.x;
-  const int tc[3] = {tile % nb, (tile / nb) % nb, tile / (nb * nb)};
-  const int lo = tstart[tile];
-  const int total = tstart[tile + 1] - lo;
-  const int ng = g.ng;
-  const int tid = threadIdx.x;
-  const int lx = tid % S, ly = (tid / S) % S, z0 = (tid / (S * S)) * ZPT;
+spread_tile_kernel(const double *__restrict__ q, Layout lq, CompSet cs, int ng, int P, int nb,
+                   const int *__restrict__ tstart, const TileRec *__restrict__ rec,
+                   const T *__restrict__ wt, int rw, T *__restrict__ grids, size_t ngrid) {
+  constexpr int NI = 3 * S, NQ = (NCM + 3) / 4 * 4;
+  __shared__ __align__(16) T lds_w[4][TCH * NI], lds_q[4][TCH * NQ];
+  const TileLane<S, ZPT> L(nb);
+  if (L.tile >= nb * nb * nb) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  T *items = lds_w[wave], *mom = lds_q[wave];
+  const int lo = tstart[L.tile], hi = tstart[L.tile + 1];
   T acc[ZPT][NCM];
 #pragma unroll
   for (int z = 0; z < ZPT; ++z)
 #pragma unroll
     for (int k = 0; k < NCM; ++k) acc[z][k] = (T)0;
-  for (int c0 = 0; c0 < total; c0 += GMAXC) {
-    const int nchunk = min(GMAXC, total - c0);
-    const int nw = nchunk * RW;
-    __syncthreads();
-    const int pj = tid < nchunk ? rec.p[lo + c0 + tid] : 0;
-    const double *wsrc = rec.w + (size_t)(lo + c0) * RW;
-    double wv[WPT];
+  for (int base = lo; base < hi; base += TCH) {
+    const int cnt = min(TCH, hi - base);
+    const TileRec r = rec[base + min(lane, cnt - 1)];
+    double qv[NCM];
+    if (lane < cnt) {
+      const double *qp = q + (size_t)r.p * lq.stride - lq.off;
 #pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int t = tid + i * NT;
-      wv[i] = t < nw ? wsrc[t] : 0.0;
+      for (int k = 0; k < NCM; ++k) qv[k] = k < cs.n ? qp[cs.idx[k]] : 0.0;
     }
-    if (tid < nchunk) {
+    stage_windows<T, S>(r, cnt, rw, items, [&](size_t e) { return wt[e * E]; });
+    if (lane < cnt)
 #pragma unroll
-      for (int k = 0; k < NCM; ++k)
-        if (k < cs.n) cq[tid * NCMP + k] = (T)q[(size_t)pj * lq.stride + cs.idx[k] - lq.off];
-    }
+      for (int k = 0; k < NCM; ++k) mom[lane * NQ + k] = (T)qv[k];
+    __builtin_amdgcn_wave_barrier();
+    for (int c = 0; c < cnt; ++c) {
+      const int wz = __builtin_amdgcn_readlane(r.win, c) >> 16;
+      const T *w = items + c * NI;
+      const T wxy = w[L.lx] * w[S + L.ly];
+      T f[NCM];
 #pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int t = tid + i * NT;
-      if (t < nw) wts[t] = (T)wv[i];
-    }
-    __syncthreads();
-    for (int j = 0; j < nchunk; ++j) {
-      const T *wj = wts + j * RW;
-      const T wxy = wj[lx] * wj[S + ly];
-      T qk[NCM];
+      for (int k = 0; k < NCM; ++k) f[k] = mom[c * NQ + k] * wxy;
+      T zw[ZPT];
 #pragma unroll
-      for (int k = 0; k < NCM; ++k) qk[k] = cq[j * NCMP + k];
+      for (int z = 0; z < ZPT; ++z) zw[z] = w[2 * S + L.z0 + z];
 #pragma unroll
       for (int z = 0; z < ZPT; ++z) {
-        const T w = wxy * wj[2 * S + z0 + z];
+        if (S == 8 && (unsigned)(wz + L.z0 + z - (S - 1)) >= (unsigned)P) continue;
 #pragma unroll
-        for (int k = 0; k < NCM; ++k)
-          if (k < cs.n) acc[z][k] += w * qk[k];
+        for (int k = 0; k < NCM; ++k) acc[z][k] += zw[z] * f[k];
       }
     }
+    __builtin_amdgcn_wave_barrier();
   }
 #pragma unroll
   for (int z = 0; z < ZPT; ++z) {
-    const size_t gi = ((size_t)(tc[2] * S + z0 + z) * ng + tc[1] * S + ly) * ng
-                      + tc[0] * S + lx;
+    const size_t gi = L.point(ng, z);
 #pragma unroll
     for (int k = 0; k < NCM; ++k)
       if (k < cs.n) grids[(size_t)k * ngrid + gi] = acc[z][k];
@@ -287,126 +203,87 @@ spread_list_kernel(const double *__restrict__ q, Layout lq, CompSet cs, GridGeom
 // transform is i C^ k K^, so the k-space factors of the stresslet column,
 // -3 i f1(ka) Y_q k, and of the torque column, (3/2) i f1(ka) k x e_c,
 // become one factor -3 f1(ka) on D^ (Eq. WSops with the gradient moved onto
-// the Gaussian).  With HF the forces are spread as well, onto three grids
-// ahead of the couplet grids: F_i K (x_n - x_b), the moment gridding of F.
-// Input groups (forces 0-2, torques 3-5, stresslets 6-10) are either all in
-// cs or absent (hasL, hasS).  Tiles, records and staging as
-// spread_list_kernel; per candidate the gradient weights along each axis are
-// g_i = -2 kcoef (d0 + i h) w_i, and per point dK/dx = g_x w_y w_z, etc.
-template <typename T, int S, int ZPT, bool HF>
-__global__ void __launch_bounds__(S * S * S / ZPT)
-spread_deriv_kernel(const double *__restrict__ q, Layout lq, CompSet cs, int hasL, int hasS,
-                    GridGeom g, int nb, const int *__restrict__ tstart, TileRecs rec,
-                    const double *__restrict__ mu, T *__restrict__ grids, size_t ngrid) {
-  constexpr int NT = S * S * S / ZPT;
-  constexpr int RW = 3 * S + 3;
-  constexpr int WPT = (GMAXC * RW + NT - 1) / NT;
-  constexpr int NQ = HF ? 12 : 9;      // per candidate: C (9), then F (3)
-  constexpr int NG = HF ? 6 : 3;
-  static_assert(GMAXC <= NT, "one candidate per thread in the moment gather");
-  __shared__ double raw[GMAXC * RW];
-  __shared__ T wg[GMAXC * 6 * S];      // per candidate: w (3 S), then g (3 S)
-  __shared__ T cq[GMAXC * NQ];
-  __shared__ double cmu[GMAXC * 6];   // per candidate: mu (3), lambda (3)
-  const int tile = blockIdx.x;
-  const int tc[3] = {tile % nb, (tile / nb) % nb, tile / (nb * nb)};
-  const int lo = tstart[tile];
-  const int total = tstart[tile + 1] - lo;
-  const int ng = g.ng;
-  const int tid = threadIdx.x;
-  const int lx = tid % S, ly = (tid / S) % S, z0 = (tid / (S * S)) * ZPT;
-  const T r2 = (T)0.70710678118654752440, r6 = (T)0.40824829046386301637;
-  // positions of the groups in cs (cs lists them in increasing order)
-  const int kL = HF ? 3 : 0, kS = kL + (hasL ? 3 : 0);
-  T acc[ZPT][NG];
+// the Gaussian).  Torques (HL) and stresslets (HS), either or both, start at
+// components iL and iS of the vector.  Per point
+//   D_i = (C_ix g_x w_y + C_iy w_x g_y) w_z + C_iz w_x w_y g_z,
+// the two brackets constant along the lane's z-column.
+template <typename T, int S, int ZPT, bool HL, bool HS>
+__global__ void __launch_bounds__(256)
+spread_deriv_kernel(const double *__restrict__ q, Layout lq, int iL, int iS, int ng, int P, int nb,
+                    const int *__restrict__ tstart, const TileRec *__restrict__ rec,
+                    const cplx<T> *__restrict__ wt, int rw, T *__restrict__ grids, size_t ngrid) {
+  using W = cplx<T>;   // (weight, gradient weight)
+  constexpr int NI = 3 * S, NQ = 12;
+  __shared__ __align__(16) W lds_w[4][TCH * NI];
+  __shared__ __align__(16) T lds_c[4][TCH * NQ];
+  const TileLane<S, ZPT> L(nb);
+  if (L.tile >= nb * nb * nb) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  W *items = lds_w[wave];
+  T *cpl = lds_c[wave];
+  const int lo = tstart[L.tile], hi = tstart[L.tile + 1];
+  T acc[ZPT][3];
 #pragma unroll
   for (int z = 0; z < ZPT; ++z)
 #pragma unroll
-    for (int k = 0; k < NG; ++k) acc[z][k] = (T)0;
-  for (int c0 = 0; c0 < total; c0 += GMAXC) {
-    const int nchunk = min(GMAXC, total - c0);
-    const int nw = nchunk * RW;
-    __syncthreads();
-    const int pj = tid < nchunk ? rec.p[lo + c0 + tid] : 0;
-    const double *wsrc = rec.w + (size_t)(lo + c0) * RW;
-    double wv[WPT];
+    for (int k = 0; k < 3; ++k) acc[z][k] = (T)0;
+  for (int base = lo; base < hi; base += TCH) {
+    const int cnt = min(TCH, hi - base);
+    const TileRec r = rec[base + min(lane, cnt - 1)];
+    double sv[5] = {}, lv[3] = {};
+    if (lane < cnt) {
+      const double *qp = q + (size_t)r.p * lq.stride - lq.off;
+      if constexpr (HS)
 #pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int t = tid + i * NT;
-      wv[i] = t < nw ? wsrc[t] : 0.0;
+        for (int k = 0; k < 5; ++k) sv[k] = qp[iS + k];
+      if constexpr (HL)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) lv[k] = qp[iL + k];
     }
-    if (tid < nchunk) {
-      const double *qp = q + (size_t)pj * lq.stride - lq.off;
-      T sq[5] = {(T)0, (T)0, (T)0, (T)0, (T)0}, lh[3] = {(T)0, (T)0, (T)0};
-      if (hasS)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) sq[k] = (T)qp[cs.idx[kS + k]];
-      if (hasL)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) lh[k] = (T)0.5 * (T)qp[cs.idx[kL + k]];
-      const T sxy = r2 * sq[0], sxz = r2 * sq[1], syz = r2 * sq[2];
-      T *o = cq + tid * NQ;
-      o[0] = r2 * sq[3] + r6 * sq[4];          // Cxx
-      o[1] = sxy - lh[2];                      // Cxy
-      o[2] = sxz + lh[1];                      // Cxz
-      o[3] = sxy + lh[2];                      // Cyx
-      o[4] = -r2 * sq[3] + r6 * sq[4];         // Cyy
-      o[5] = syz - lh[0];                      // Cyz
-      o[6] = sxz - lh[1];                      // Czx
-      o[7] = syz + lh[0];                      // Czy
-      o[8] = (T)-2 * r6 * sq[4];               // Czz
-      if constexpr (HF)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) o[9 + k] = (T)qp[cs.idx[k]];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) cmu[tid * 6 + k] = mu[6 * (size_t)pj + k];
+    stage_windows<W, S>(r, cnt, rw, items, [&](size_t e) { return wt[e]; });
+    if (lane < cnt) {
+      const T r2 = (T)0.70710678118654752440, r6 = (T)0.40824829046386301637;
+      const T xy = r2 * (T)sv[0], xz = r2 * (T)sv[1], yz = r2 * (T)sv[2], a = r2 * (T)sv[3],
+              b = r6 * (T)sv[4];
+      const T lx = (T)0.5 * (T)lv[0], ly = (T)0.5 * (T)lv[1], lz = (T)0.5 * (T)lv[2];
+      T *o = cpl + lane * NQ;   // rows of C, four apart
+      o[0] = b + a;      o[1] = xy - lz;  o[2] = xz + ly;
+      o[4] = xy + lz;    o[5] = b - a;    o[6] = yz - lx;
+      o[8] = xz - ly;    o[9] = yz + lx;  o[10] = (T)-2 * b;
     }
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int t = tid + i * NT;
-      if (t < nw) raw[t] = wv[i];
-    }
-    __syncthreads();
-    for (int t = tid; t < nchunk * 3 * S; t += NT) {
-      const int j = t / (3 * S), r = t % (3 * S), d = r / S, i = r % S;
-      const double w = raw[j * RW + r];
-      const double dx = raw[j * RW + 3 * S + d] + i * g.h;
-      wg[j * 6 * S + r] = (T)w;
-      wg[j * 6 * S + 3 * S + r] =
-          (T)(cmu[j * 6 + 3 + d] * (-2.0 * g.kcoef * dx - cmu[j * 6 + d]) * w);
-    }
-    __syncthreads();
-    for (int j = 0; j < nchunk; ++j) {
-      const T *wj = wg + j * 6 * S, *gj = wj + 3 * S, *cj = cq + j * NQ;
-      const T gxwy = gj[lx] * wj[S + ly], wxgy = wj[lx] * gj[S + ly], wxwy = wj[lx] * wj[S + ly];
-      // D_i = (C_ix g_x w_y + C_iy w_x g_y) w_z + C_iz w_x w_y g_z: the two
-      // brackets are constant along the thread's z-column
-      T a[3], b[3], f[3];
+    __builtin_amdgcn_wave_barrier();
+    for (int c = 0; c < cnt; ++c) {
+      const int wz = __builtin_amdgcn_readlane(r.win, c) >> 16;
+      const W *w = items + c * NI;
+      const T *C = cpl + c * NQ;
+      const W X = w[L.lx], Y = w[S + L.ly];
+      const T gxwy = X.y * Y.x, wxgy = X.x * Y.y, wxwy = X.x * Y.x;
+      T a[3], b[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        a[i] = cj[3 * i] * gxwy + cj[3 * i + 1] * wxgy;
-        b[i] = cj[3 * i + 2] * wxwy;
+        a[i] = C[4 * i] * gxwy + C[4 * i + 1] * wxgy;
+        b[i] = C[4 * i + 2] * wxwy;
       }
-      if constexpr (HF)
+      W zw[ZPT];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) f[i] = cj[9 + i] * wxwy;
+      for (int z = 0; z < ZPT; ++z) zw[z] = w[2 * S + L.z0 + z];
 #pragma unroll
       for (int z = 0; z < ZPT; ++z) {
-        const T wz = wj[2 * S + z0 + z], gz = gj[2 * S + z0 + z];
+        if (S == 8 && (unsigned)(wz + L.z0 + z - (S - 1)) >= (unsigned)P) continue;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-          if constexpr (HF) acc[z][i] += f[i] * wz;
-          acc[z][NG - 3 + i] += a[i] * wz + b[i] * gz;
+          acc[z][i] += a[i] * zw[z].x;
+          acc[z][i] += b[i] * zw[z].y;
         }
       }
     }
+    __builtin_amdgcn_wave_barrier();
   }
 #pragma unroll
   for (int z = 0; z < ZPT; ++z) {
-    const size_t gi = ((size_t)(tc[2] * S + z0 + z) * ng + tc[1] * S + ly) * ng
-                      + tc[0] * S + lx;
+    const size_t gi = L.point(ng, z);
 #pragma unroll
-    for (int k = 0; k < NG; ++k) grids[(size_t)k * ngrid + gi] = acc[z][k];
+    for (int k = 0; k < 3; ++k) grids[(size_t)k * ngrid + gi] = acc[z][k];
   }
 }
 
@@ -1341,20 +1218,6 @@ __global__ void to_double_kernel(const T *src, size_t n, double *dst) {
 
 // ----------------------------------------------------------- host side --
 
-static GridGeom geom(const Handle &h) {
-  GridGeom g;
-  g.ng = h.d.grid;
-  g.P = h.d.support;
-  g.L = h.p.box;
-  g.h = h.d.h;
-  const double xi2 = h.d.xi * h.d.xi;
-  g.kcoef = 2.0 * xi2 / h.d.eta_s;
-  g.knorm = sqrt(2.0 * xi2 / (M_PI * h.d.eta_s));
-  g.def = h.def.on;
-  for (int i = 0; i < 6; ++i) g.G[i] = h.def.G[i];
-  return g;
-}
-
 static KGeom kgeom(const Handle &h) {
   KGeom k;
   k.ng = h.d.grid;
@@ -1410,89 +1273,6 @@ void build_ktable(Handle &h) {
   }
 }
 
-namespace {
-
-// The record arrays inside the handle's tile-record allocation: tl_cap
-// particle indices, then (from a 256-byte boundary) tl_cap x 3 S weights.
-TileRecs tile_recs(const Handle &h) {
-  const size_t off = (h.tl_cap * sizeof(int) + 255) / 256 * 256;
-  return TileRecs{(int *)h.tl_rec, (double *)((char *)h.tl_rec + off)};
-}
-
-}  // namespace
-
-// Candidate lists of the spreading tiles for wrapped positions xw (after the
-// spreading bins are current).
-// The capacity N * (ceil((P-1)/S) + 1)^3 is the most tiles a stencil can
-// meet, so the lists never overflow.
-void build_tile_lists(Handle &h, const double *xw) {
-  if (!h.stile) return;
-  const GridGeom g = geom(h);
-  const int nb = h.sbins.nc;
-  const int ntile = nb * nb * nb;
-  const unsigned blocks = (unsigned)((ntile + 3) / 4);
-  hipLaunchKernelGGL((tile_list_kernel<false>), dim3(blocks), dim3(256), 0, h.stream, xw, g,
-                     h.stile, nb, (const int *)h.sbins.start, (const int *)h.sbins.perm,
-                     h.tl_cnt, nullptr, TileRecs{nullptr, nullptr});
-  PSE_LAUNCH_CHECK();
-  exclusive_scan(h, h.tl_cnt, h.tl_start, h.tl_scan, ntile);
-  hipLaunchKernelGGL((tile_list_kernel<true>), dim3(blocks), dim3(256), 0, h.stream, xw, g,
-                     h.stile, nb, (const int *)h.sbins.start, (const int *)h.sbins.perm, nullptr,
-                     (const int *)h.tl_start, tile_recs(h));
-  PSE_LAUNCH_CHECK();
-  // grid over the capacity; the kernel reads the list's length on the device
-  hipLaunchKernelGGL(tile_weights_kernel, dim3(nblocks(h.tl_cap, TW_RECS)), dim3(3 * TW_RECS),
-                     (size_t)TW_RECS * (3 * h.stile + 3) * sizeof(double), h.stream, xw, g,
-                     h.stile, nb, (const int *)h.tl_start + ntile, (int64_t)h.tl_cap,
-                     tile_recs(h));
-  PSE_LAUNCH_CHECK();
-}
-
-// Moment correction of the gradient weights of derivative gridding.  On the
-// grid the gradient of the truncated Gaussian does not have the moments of
-// the continuous one: along axis d its one-dimensional weights
-// g_i = dK1/dx (x_i - x) sum to mu_d times the Gaussian's, sum_i g_i =
-// mu_d sum_i w_i, with mu_d a small number that depends on the particle's
-// offset from the grid, and their first moment sum_i d_i g_i (d_i = x_i - x)
-// differs from -sum_i w_i, its continuous value.  A spread couplet then
-// leaves a spurious monopole in the smallest wave numbers, where the Stokes
-// kernel amplifies it, and the interpolated gradient of a smooth field picks
-// up the field itself.  Spreading and interpolation take instead
-// lambda_d (g_i - mu_d w_i), still separable, whose discrete sum is zero and
-// whose first moment is -sum_i w_i: the gradient of a constant field is
-// zero and that of a linear field exact, relative to the Gaussian's own
-// normalisation.  mu and lambda (three each per particle) are formed once
-// per position update.
-__global__ void __launch_bounds__(256)
-dg_mu_kernel(const double *__restrict__ x, int64_t n, GridGeom g, double *__restrict__ mu) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 3 * n) return;
-  const double xc = x[t];
-  const int i0 = stencil_start(xc, g.h, g.P);
-  double s0 = 0.0, s1 = 0.0, sd = 0.0, sd1 = 0.0;
-  for (int i = 0; i < g.P; ++i) {
-    const double d = (i0 + i) * g.h - xc;
-    const double w = exp(-g.kcoef * d * d);
-    const double gi = -2.0 * g.kcoef * d * w;
-    s0 += w;
-    s1 += gi;
-    sd += d * w;
-    sd1 += d * gi;
-  }
-  const double m = s1 / s0;
-  // sum_i d_i (g_i - m w_i) = sd1 - m sd
-  const int64_t p = t / 3, ax = t % 3;
-  mu[6 * p + ax] = m;
-  mu[6 * p + 3 + ax] = -s0 / (sd1 - m * sd);
-}
-
-void build_dg_mu(Handle &h, const double *xw) {
-  if (!h.deriv) return;
-  hipLaunchKernelGGL(dg_mu_kernel, dim3(nblocks(3 * (size_t)h.n, 256)), dim3(256), 0, h.stream,
-                     xw, h.n, geom(h), h.dg_mu);
-  PSE_LAUNCH_CHECK();
-}
-
 size_t tile_record_bytes(int S) { return sizeof(int) + (3 * (size_t)S + 3) * sizeof(double); }
 
 namespace {
@@ -1516,7 +1296,7 @@ template <typename F> void with_ncm(int n, F f) {
 // come first and give the velocity by plain interpolation.  One wavefront
 // per particle as interp_kernel; per stencil point the gradient weight is
 // lambda (-2 kcoef d - mu) K(d), d = x_n - x_p, with the moment corrections
-// mu, lambda of the particle (see dg_mu_kernel).  cs: the output components (velocity 0-2
+// mu, lambda of the particle (see weight_rows).  cs: the output components (velocity 0-2
 // with HU, rotation 3-5, strain 6-10), any subset.
 template <typename T, int MAXIT, bool HU>
 __global__ void __launch_bounds__(256)
@@ -1676,31 +1456,55 @@ interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids, s
   }
 }
 
+template <typename T> static const T *weights(const Handle &h) {
+  if constexpr (sizeof(T) == 8) return h.wt64;
+  else return h.wt32;
+}
+
+// Workgroups of the tile kernels: four wavefronts each, `parts` per tile.
+static dim3 tile_blocks(const Handle &h, int parts) {
+  const size_t nb = (size_t)h.sbins.nc;
+  return dim3(nblocks(nb * nb * nb * parts, 4));
+}
+
+static void check_tiles(const Handle &h) {
+  if (!h.tiles_current)
+    throw Error{PSE_ERR_INVALID, "spreading tile lists not built for these positions"};
+  if (h.stile != 4 && h.stile != 8)
+    throw Error{PSE_ERR_INVALID, "unsupported spreading tile"};
+}
+
 template <typename T>
 void spread(Handle &h, const double *x, const double *q, Layout lq, const CompSet &cs,
             T *grids) {
   const GridGeom g = geom(h);
   if (h.stile) {
-    if (!h.tiles_current)
-      throw Error{PSE_ERR_INVALID, "spreading tile lists not built for these positions"};
+    check_tiles(h);
     ProfScope ps(h, PK_SPREAD, (double)cs.n * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
-    const int nb = h.sbins.nc;
-    const unsigned tiles = (unsigned)nb * nb * nb;
-    const TileRecs rec = tile_recs(h);
-    const int *ts = (const int *)h.tl_start;
-    with_ncm(cs.n, [&](auto ncm) {
-      constexpr int M = decltype(ncm)::value;
-      // z points per thread: a whole column of the tile while the
-      // accumulators fit, half of it for the 11-component product
-      constexpr int Z8 = M <= 6 ? 8 : 4;
-      if (h.stile == 4)
-        hipLaunchKernelGGL((spread_list_kernel<T, 4, M, 1>), dim3(tiles), dim3(64), 0,
-                           h.stream, q, lq, cs, g, nb, ts, rec, grids, h.ngrid);
-      else if (h.stile == 8)
-        hipLaunchKernelGGL((spread_list_kernel<T, 8, M, Z8>), dim3(tiles), dim3(512 / Z8), 0,
-                           h.stream, q, lq, cs, g, nb, ts, rec, grids, h.ngrid);
-      else
-        throw Error{PSE_ERR_INVALID, "unsupported spreading tile"};
+    const int rw = weight_row(g.P, h.stile);
+    const auto launch = [&](auto e, auto s, auto m, auto z) {
+      constexpr int E = decltype(e)::value, S = decltype(s)::value, M = decltype(m)::value,
+                    Z = decltype(z)::value;
+      hipLaunchKernelGGL((spread_tile_kernel<T, E, S, M, Z>), tile_blocks(h, S == 8 ? 8 / Z : 1),
+                         dim3(256), 0, h.stream, q, lq, cs, g.ng, g.P, h.sbins.nc,
+                         (const int *)h.tl_start, (const TileRec *)h.tl_rec, weights<T>(h), rw,
+                         grids, h.ngrid);
+    };
+    with_ncm(cs.n, [&](auto m) {
+      // a lane's whole column while its accumulators leave room for several
+      // wavefronts, half of it for the 11-component product
+      using Z8 = std::integral_constant<int, decltype(m)::value <= 6 ? 8 : 4>;
+      using I1 = std::integral_constant<int, 1>;
+      using I2 = std::integral_constant<int, 2>;
+      using I4 = std::integral_constant<int, 4>;
+      using I8 = std::integral_constant<int, 8>;
+      if (h.deriv) {
+        if (h.stile == 8) launch(I2(), I8(), m, Z8());
+        else launch(I2(), I4(), m, I1());
+      } else {
+        if (h.stile == 8) launch(I1(), I8(), m, Z8());
+        else launch(I1(), I4(), m, I1());
+      }
     });
     PSE_LAUNCH_CHECK();
     return;
@@ -1746,40 +1550,32 @@ void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, 
   PSE_LAUNCH_CHECK();
 }
 
-// Derivative gridding of the constraint operator (tile lists required): the
-// stresslet components cs (five, in the Y_q basis) of q in layout lq spread
-// onto three grids with the Gaussian's gradient.
+// Derivative gridding of couplets (tile lists required): the torques (hasL)
+// and stresslets (hasS) of q in layout lq onto three grids with the Gaussian's
+// gradient.
 template <typename T>
-void spread_deriv(Handle &h, const double *q, Layout lq, const CompSet &cs, bool hf, bool hasL,
-                  bool hasS, T *grids) {
+void spread_deriv(Handle &h, const double *q, Layout lq, bool hasL, bool hasS, T *grids) {
   if (!h.stile) throw Error{PSE_ERR_INVALID, "derivative gridding unavailable"};
-  if (!h.tiles_current)
-    throw Error{PSE_ERR_INVALID, "spreading tile lists not built for these positions"};
+  check_tiles(h);
   const GridGeom g = geom(h);
-  const int ng = hf ? 6 : 3;
-  ProfScope ps(h, PK_SPREAD, (double)ng * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
-  const int nb = h.sbins.nc;
-  const unsigned tiles = (unsigned)nb * nb * nb;
-  const TileRecs rec = tile_recs(h);
-  const int *ts = (const int *)h.tl_start;
-  const int L = hasL ? 1 : 0, S3 = hasS ? 1 : 0;
-  if (h.stile == 4) {
-    if (hf)
-      hipLaunchKernelGGL((spread_deriv_kernel<T, 4, 1, true>), dim3(tiles), dim3(64), 0,
-                         h.stream, q, lq, cs, L, S3, g, nb, ts, rec, h.dg_mu, grids, h.ngrid);
-    else
-      hipLaunchKernelGGL((spread_deriv_kernel<T, 4, 1, false>), dim3(tiles), dim3(64), 0,
-                         h.stream, q, lq, cs, L, S3, g, nb, ts, rec, h.dg_mu, grids, h.ngrid);
-  } else if (h.stile == 8) {
-    if (hf)
-      hipLaunchKernelGGL((spread_deriv_kernel<T, 8, 4, true>), dim3(tiles), dim3(128), 0,
-                         h.stream, q, lq, cs, L, S3, g, nb, ts, rec, h.dg_mu, grids, h.ngrid);
-    else
-      hipLaunchKernelGGL((spread_deriv_kernel<T, 8, 4, false>), dim3(tiles), dim3(128), 0,
-                         h.stream, q, lq, cs, L, S3, g, nb, ts, rec, h.dg_mu, grids, h.ngrid);
-  } else {
-    throw Error{PSE_ERR_INVALID, "unsupported spreading tile"};
-  }
+  const int ncomp = (hasL ? 3 : 0) + (hasS ? 5 : 0);
+  ProfScope ps(h, PK_SPREAD, 3.0 * h.ngrid * sizeof(T) + (double)h.n * (3 + ncomp) * 8);
+  const int rw = weight_row(g.P, h.stile);
+  const auto launch = [&](auto s, auto z, auto hl, auto hs) {
+    constexpr int S = decltype(s)::value, Z = decltype(z)::value;
+    hipLaunchKernelGGL((spread_deriv_kernel<T, S, Z, decltype(hl)::value, decltype(hs)::value>),
+                       tile_blocks(h, 1), dim3(256), 0, h.stream, q, lq, 3, 6, g.ng, g.P,
+                       h.sbins.nc, (const int *)h.tl_start, (const TileRec *)h.tl_rec,
+                       reinterpret_cast<const cplx<T> *>(weights<T>(h)), rw, grids, h.ngrid);
+  };
+  const auto tile = [&](auto hl, auto hs) {
+    if (h.stile == 8)
+      launch(std::integral_constant<int, 8>(), std::integral_constant<int, 8>(), hl, hs);
+    else launch(std::integral_constant<int, 4>(), std::integral_constant<int, 1>(), hl, hs);
+  };
+  if (hasL && hasS) tile(std::true_type(), std::true_type());
+  else if (hasL) tile(std::true_type(), std::false_type());
+  else tile(std::false_type(), std::true_type());
   PSE_LAUNCH_CHECK();
 }
 
@@ -1960,8 +1756,7 @@ template <typename T> void to_double(Handle &h, const T *src, size_t n, double *
   template void kspace_fused<T>(Handle &, const cplx<T> *, const CompSet &,      \
                                 cplx<T> *, const CompSet &, const cplx<T> *,     \
                                 bool);                                           \
-  template void spread_deriv<T>(Handle &, const double *, Layout, const CompSet &, \
-                                bool, bool, bool, T *);                          \
+  template void spread_deriv<T>(Handle &, const double *, Layout, bool, bool, T *); \
   template void interp_deriv<T>(Handle &, const double *, const T *, bool,       \
                                 const CompSet &, double *, Layout, bool, double); \
   template void zero_grids<T>(Handle &, T *, int);                               \

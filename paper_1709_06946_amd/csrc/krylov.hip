@@ -773,6 +773,7 @@ lanczos_sqrt_kernel(const double *alpha, const double *beta, int m, const double
 // non-finite input vector or operator result).
 static void host_scalars(Handle &h, int hcap, int n) {
   PSE_HIP(hipStreamSynchronize(h.stream));
+  verify_lists(h);
   const volatile double *k = h.kry;
   bool ok = std::isfinite(k[0]);
   for (int i = 0; i < n; ++i) ok = ok && std::isfinite(k[1 + i]) && std::isfinite(k[1 + hcap + i]);

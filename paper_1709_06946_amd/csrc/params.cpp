@@ -230,11 +230,13 @@ size_t footprint(const pse_params &p, const pse_derived &d) {
   const int S = spread_tile(d.grid, d.support);
   const size_t tiles3 = S ? ng3 / ((size_t)S * S * S) : 0;
   if (S) {
-    // tile CSR and one record per (tile, particle) pair: the particle index,
-    // 3 S one-dimensional weights and 3 offsets
+    // tile CSR, one record per (tile, particle) pair, and the particles'
+    // weight rows (gradient weights too with derivative gridding; both
+    // precisions in mixed handles)
     const size_t cap = n * tiles_per_particle(d.support, S);
-    bytes += (2 * tiles3 + tiles3 / 1024 + 16) * sizeof(int)
-             + cap * (sizeof(int) + (3 * (size_t)S + 3) * sizeof(double)) + 256;
+    bytes += (2 * tiles3 + tiles3 / 1024 + 16) * sizeof(int) + cap * sizeof(TileRec);
+    bytes += 3 * n * (size_t)weight_row(d.support, S) * (d.deriv_gridding == 2 ? 2 : 1) *
+             (sizeof(double) + (mixed ? sizeof(float) : 0));
   }
   bytes += (2 * (ncell3 + tiles3) + 4 + (ncell3 + tiles3) / 1024 + 16) * sizeof(int)
            + 8 * n * sizeof(int);

@@ -90,6 +90,12 @@ struct GridGeom {
   double G[6];
 };
 
+// One (tile, particle) pair of the spreading tiles' lists: win holds the
+// window start of the tile in the particle's weight rows, a byte per axis.
+struct TileRec {
+  int p, win;
+};
+
 // Device workspace of one precision.
 template <typename T> struct GridSet {
   cplx<T> *gin = nullptr;    // MAX_PACK packed complex grids
@@ -176,7 +182,7 @@ struct Handle {
 
   // particle work vectors (double, N x 11 each)
   // (in the library's own order of the call: particle t is the caller's
-  // order[t], see sort_positions)
+  // order[t], see prepare_positions)
   int *order = nullptr;      // N
   double *xw = nullptr;      // wrapped positions N x 3
   double *xh = nullptr;      // mid-point positions N x 3
@@ -191,7 +197,10 @@ struct Handle {
   float *ktab32 = nullptr;   // the same rounded to float (mixed handles)
   double *kdg = nullptr;     // derivative gridding: the constraint operator's k-space
   float *kdg32 = nullptr;    // factor -9 f1^2 mob per |k|^2 (FP64; FP32 in mixed handles)
-  int *bad_pos = nullptr;    // set by the wrap kernel on a non-finite coordinate
+  // words that kernels report to the host (INFO_*): pinned host memory, or the
+  // arena's; lists_open lists of the running call are not yet verified
+  int *info = nullptr;
+  int lists_open = 0;
   double *dg_mu = nullptr;   // derivative gridding: moment corrections, 6 per particle
   void *mpack = nullptr;     // pair sums: moments packed 12 per particle (FP64 size)
   // real-space pair list (CSR in cell order): start[N+1], neighbour index and
@@ -204,8 +213,12 @@ struct Handle {
   // spreading-tile candidate lists (CSR over tiles): one record per (tile,
   // particle) pair, tl_cap records at most
   int *tl_cnt = nullptr, *tl_start = nullptr, *tl_scan = nullptr;
-  void *tl_rec = nullptr;
+  TileRec *tl_rec = nullptr;
   size_t tl_cap = 0;
+  // one-dimensional Gaussian weights per particle and axis, in the precisions
+  // the handle spreads in (see weight_rows)
+  double *wt64 = nullptr;
+  float *wt32 = nullptr;
 
   // Krylov storage
   double *lz_V = nullptr;    // (lanczos_maxit + 1) x 11N
@@ -250,6 +263,16 @@ struct Handle {
   // allocation, 256-byte aligned) instead of the runtime, and frees nothing.
   unsigned char *arena = nullptr;
   size_t arena_size = 0, arena_used = 0;
+};
+
+// Words of h.info: a non-finite position was met, the lengths of the pair
+// lists built since the last look (two at most), a non-finite result.
+enum { INFO_BAD = 0, INFO_PAIRS = 1, INFO_LISTS = 2, INFO_FINITE = 3, INFO_WORDS = 4 };
+
+// Thrown by verify_lists: the pair list needs `total` entries; the call starts
+// over once its storage has grown.
+struct Regrow {
+  size_t total;
 };
 
 // Device control words of a handle (ints at h.dctl): Lanczos and GMRES
@@ -360,14 +383,12 @@ bool kspace_noise_z(Handle &h, const double *psi, uint64_t seed, uint64_t counte
 template <typename T>
 void kspace_fused(Handle &h, const cplx<T> *in, const CompSet &cin, cplx<T> *out,
                   const CompSet &cout, const cplx<T> *tw, bool dg = false);
-// derivative gridding: forces (hf: all three in cs, first) onto three grids
-// and couplets (torques with hasL, stresslets with hasS, complete groups in
-// cs, in that order) onto three more; interpolation of velocity (hu) from
-// the first three of six grids and of rotation and strain from the gradient
-// of the other three (any components cs)
+// derivative gridding: couplets (torques with hasL, stresslets with hasS) onto
+// three grids; interpolation of velocity (hu) from the first three of six
+// grids and of rotation and strain from the gradient of the other three (any
+// components cs)
 template <typename T>
-void spread_deriv(Handle &h, const double *q, Layout lq, const CompSet &cs, bool hf, bool hasL,
-                  bool hasS, T *grids);
+void spread_deriv(Handle &h, const double *q, Layout lq, bool hasL, bool hasS, T *grids);
 template <typename T>
 void interp_deriv(Handle &h, const double *x, const T *grids, bool hu, const CompSet &cs,
                   double *out, Layout lo, bool accumulate, double scale);
@@ -377,10 +398,6 @@ template <typename T>
 void kspace_deformed(Handle &h, const cplx<T> *in, const CompSet &cin, cplx<T> *out,
                      const CompSet &cout);
 template <typename T> void zero_grids(Handle &h, T *g, int ncomp);
-void build_tile_lists(Handle &h, const double *xw);
-// moment corrections of the gradient weights (derivative-gridding handles)
-void build_dg_mu(Handle &h, const double *xw);
-size_t tile_record_bytes(int S);                  // one (tile, particle) record
 int ktable_len(int grid);                         // entries of the |k|^2 table
 void build_ktable(Handle &h);
 template <typename T> void from_double(Handle &h, const double *src, size_t n, T *dst);
@@ -406,6 +423,8 @@ inline size_t tiles_per_particle(int P, int S) {
   const size_t k = (size_t)((P - 1 + S - 1) / S + 1);
   return k * k * k;
 }
+// Entries of a weight row (P weights with S - 1 zeros on either side).
+inline int weight_row(int P, int S) { return P + 2 * (S - 1); }
 // Spreading tile side: the stencil may reach one tile beyond its particle's
 // bin, with one grid point of slack for rounding in the bin assignment.
 inline int spread_tile(int grid, int P) {
@@ -468,22 +487,26 @@ __device__ __forceinline__ int nbr27_slot(int idx, int first, int pre) {
   return __shfl(first, lo, 64) + idx - __shfl(pre, lo, 64);
 }
 
-// ---- real.hip
-void build_tables(Handle &h);
-void exclusive_scan(Handle &h, const int *in, int *out, int *tmp, int n);
+// ---- lists.hip
 // The caller's positions x wrapped and put in the library's order (h.order,
-// h.xw) with their cells; with lists, prepare_positions builds the pair list
-// too, and the spreading bins and tile lists unless spreading is false
-// (positions where only pair sums and interpolation run).
-void sort_positions(Handle &h, const double *x);
+// h.xw) with their cells and pair list, and the spreading bins, tile lists
+// and weights too unless spreading is false (positions where only pair sums
+// and interpolation run).
 void prepare_positions(Handle &h, const double *x, bool spreading = true);
 // Cells and lists for wrapped positions xw already in the library's order.
 void build_cells(Handle &h, const double *xw, bool spreading = true);
+// Synchronous calls: looks at what the kernels reported, once the stream is
+// idle (throws on non-finite positions; Regrow on a list beyond its capacity).
+void verify_lists(Handle &h);
+void regrow_pairs(Handle &h, size_t total);
 // dst[t] = src[order[t]], and dst[order[t]] = src[t] for the components
 // [lo, hi) of rows of w numbers (bad: see scatter_rows_kernel).
 void gather_rows(Handle &h, const double *src, int w, double *dst);
 void scatter_rows(Handle &h, const double *src, int w, int lo, int hi, double *dst,
                   int *bad = nullptr);
+
+// ---- real.hip
+void build_tables(Handle &h);
 template <typename T>
 void real_apply(Handle &h, const double *x, const double *in, Layout lin,
                 const CompSet &cin, double *out, Layout lout, const CompSet &cout);

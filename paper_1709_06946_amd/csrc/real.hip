@@ -30,7 +30,7 @@
 // Both are tabulated once per handle on the GPU (FP64) on a uniform r grid
 // with a node at r = 2a, and interpolated with 4-point Lagrange stencils that
 // never straddle r = 2a.
-#include "pse_internal.h"
+#include "pairrec.h"
 
 namespace pse {
 
@@ -196,326 +196,7 @@ void build_tables(Handle &h) {
   PSE_LAUNCH_CHECK();
 }
 
-// ---------------------------------------------------------- positions --
-
-// Non-finite coordinates raise *bad and are replaced by 0, so that every
-// later kernel stays in bounds until the host reports the error.
-// Positions of a deformed lattice to lattice coordinates A^-1 x (then
-// wrapped like the cube's).
-__global__ void lattice_coords_kernel(const double *__restrict__ x, double *__restrict__ xl,
-                                      int64_t n, Deform df) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double p[3] = {x[3 * i], x[3 * i + 1], x[3 * i + 2]};
-  for (int r = 0; r < 3; ++r)
-    xl[3 * i + r] = df.Ai[3 * r] * p[0] + df.Ai[3 * r + 1] * p[1] + df.Ai[3 * r + 2] * p[2];
-}
-
-__global__ void wrap_kernel(const double *__restrict__ x, double *__restrict__ xw,
-                            int64_t n3, double L, int *__restrict__ bad,
-                            int *__restrict__ status) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n3) return;
-  double v = x[i];
-  if (!isfinite(v)) {
-    *bad = 1;
-    atomicOr(status, (int)PSE_STATUS_NONFINITE_POS);
-    v = 0.0;
-  }
-  v -= L * floor(v / L);
-  if (v >= L) v -= L;
-  if (v < 0) v = 0;
-  xw[i] = v;
-}
-
-static void wrap_positions(Handle &h, const double *x, double *xw) {
-  // the flag is cleared by a kernel, not a memset node, so that the launches
-  // can be captured into graphs
-  fill_int(h, h.bad_pos, 1, 0);
-  if (h.def.on) {
-    // lattice coordinates first, then wrapped in place like the cube's
-    hipLaunchKernelGGL(lattice_coords_kernel, dim3(nblocks(h.n, 256)), dim3(256), 0,
-                       h.stream, x, xw, h.n, h.def);
-    PSE_LAUNCH_CHECK();
-    x = xw;
-  }
-  hipLaunchKernelGGL(wrap_kernel, dim3(nblocks(3 * h.n, 256)), dim3(256), 0,
-                     h.stream, x, xw, 3 * h.n, h.p.box, h.bad_pos, h.dctl + CTL_STATUS);
-  PSE_LAUNCH_CHECK();
-}
-
-// ----------------------------------------------------------- cell list --
-
-__global__ void cell_assign_kernel(const double *__restrict__ xw, int64_t n,
-                                   int nc, double inv_cs, int *__restrict__ cell_of,
-                                   int *__restrict__ slot, int *__restrict__ count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int c[3];
-  for (int d = 0; d < 3; ++d) {
-    int v = (int)(xw[3 * i + d] * inv_cs);
-    c[d] = v < 0 ? 0 : (v >= nc ? nc - 1 : v);
-  }
-  const int cell = (c[2] * nc + c[1]) * nc + c[0];
-  cell_of[i] = cell;
-  slot[i] = atomicAdd(&count[cell], 1);
-}
-
-// Exclusive scan in chunks of 1024 (256 threads x 4).
-__global__ void scan_block_kernel(const int *__restrict__ in, int *__restrict__ out,
-                                  int *__restrict__ block_sums, int n) {
-  __shared__ int s[256];
-  const int base = blockIdx.x * 1024 + threadIdx.x * 4;
-  int v[4], sum = 0;
-  for (int j = 0; j < 4; ++j) {
-    v[j] = base + j < n ? in[base + j] : 0;
-    sum += v[j];
-  }
-  s[threadIdx.x] = sum;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-    __syncthreads();
-    s[threadIdx.x] += t;
-    __syncthreads();
-  }
-  int run = s[threadIdx.x] - sum;
-  for (int j = 0; j < 4; ++j) {
-    if (base + j < n) out[base + j] = run;
-    run += v[j];
-  }
-  if (threadIdx.x == 255) block_sums[blockIdx.x] = s[255];
-}
-
-__global__ void scan_sums_kernel(int *__restrict__ sums, int nb, int *__restrict__ total) {
-  // single block: exclusive scan of nb block sums with a running carry
-  __shared__ int s[256];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int b0 = 0; b0 < nb; b0 += 256) {
-    const int i = b0 + threadIdx.x;
-    const int v = i < nb ? sums[i] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const int t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-      __syncthreads();
-      s[threadIdx.x] += t;
-      __syncthreads();
-    }
-    if (i < nb) sums[i] = carry + s[threadIdx.x] - v;
-    __syncthreads();
-    if (threadIdx.x == 255) carry += s[255];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *total = carry;
-}
-
-__global__ void scan_add_kernel(int *__restrict__ out, const int *__restrict__ sums, int n) {
-  const int i = blockIdx.x * 1024 + threadIdx.x * 4;
-  const int add = sums[blockIdx.x];
-  for (int j = 0; j < 4; ++j)
-    if (i + j < n) out[i + j] += add;
-}
-
-// Exclusive scan of at most 1024 x SCAN1_PER ints in one workgroup: thread
-// t takes a contiguous chunk, the chunk totals are scanned within each wave
-// (shuffles) and across the 16 waves (LDS), and every thread then writes its
-// chunk's prefixes; out[n] = total.  One launch instead of three.
-constexpr int SCAN1_PER = 16;
-
-__global__ void __launch_bounds__(1024)
-scan_single_kernel(const int *__restrict__ in, int *__restrict__ out, int n) {
-  __shared__ int wsum[16];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int per = (n + 1023) / 1024;
-  const int lo = t * per, hi = min(lo + per, n);
-  int sum = 0;
-  for (int i = lo; i < hi; ++i) sum += in[i];
-  int incl = sum;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int u = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += u;
-  }
-  if (lane == 63) wsum[wv] = incl;
-  __syncthreads();
-  if (wv == 0) {
-    const int w = lane < 16 ? wsum[lane] : 0;
-    int wi = w;
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-      const int u = __shfl_up(wi, off, 64);
-      if (lane >= off) wi += u;
-    }
-    if (lane < 16) wsum[lane] = wi - w;
-  }
-  __syncthreads();
-  int run = wsum[wv] + incl - sum;
-  for (int i = lo; i < hi; ++i) {
-    const int x = in[i];
-    out[i] = run;
-    run += x;
-  }
-  if (t == 1023) out[n] = run;
-}
-
-__global__ void cell_scatter_kernel(const int *__restrict__ cell_of,
-                                    const int *__restrict__ slot,
-                                    const int *__restrict__ start, int64_t n,
-                                    int *__restrict__ scat) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  scat[start[cell_of[i]] + slot[i]] = (int)i;
-}
-
-// The arrival order within a bin (atomic slots) varies from run to run; every
-// later sum runs in bin order, so each bin's members are put in increasing
-// particle index: one wavefront per bin, member p going to the position of
-// its rank among the bin's indices.  Results are then reproducible bit for
-// bit.  at[t]: the bin of position t.
-// SORT: the particles themselves take this order (the library's own order of
-// a call, see sort_positions): order[t] is the caller's index of particle t,
-// xs its position, and perm the identity.
-template <bool SORT>
-__global__ void __launch_bounds__(256)
-cell_order_kernel(const int *__restrict__ start, const int *__restrict__ scat, int nbins,
-                  int *__restrict__ perm, int *__restrict__ at, const double *__restrict__ x,
-                  int *__restrict__ order, double *__restrict__ xs) {
-  const int bin = blockIdx.x * 4 + threadIdx.x / 64;
-  const int lane = threadIdx.x % 64;
-  if (bin >= nbins) return;
-  const int lo = start[bin], k = start[bin + 1] - lo;
-  for (int p = lane; p < k; p += 64) {
-    const int v = scat[lo + p];
-    int rank = 0;
-    for (int q = 0; q < k; ++q) rank += scat[lo + q] < v ? 1 : 0;
-    const int t = lo + rank;
-    at[t] = bin;
-    if constexpr (SORT) {
-      perm[t] = t;
-      order[t] = v;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) xs[3 * (size_t)t + d] = x[3 * (size_t)v + d];
-    } else {
-      perm[t] = v;
-    }
-  }
-}
-
-// Bin b of an nc^3 lattice (x fastest) at its position in block order:
-// blocks of BIN_BLOCK^3 bins in lexicographic order, bins lexicographic
-// within a block (partial blocks at the far faces).
-__device__ __forceinline__ int block_order_pos(int b, int nc) {
-  const int bx = b % nc, by = (b / nc) % nc, bz = b / (nc * nc);
-  const int B = BIN_BLOCK, nb = (nc + B - 1) / B;
-  const int Bx = bx / B, By = by / B, Bz = bz / B;
-  // bins before this block: full slabs and rows of blocks, with the widths
-  // of the partial blocks at the far faces
-  const auto w = [&](int blk) { return blk + 1 < nb ? B : nc - B * (nb - 1); };
-  const int wx = w(Bx), wy = w(By);
-  const int before = Bz * B * nc * nc + By * B * nc * w(Bz) + Bx * B * wy * w(Bz);
-  const int lx = bx - Bx * B, ly = by - By * B, lz = bz - Bz * B;
-  return before + (lz * wy + ly) * wx + lx;
-}
-
-// counts permuted into block order
-__global__ void block_count_kernel(const int *__restrict__ count, int nc,
-                                   int *__restrict__ bcount) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nc * nc * nc) return;
-  bcount[block_order_pos(b, nc)] = count[b];
-}
-
-// trav: each bin's members (in perm order) at the bin's block-order offset
-__global__ void block_trav_kernel(const int *__restrict__ start, const int *__restrict__ perm,
-                                  const int *__restrict__ bstart, int nc,
-                                  int *__restrict__ trav) {
-  const int b = blockIdx.x * 4 + threadIdx.x / 64;
-  const int lane = threadIdx.x % 64;
-  if (b >= nc * nc * nc) return;
-  const int lo = start[b], k = start[b + 1] - lo, dst = bstart[block_order_pos(b, nc)];
-  for (int p = lane; p < k; p += 64) trav[dst + p] = perm[lo + p];
-}
-
-// out[0..n] = exclusive prefix sums of in[0..n) (out[n] = total); tmp holds
-// n/1024 + 8 ints.
-void exclusive_scan(Handle &h, const int *in, int *out, int *tmp, int n) {
-  if (n <= 1024 * SCAN1_PER) {
-    hipLaunchKernelGGL(scan_single_kernel, dim3(1), dim3(1024), 0, h.stream, in, out, n);
-    PSE_LAUNCH_CHECK();
-    return;
-  }
-  const int sb = (n + 1023) / 1024;
-  hipLaunchKernelGGL(scan_block_kernel, dim3(sb), dim3(256), 0, h.stream, in, out, tmp, n);
-  PSE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, h.stream, tmp, sb, out + n);
-  PSE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(scan_add_kernel, dim3(sb), dim3(256), 0, h.stream, out, tmp, n);
-  PSE_LAUNCH_CHECK();
-}
-
-// Bins of the positions xw; with xs, the particles take the bins' order
-// (h.order) and xs their positions in it.
-static void build_bins(Handle &h, const double *xw, Bins &b, double *xs = nullptr) {
-  const int nc = b.nc;
-  const int ncells = nc * nc * nc;
-  fill_int(h, b.count, ncells, 0);
-  hipLaunchKernelGGL(cell_assign_kernel, dim3(nblocks(h.n, 256)), dim3(256), 0,
-                     h.stream, xw, h.n, nc, nc / h.p.box, b.of, b.slot, b.count);
-  PSE_LAUNCH_CHECK();
-  exclusive_scan(h, b.count, b.start, b.scan_tmp, ncells);
-  hipLaunchKernelGGL(cell_scatter_kernel, dim3(nblocks(h.n, 256)), dim3(256), 0,
-                     h.stream, b.of, b.slot, b.start, h.n, b.scat);
-  PSE_LAUNCH_CHECK();
-  // the arrival slots are not needed past the scatter: their array takes the
-  // bin of each position
-  if (xs)
-    hipLaunchKernelGGL(cell_order_kernel<true>, dim3((unsigned)((ncells + 3) / 4)), dim3(256), 0,
-                       h.stream, b.start, b.scat, ncells, b.perm, b.slot, xw, h.order, xs);
-  else
-    hipLaunchKernelGGL(cell_order_kernel<false>, dim3((unsigned)((ncells + 3) / 4)), dim3(256),
-                       0, h.stream, b.start, b.scat, ncells, b.perm, b.slot, xw, nullptr, nullptr);
-  PSE_LAUNCH_CHECK();
-  if (b.trav) {
-    hipLaunchKernelGGL(block_count_kernel, dim3(nblocks(ncells, 256)), dim3(256), 0, h.stream,
-                       b.count, nc, b.bcount);
-    PSE_LAUNCH_CHECK();
-    exclusive_scan(h, b.bcount, b.bstart, b.scan_tmp, ncells);
-    hipLaunchKernelGGL(block_trav_kernel, dim3((unsigned)((ncells + 3) / 4)), dim3(256), 0,
-                       h.stream, b.start, b.perm, b.bstart, nc, b.trav);
-    PSE_LAUNCH_CHECK();
-  }
-}
-
 // ------------------------------------------------------------ pair sum --
-
-template <typename T>
-__device__ __forceinline__ void lookup(const T *__restrict__ tab, T r, T inv_dr,
-                                       int n2a, int ntab, T *co) {
-  const T f = r * inv_dr;
-  int i0 = (int)f;
-  int base;
-  if (i0 < n2a) {
-    base = i0 - 1;
-    if (base < 0) base = 0;
-    if (base > n2a - 3) base = n2a - 3;
-  } else {
-    base = i0 - 1;
-    if (base < n2a) base = n2a;
-    if (base > ntab - 4) base = ntab - 4;
-  }
-  const T t = f - (T)base;
-  const T w0 = -(t - 1) * (t - 2) * (t - 3) / (T)6;
-  const T w1 = t * (t - 2) * (t - 3) / (T)2;
-  const T w2 = -t * (t - 1) * (t - 3) / (T)2;
-  const T w3 = t * (t - 1) * (t - 2) / (T)6;
-  const T *p = tab + (size_t)base * NCOEF;
-#pragma unroll
-  for (int j = 0; j < NCOEF; ++j)
-    co[j] = w0 * p[j] + w1 * p[NCOEF + j] + w2 * p[2 * NCOEF + j] + w3 * p[3 * NCOEF + j];
-}
 
 // Acting with the pair block M(r) on (F, C) of the partner; adds to U and D.
 // UF, UC: forces, couplets present; OU, OD: velocity, gradient wanted (the
@@ -680,185 +361,6 @@ __device__ __forceinline__ T group_sum(T v) {
   v += row_rotate<2>(v);
   v += row_rotate<1>(v);
   return v;
-}
-
-// ------------------------------------------------------------ pair list --
-// The positions stay fixed over all the operator applications of a Krylov
-// solve, so the neighbours within rcut are found once per position update
-// and stored as a CSR list in cell order: row t holds the neighbours of
-// particle perm[t].  Rows are filled in a fixed order (cells, then
-// candidates, ranked with a ballot inside the group).  Each entry holds the
-// neighbour index and the pair's data -- the seven interpolated radial
-// coefficients and the unit vector -- in the precision of the handle's own
-// pair sums (FP64 handles: doubles; mixed handles: floats, read by their
-// FP32 sums).  A sum in the other precision (the FP64 residual of a mixed
-// handle, once per step) forms the data from the positions itself.
-
-// Records lie in blocks of REC_BLOCK entries, field by field within a block: a
-// lane reaches every field of its entry from one address, and the six fields
-// of the stresslet-strain sum are one contiguous run of a block (2*10^5
-// spheres, 111 neighbours each, FP32: 349 -> 305 us for the whole sum, 213 ->
-// 190 for that block, against one array per field; FP64 at 2*10^4: 26 -> 24).
-constexpr int PAIR_REC = 10;
-constexpr int REC_BLOCK = 16;
-// fields: d2 d3 d4, the unit vector, a b, c1 c2 (see the list of radial
-// coefficients above)
-enum { F_D2 = 0, F_D3, F_D4, F_E, F_A = F_E + 3, F_B, F_C1, F_C2 };
-
-// Entry s of the records: field f at [f].
-template <typename R> struct Entry {
-  R *p;
-  __device__ __forceinline__ Entry(R *rec, uint32_t s)
-      : p(rec + (size_t)(s / REC_BLOCK) * (PAIR_REC * REC_BLOCK) + s % REC_BLOCK) {}
-  __device__ __forceinline__ R &operator[](int f) const { return p[f * REC_BLOCK]; }
-};
-
-struct PairArgs {
-  int64_t n;
-  int nc;
-  double L, rcut2;
-  double inv_cs, cs2;   // cells per unit length, squared cell side
-  double inv_dr;
-  int n2a, ntab;
-  int64_t cap;     // pair-list capacity: entries at or beyond it are not written
-  int *status;     // PSE_STATUS_PAIR_OVERFLOW is or-ed in when one is dropped
-  int def;         // deformed lattice: positions are lattice coordinates and
-  double A[9];     // separations are mapped back by A
-};
-
-// Separation x_i - x_j of wrapped positions: nearest image, and on a
-// deformed lattice mapped from lattice offsets to Cartesian ones (the cutoff
-// is at most a third of the cell's thinnest width, so the image is the
-// nearest one).
-__device__ __forceinline__ void separation(const double *__restrict__ xw, double xi0, double xi1,
-                                           double xi2, int j, double L, int def, const double *A,
-                                           double *d) {
-  d[0] = xi0 - xw[3 * j];
-  d[1] = xi1 - xw[3 * j + 1];
-  d[2] = xi2 - xw[3 * j + 2];
-  // positions are wrapped into [0, L): one image shift per axis suffices
-  const double hL = 0.5 * L;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) d[k] += d[k] > hL ? -L : (d[k] < -hL ? L : 0.0);
-  if (def) {
-    const double e[3] = {d[0], d[1], d[2]};
-#pragma unroll
-    for (int r = 0; r < 3; ++r) d[r] = A[3 * r] * e[0] + A[3 * r + 1] * e[1] + A[3 * r + 2] * e[2];
-  }
-}
-
-__device__ __forceinline__ bool near_pair(const double *__restrict__ xw, double xi0, double xi1,
-                                          double xi2, int j, const PairArgs &pa, double *d) {
-  separation(xw, xi0, xi1, xi2, j, pa.L, pa.def, pa.A, d);
-  return d[0] * d[0] + d[1] * d[1] + d[2] * d[2] < pa.rcut2;
-}
-
-// FILL = false: count the neighbours of each row into cnt[t]; FILL = true:
-// write them from start[t] on.  One wavefront per row enumerates the
-// candidates of the 27 cells around the particle 64 at a time.
-template <bool FILL>
-__global__ void __launch_bounds__(256)
-pair_list_kernel(const double *__restrict__ xw, const int *__restrict__ perm,
-                 const int *__restrict__ cell_start, const int *__restrict__ cell_at,
-                 PairArgs pa, int *__restrict__ cnt, const int *__restrict__ start,
-                 const double *__restrict__ tab, int *__restrict__ nbr,
-                 double *__restrict__ rec64, float *__restrict__ rec32) {
-  const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int lane = threadIdx.x % 64;
-  if (t >= pa.n) return;
-  const int i = perm[t];
-  const double xi0 = xw[3 * i], xi1 = xw[3 * i + 1], xi2 = xw[3 * i + 2];
-  const int nc = pa.nc;
-  const int ci = cell_at[t];
-  const int cc[3] = {ci % nc, (ci / nc) % nc, ci / (nc * nc)};
-  // a neighbouring cell whose gap to the particle exceeds the cutoff holds no
-  // neighbour: it is skipped (the list is the same; on a deformed lattice,
-  // where cell units are not lengths, every cell is searched)
-  bool skip = false;
-  if (!pa.def && lane < 27) {
-    const int off[3] = {lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1};
-    const double xi[3] = {xi0, xi1, xi2};
-    double g2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const double u = xi[d] * pa.inv_cs - cc[d];   // position in the cell, cell units
-      const double gap = off[d] > 0 ? 1.0 - u : (off[d] < 0 ? u : 0.0);
-      if (gap > 0.0) g2 += gap * gap;
-    }
-    skip = g2 * pa.cs2 > pa.rcut2 * (1.0 + 1e-9);
-  }
-  int first, pre, total;
-  nbr27_setup(lane, cc[0], cc[1], cc[2], nc, cell_start, first, pre, total, skip);
-  int pos = FILL ? start[t] : 0;
-  int count = 0;
-  for (int base = 0; base < total; base += 64) {
-    const int idx = base + lane;
-    const int s = nbr27_slot(idx, first, pre);
-    double d[3];
-    int j = -1;
-    bool ok = false;
-    if (idx < total) {
-      j = perm[s];
-      ok = j != i && near_pair(xw, xi0, xi1, xi2, j, pa, d);
-    }
-    if (!FILL) {
-      count += ok ? 1 : 0;
-    } else {
-      const unsigned long long m = __ballot(ok);
-      const int slot = pos + __popcll(m & ((1ull << lane) - 1ull));
-      if (ok && slot >= pa.cap) {
-        atomicOr(pa.status, (int)PSE_STATUS_PAIR_OVERFLOW);
-        ok = false;
-      }
-      if (ok) {
-        nbr[slot] = j;
-        if (rec64 || rec32) {
-          // the unit vector now, the distance in field d2 for
-          // pair_coef_kernel (the table interpolation runs there on every
-          // lane, not on the few lanes of a candidate batch that found a
-          // neighbour)
-          const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-          const double inv = r > 0 ? 1.0 / r : 0.0;
-          if (rec64) {
-            const Entry<double> p(rec64, slot);
-            p[F_D2] = r;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) p[F_E + k] = d[k] * inv;
-          } else {
-            const Entry<float> p(rec32, slot);
-            p[F_D2] = (float)r;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) p[F_E + k] = (float)(d[k] * inv);
-          }
-        }
-      }
-      pos += __popcll(m);
-    }
-  }
-  if (!FILL) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off, 64);
-    if (lane == 0) cnt[t] = count;
-  }
-}
-
-// The seven radial coefficients of every stored pair, interpolated from the
-// table at the distance the fill left in field d2 (entries up to the list's
-// length, read on the device, and its capacity).
-// In the records' precision, from the table of that precision.
-template <typename R>
-__global__ void __launch_bounds__(256)
-pair_coef_kernel(R *__restrict__ rec, const int *__restrict__ total, int64_t cap,
-                 const R *__restrict__ tab, double inv_dr, int n2a, int ntab) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t len = min((int64_t)total[0], cap);
-  if (s >= len) return;
-  R co[NCOEF];
-  const Entry<R> p(rec, (uint32_t)s);
-  lookup<R>(tab, p[F_D2], (R)inv_dr, n2a, ntab, co);
-  constexpr int field[NCOEF] = {F_A, F_B, F_C1, F_C2, F_D2, F_D3, F_D4};
-#pragma unroll
-  for (int k = 0; k < NCOEF; ++k) p[field[k]] = co[k];
 }
 
 struct RealArgs {
@@ -1100,193 +602,6 @@ es_pair_kernel(const double *__restrict__ xw, const double *__restrict__ in, Lay
   const T f = (T)-3 * tab[4] - tab[5];
   out[(size_t)i * ra.lout.stride + 6 - ra.lout.off + lane] =
       alpha * v + beta * (double)((T)-9 * (a + f * (T)v));
-}
-
-// Second half of the pair-list fill: the coefficients of the stored pairs
-// (grid over pl_pairs: the count in synchronous handles, the capacity in
-// asynchronous ones, whose kernel reads the count on the device).
-static void pair_coefficients(Handle &h) {
-  if (h.pl_pairs == 0 || (!h.pl_rec64 && !h.pl_rec32)) return;
-  const dim3 grid(nblocks(h.pl_pairs, 256)), block(256);
-  const int *total = h.pl_start + h.n;
-  if (h.pl_rec64)
-    hipLaunchKernelGGL(pair_coef_kernel<double>, grid, block, 0, h.stream, h.pl_rec64, total,
-                       (int64_t)h.pl_cap, (const double *)h.g64.table, 1.0 / h.dr, h.n2a,
-                       h.ntab);
-  else
-    hipLaunchKernelGGL(pair_coef_kernel<float>, grid, block, 0, h.stream, h.pl_rec32, total,
-                       (int64_t)h.pl_cap, (const float *)h.g32.table, 1.0 / h.dr, h.n2a,
-                       h.ntab);
-  PSE_LAUNCH_CHECK();
-}
-
-// Builds the pair list for the current cell list; grows its storage when
-// the count exceeds the capacity (one host read of the total per update).
-static void build_pair_list(Handle &h, const double *xw) {
-  PairArgs pa;
-  pa.n = h.n;
-  pa.nc = h.cells.nc;
-  pa.L = h.p.box;
-  pa.rcut2 = h.d.rcut * h.d.rcut;
-  // the cell assignment's own scale (cell = floor(x nc / L))
-  pa.inv_cs = pa.nc / h.p.box;
-  pa.cs2 = (h.p.box / pa.nc) * (h.p.box / pa.nc);
-  pa.inv_dr = 1.0 / h.dr;
-  pa.n2a = h.n2a;
-  pa.ntab = h.ntab;
-  pa.cap = (int64_t)h.pl_cap;
-  pa.status = h.dctl + CTL_STATUS;
-  pa.def = h.def.on;
-  for (int i = 0; i < 9; ++i) pa.A[i] = h.def.A[i];
-  const unsigned nb = nblocks((size_t)h.n * 64, 256);
-  hipLaunchKernelGGL((pair_list_kernel<false>), dim3(nb), dim3(256), 0, h.stream, xw,
-                     h.cells.perm, h.cells.start, h.cells.slot, pa, h.pl_cnt, nullptr, nullptr,
-                     nullptr, nullptr, nullptr);
-  PSE_LAUNCH_CHECK();
-  const int n = (int)h.n;
-  exclusive_scan(h, h.pl_cnt, h.pl_start, h.pl_scan, n);
-  if (h.async) {
-    // no host read: the list keeps its capacity, pairs beyond it are dropped
-    // and flagged in the device status (non-finite positions are flagged by
-    // the wrap kernel)
-    h.pl_pairs = h.pl_cap;
-    hipLaunchKernelGGL((pair_list_kernel<true>), dim3(nb), dim3(256), 0, h.stream, xw,
-                       h.cells.perm, h.cells.start, h.cells.slot, pa, nullptr, h.pl_start,
-                       h.g64.table, h.pl_nbr, h.pl_rec64, h.pl_rec32);
-    PSE_LAUNCH_CHECK();
-    pair_coefficients(h);
-    return;
-  }
-  int total = 0, bad = 0;
-  PSE_HIP(hipMemcpyAsync(&total, h.pl_start + n, sizeof(int), hipMemcpyDeviceToHost,
-                         h.stream));
-  PSE_HIP(hipMemcpyAsync(&bad, h.bad_pos, sizeof(int), hipMemcpyDeviceToHost, h.stream));
-  PSE_HIP(hipStreamSynchronize(h.stream));
-  if (bad) throw Error{PSE_ERR_NONFINITE, "non-finite particle position"};
-  if ((size_t)total > h.pl_cap) {
-    if (h.arena)
-      throw Error{PSE_ERR_NOMEM, "real-space pair list beyond its capacity in the "
-                                 "allocation-free product (" + std::to_string(total) +
-                                 " pairs)"};
-    clear_graphs(h);   // captured real-space launches hold the old buffers
-    const size_t cap = (size_t)total + total / 4 + 1024;
-    pair_storage(h, cap, false);
-    pa.cap = (int64_t)h.pl_cap;
-  }
-  h.pl_pairs = (size_t)total;
-  hipLaunchKernelGGL((pair_list_kernel<true>), dim3(nb), dim3(256), 0, h.stream, xw,
-                     h.cells.perm, h.cells.start, h.cells.slot, pa, nullptr, h.pl_start,
-                     h.g64.table, h.pl_nbr, h.pl_rec64, h.pl_rec32);
-  PSE_LAUNCH_CHECK();
-  pair_coefficients(h);
-}
-
-void pair_storage(Handle &h, size_t cap, bool at_create) {
-  if (!at_create) {
-    dev_free(h.pl_nbr);
-    dev_free(h.pl_rec64);
-    dev_free(h.pl_rec32);
-    h.pl_nbr = nullptr;
-    h.pl_rec64 = nullptr;
-    h.pl_rec32 = nullptr;
-    h.pl_cap = 0;
-  }
-  const auto alloc = [&](void **ptr, size_t bytes) {
-    if (at_create) handle_alloc(h, ptr, bytes);
-    else dev_alloc(ptr, bytes);
-  };
-  cap = (cap + REC_BLOCK - 1) / REC_BLOCK * REC_BLOCK;   // whole blocks
-  alloc((void **)&h.pl_nbr, cap * sizeof(int));
-  if (h.mixed) alloc((void **)&h.pl_rec32, cap * PAIR_REC * sizeof(float));
-  else alloc((void **)&h.pl_rec64, cap * PAIR_REC * sizeof(double));
-  h.pl_cap = cap;
-}
-
-// The library's own order of the particles for one call: the caller's
-// positions x are wrapped, binned into the real-space cells and put in cell
-// order, xw[t] = wrapped x[order[t]].  Every particle vector of the call is
-// kept in this order (gather_rows on the way in, scatter_rows on the way
-// out), so neighbours' data lie next to each other whatever the caller's
-// order: the pair sums gather moments, the list builders positions and the
-// grid kernels weights and moments from near addresses (a caller's random
-// order made each gather a line of its own).  N = 10^6 in random order: the
-// constraint operator's pair sum 349 -> 276 us, the full one 564 -> 468, the
-// list's counting pass 846 -> 704, gradient interpolation 2.02 -> 1.89 ms.
-void sort_positions(Handle &h, const double *x) {
-  double *xu = h.xh;   // wrapped, in the caller's order: the mid-point's buffer
-  wrap_positions(h, x, xu);
-  build_bins(h, xu, h.cells, h.xw);
-}
-
-// Lists of the wrapped positions xw whose cells are current: the spreading
-// bins and tile lists (unless spreading is false) and the pair list.
-static void build_lists(Handle &h, const double *xw, bool spreading) {
-  const bool tiles = h.stile && spreading;
-  if (tiles) {
-    build_bins(h, xw, h.sbins);
-    build_tile_lists(h, xw);
-  }
-  if (h.stile) build_dg_mu(h, xw);
-  h.tiles_current = tiles;
-  build_pair_list(h, xw);
-}
-
-static double cells_bytes(const Handle &h, bool spreading) {
-  const bool tiles = h.stile && spreading;
-  const double nc3 = (double)h.cells.nc * h.cells.nc * h.cells.nc
-                     + (tiles ? (double)h.sbins.nc * h.sbins.nc * h.sbins.nc : 0.0);
-  return (double)h.n * (24 + 16) * (tiles ? 2 : 1) + 12.0 * nc3;
-}
-
-void prepare_positions(Handle &h, const double *x, bool spreading) {
-  ProfScope ps(h, PK_CELLS, cells_bytes(h, spreading));
-  sort_positions(h, x);
-  build_lists(h, h.xw, spreading);
-}
-
-void build_cells(Handle &h, const double *xw, bool spreading) {
-  ProfScope ps(h, PK_CELLS, cells_bytes(h, spreading));
-  build_bins(h, xw, h.cells);
-  build_lists(h, xw, spreading);
-}
-
-// Rows of w numbers between the caller's order and the library's.
-__global__ void __launch_bounds__(256)
-gather_rows_kernel(const double *__restrict__ src, const int *__restrict__ order, int w,
-                   int64_t nw, double *__restrict__ dst) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nw) return;
-  const int64_t t = i / w;
-  dst[i] = src[(int64_t)order[t] * w + (i - t * w)];
-}
-
-// The components [lo, hi) of the rows; *bad is raised (bad not NULL) by a
-// non-finite number in any component of the rows as they are left.
-__global__ void __launch_bounds__(256)
-scatter_rows_kernel(const double *__restrict__ src, const int *__restrict__ order, int w, int lo,
-                    int hi, int64_t nw, double *__restrict__ dst, int *__restrict__ bad) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nw) return;
-  const int64_t t = i / w;
-  const int c = (int)(i - t * w);
-  double *o = dst + (int64_t)order[t] * w + c;
-  double v;
-  if (c >= lo && c < hi) *o = v = src[i];
-  else if (bad) v = *o;
-  else return;
-  if (bad && !isfinite(v)) *bad = 1;
-}
-
-void gather_rows(Handle &h, const double *src, int w, double *dst) {
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(nblocks((size_t)h.n * w, 256)), dim3(256), 0,
-                     h.stream, src, (const int *)h.order, w, h.n * w, dst);
-  PSE_LAUNCH_CHECK();
-}
-
-void scatter_rows(Handle &h, const double *src, int w, int lo, int hi, double *dst, int *bad) {
-  hipLaunchKernelGGL(scatter_rows_kernel, dim3(nblocks((size_t)h.n * w, 256)), dim3(256), 0,
-                     h.stream, src, (const int *)h.order, w, lo, hi, h.n * w, dst, bad);
-  PSE_LAUNCH_CHECK();
 }
 
 static int mask_of(const CompSet &cs) {
