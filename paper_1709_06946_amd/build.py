@@ -18,8 +18,8 @@ PACK_LIB = os.path.join(HERE, 'libpack.so')
 HIPCC = os.environ.get('HIPCC', '/opt/rocm/bin/hipcc')
 ARCH = 'gfx950'
 
-SOURCES = ['params.cpp', 'serve.cpp', 'fft.hip', 'grid.hip', 'lists.hip', 'real.hip',
-           'krylov.hip', 'api.hip']
+SOURCES = ['params.cpp', 'serve.cpp', 'fft.hip', 'grid.hip', 'interp.hip', 'lists.hip',
+           'real.hip', 'krylov.hip', 'api.hip']
 
 FLAGS = ['-O3', '-std=c++17', '-fPIC', f'--offload-arch={ARCH}',
          '-Xclang', '-target-feature', '-Xclang', '-packed-fp32-ops',

@@ -775,6 +775,8 @@ static void create(const pse_params &p, Handle &h) {
     handle_alloc(h, (void **)&h.tl_scan, ((ntile + 1023) / 1024 + 8) * sizeof(int));
     h.tl_cap = n * tiles_per_particle(h.d.support, h.stile);
     handle_alloc(h, (void **)&h.tl_rec, h.tl_cap * sizeof(TileRec));
+  }
+  if (!h.def.on) {
     const size_t entries = 3 * n * (size_t)weight_row(h.d.support, h.stile) * (h.deriv ? 2 : 1);
     handle_alloc(h, (void **)&h.wt64, entries * sizeof(double));
     if (h.mixed) handle_alloc(h, (void **)&h.wt32, entries * sizeof(float));
@@ -786,7 +788,6 @@ static void create(const pse_params &p, Handle &h) {
   // length): twice the capacity up front
   h.pl_cap = (h.async ? 2 : 1) * pair_capacity(h.p, h.d);
   pair_storage(h, h.pl_cap, true);
-  if (h.deriv) handle_alloc(h, (void **)&h.dg_mu, 6 * n * sizeof(double));
   handle_alloc(h, (void **)&h.mpack, 12 * n * sizeof(double));
   for (Bins *b : {&h.cells, &h.sbins}) {
     if (b->nc == 0) continue;
@@ -846,7 +847,7 @@ static void release(Handle &h) {
                   h.es_d, h.es_p, h.lz_V, h.gm_V, h.small, h.dots, h.ktab, h.pl_cnt,
                   h.pl_start, h.pl_scan, h.pl_nbr, h.pl_rec64, h.pl_rec32, h.tl_cnt, h.tl_start,
                   h.tl_scan, h.tl_rec, h.wt64, h.wt32, h.ktab32, h.dctl, h.dstats, h.dstep,
-                  h.dg_mu, h.mpack, h.kdg, h.kdg32};
+                  h.mpack, h.kdg, h.kdg32};
   if (!h.arena)
     for (void *p : ptrs) dev_free(p);
   host_free(h.kry);

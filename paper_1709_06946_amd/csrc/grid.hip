@@ -289,75 +289,15 @@ spread_deriv_kernel(const double *__restrict__ q, Layout lq, int iL, int iS, int
 
 // --------------------------------------------------------- interpolation --
 
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, l);
-  const long long hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double((hi << 32) | lo);
-}
-
-// Any support: lane l holds the one-dimensional factors exp(-kcoef d^2) at
-// offset l along x, y and z (meaningful for l < P); stencil point (a, b, c)
-// takes the product of the three, fetched from lanes a, b and c.  Every lane
-// of the wavefront must call it and the shuffles (all lanes active).
-__device__ __forceinline__ void factors1d(int lane, double px, double py, double pz, int ix0,
-                                          int iy0, int iz0, const GridGeom &g, double f[3]) {
-  const double dx = (ix0 + lane) * g.h - px, dy = (iy0 + lane) * g.h - py;
-  const double dz = (iz0 + lane) * g.h - pz;
-  f[0] = exp(-g.kcoef * dx * dx);
-  f[1] = exp(-g.kcoef * dy * dy);
-  f[2] = exp(-g.kcoef * dz * dz);
-}
-
-__device__ __forceinline__ double gauss_at(const double f[3], int a, int b, int c) {
-  return __shfl(f[0], a & 63, 64) * __shfl(f[1], b & 63, 64) * __shfl(f[2], c & 63, 64);
-}
-
-// Support 8 (512 stencil points, 8 per lane): lane l covers the points
-// (a, b) = (l % 8, l / 8) at every z index c, its point it being c = it.
-// The Gaussian factorises, so a lane takes one exponential for its x-y
-// factor and one for the z factor of c = l % 8; the z factor of point it is
-// read from lane it.  Fills the grid offsets (within one grid: below 2^31
-// for every supported length) and exp(-kcoef |d|^2) of the lane's eight
-// points, and their offsets d along z (x and y are dx, dy); the weights and
-// z offsets in the kernel's type T (FP32 kernels keep half the registers).
-__device__ __forceinline__ float readlane_t(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ double readlane_t(double v, int l) { return readlane_d(v, l); }
-
+// Deformed lattices, where the Gaussian does not factorise over the lattice
+// axes: one wavefront per particle, lane s covering stencil points s, s + 64,
+// ... (interp.hip has the cube's kernels).
 template <typename T>
-__device__ __forceinline__ void stencil8(int lane, double px, double py, double pz, int ix0,
-                                         int iy0, int iz0, const GridGeom &g, uint32_t gi[8],
-                                         T e[8], T dz[8], double &dx, double &dy) {
-  const int a = lane & 7, b = lane >> 3;
-  dx = (ix0 + a) * g.h - px;
-  dy = (iy0 + b) * g.h - py;
-  const T exy = (T)exp(-g.kcoef * (dx * dx + dy * dy));
-  const double dzl = (iz0 + a) * g.h - pz;
-  const T ezl = (T)exp(-g.kcoef * dzl * dzl);
-  const uint32_t gxy = (uint32_t)wrapi(iy0 + b, g.ng) * g.ng + wrapi(ix0 + a, g.ng);
-#pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    dz[it] = (T)((iz0 + it) * g.h - pz);
-    e[it] = exy * readlane_t(ezl, it);
-    gi[it] = (uint32_t)wrapi(iz0 + it, g.ng) * g.ng * g.ng + gxy;
-  }
-}
-
-// One wavefront per particle (particles in cell order, each XCD taking a
-// contiguous range of them so that neighbouring stencils share its L2);
-// lane s covers stencil points s, s + 64, ...
-// With MAXIT = ceil(P^3 / 64) fixed at compile time, a lane first forms all
-// its grid indices and weights and then issues every grid load at once, so
-// that the loads of all stencil points and components are in flight
-// together (MAXIT = 0: generic loop for large supports).
-template <typename T, int MAXIT>
 __global__ void __launch_bounds__(256)
-interp_kernel(const double *__restrict__ x, const T *__restrict__ grids,
-              size_t ngrid, CompSet cs, GridGeom g, const int *__restrict__ order,
-              int64_t n, double *__restrict__ out, Layout lo, int accumulate,
-              double scale) {
+interp_deformed_kernel(const double *__restrict__ x, const T *__restrict__ grids,
+                       size_t ngrid, CompSet cs, GridGeom g, const int *__restrict__ order,
+                       int64_t n, double *__restrict__ out, Layout lo, int accumulate,
+                       double scale) {
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
   if (t >= n) return;
@@ -371,60 +311,17 @@ interp_kernel(const double *__restrict__ x, const T *__restrict__ grids,
 #pragma unroll
   for (int k = 0; k < NC; ++k) acc[k] = (T)0;
   const double kn3 = g.knorm * g.knorm * g.knorm;
-  if constexpr (MAXIT > 0) {
-    uint32_t gi[MAXIT];
-    T w[MAXIT];
-    bool done = false;
-    if constexpr (MAXIT == 8) {
-      if (P == 8) {
-        T e[8], dz[8];
-        double dx, dy;
-        stencil8<T>(lane, px, py, pz, ix0, iy0, iz0, g, gi, e, dz, dx, dy);
+  for (int s = lane; s < P3; s += 64) {
+    const int a = s % P, b = (s / P) % P, c = s / (P * P);
+    const double dx = (ix0 + a) * g.h - px;
+    const double dy = (iy0 + b) * g.h - py;
+    const double dz = (iz0 + c) * g.h - pz;
+    const T w = (T)(kn3 * exp(-g.kcoef * qform(g.G, dx, dy, dz)));
+    const size_t gi = ((size_t)wrapi(iz0 + c, g.ng) * g.ng + wrapi(iy0 + b, g.ng)) * g.ng
+                      + wrapi(ix0 + a, g.ng);
 #pragma unroll
-        for (int it = 0; it < 8; ++it) w[it] = (T)kn3 * e[it];
-        done = true;
-      }
-    }
-    if (!done) {
-      double f[3];
-      factors1d(lane, px, py, pz, ix0, iy0, iz0, g, f);
-#pragma unroll
-      for (int it = 0; it < MAXIT; ++it) {
-        const int s = lane + 64 * it;
-        const int a = s % P, b = (s / P) % P, c = s / (P * P);
-        const bool in = s < P3;
-        const double e = gauss_at(f, a, b, c);
-        w[it] = in ? (T)(kn3 * e) : (T)0;
-        gi[it] = in ? ((uint32_t)wrapi(iz0 + c, g.ng) * g.ng + wrapi(iy0 + b, g.ng)) * g.ng
-                          + wrapi(ix0 + a, g.ng)
-                    : 0;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      if (k < cs.n) {
-        const T *gk = grids + (size_t)k * ngrid;
-        T v[MAXIT];
-#pragma unroll
-        for (int it = 0; it < MAXIT; ++it) v[it] = gk[gi[it]];
-#pragma unroll
-        for (int it = 0; it < MAXIT; ++it) acc[k] += w[it] * v[it];
-      }
-    }
-  } else {
-    for (int s = lane; s < P3; s += 64) {
-      const int a = s % P, b = (s / P) % P, c = s / (P * P);
-      const double dx = (ix0 + a) * g.h - px;
-      const double dy = (iy0 + b) * g.h - py;
-      const double dz = (iz0 + c) * g.h - pz;
-      const double r2 = g.def ? qform(g.G, dx, dy, dz) : dx * dx + dy * dy + dz * dz;
-      const T w = (T)(kn3 * exp(-g.kcoef * r2));
-      const size_t gi = ((size_t)wrapi(iz0 + c, g.ng) * g.ng + wrapi(iy0 + b, g.ng)) * g.ng
-                        + wrapi(ix0 + a, g.ng);
-#pragma unroll
-      for (int k = 0; k < NC; ++k)
-        if (k < cs.n) acc[k] += w * grids[(size_t)k * ngrid + gi];
-    }
+    for (int k = 0; k < NC; ++k)
+      if (k < cs.n) acc[k] += w * grids[(size_t)k * ngrid + gi];
   }
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
@@ -1287,180 +1184,6 @@ template <typename F> void with_ncm(int n, F f) {
 
 }  // namespace
 
-// Rotation and strain from derivative gridding: with v = the three velocity
-// grids of the k-space factor 3 f1(ka) u^, and the sums
-// G_ij = sum_n v_i(x_n) dK/dx_j (x_n - x_p) = -(d v_i / d x_j)(x_p) (the
-// interpolation of grad v with the gradient moved onto the Gaussian), the
-// strain is e_q = Y_q : grad v and the rotation curl v / 2 (the adjoints of
-// the stresslet and torque columns).  With HU the three grids of j0(ka) u^
-// come first and give the velocity by plain interpolation.  One wavefront
-// per particle as interp_kernel; per stencil point the gradient weight is
-// lambda (-2 kcoef d - mu) K(d), d = x_n - x_p, with the moment corrections
-// mu, lambda of the particle (see weight_rows).  cs: the output components (velocity 0-2
-// with HU, rotation 3-5, strain 6-10), any subset.
-template <typename T, int MAXIT, bool HU>
-__global__ void __launch_bounds__(256)
-interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids, size_t ngrid,
-                    CompSet cs, int rot, GridGeom g, const int *__restrict__ order, int64_t n,
-                    const double *__restrict__ mu, double *__restrict__ out, Layout lo,
-                    int accumulate, double scale) {
-  const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-  if (t >= n) return;
-  const int64_t p = order ? order[t] : t;
-  const double px = x[3 * p], py = x[3 * p + 1], pz = x[3 * p + 2];
-  const int P = g.P, P3 = P * P * P;
-  const int ix0 = stencil_start(px, g.h, P);
-  const int iy0 = stencil_start(py, g.h, P);
-  const int iz0 = stencil_start(pz, g.h, P);
-  const double kn3 = g.knorm * g.knorm * g.knorm;
-  const double mx = mu[6 * p], my = mu[6 * p + 1], mz = mu[6 * p + 2];
-  const double lx = mu[6 * p + 3], ly = mu[6 * p + 4], lz = mu[6 * p + 5];
-  const T *vg = grids + (HU ? 3 * ngrid : 0);
-  // G (row-major, 9) and the velocity (3)
-  T acc[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = (T)0;
-  bool done = false;
-  if constexpr (MAXIT == 8) {
-    if (P == 8) {
-      // the lane's points share x and y: with dK/dx_i = c d_i e (c = -2
-      // kcoef knorm^3, e the Gaussian), the column sums s_k = sum v_k e and
-      // z_k = sum v_k e dz give every G_ij
-      uint32_t gi[8];
-      T e[8], dz[8];
-      double dx, dy;
-      stencil8<T>(lane, px, py, pz, ix0, iy0, iz0, g, gi, e, dz, dx, dy);
-      T v[3][8], u[HU ? 3 : 1][8];
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int it = 0; it < 8; ++it) v[k][it] = vg[(size_t)k * ngrid + gi[it]];
-      if constexpr (HU)
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-          for (int it = 0; it < 8; ++it) u[k][it] = grids[(size_t)k * ngrid + gi[it]];
-      // moment correction: lambda_i (dK/dx_i - mu_i K) = lambda_i c (d_i - mu_i / (-2 kcoef)) e
-      T sk[3] = {(T)0, (T)0, (T)0}, zk[3] = {(T)0, (T)0, (T)0}, uk[3] = {(T)0, (T)0, (T)0};
-      const double sh = 1.0 / (-2.0 * g.kcoef);
-      dx -= mx * sh;
-      dy -= my * sh;
-      const T mzs = (T)(mz * sh);
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const T et = e[it], dzt = dz[it] - mzs;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const T ve = v[k][it] * et;
-          sk[k] += ve;
-          zk[k] += ve * dzt;
-          if constexpr (HU) uk[k] += u[k][it] * et;
-        }
-      }
-      const double c = -2.0 * g.kcoef * kn3;
-      const T c0 = (T)(c * lz), cx = (T)(c * lx * dx), cy = (T)(c * ly * dy);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        acc[3 * k] = cx * sk[k];
-        acc[3 * k + 1] = cy * sk[k];
-        acc[3 * k + 2] = c0 * zk[k];
-        if constexpr (HU) acc[9 + k] = (T)kn3 * uk[k];
-      }
-      done = true;
-    }
-  }
-  if (!done) {
-    uint32_t gi[MAXIT];
-    T gw[MAXIT][3], w0[MAXIT];
-    double f1[3];
-    factors1d(lane, px, py, pz, ix0, iy0, iz0, g, f1);
-#pragma unroll
-    for (int it = 0; it < MAXIT; ++it) {
-      const int s = lane + 64 * it;
-      const int a = s % P, b = (s / P) % P, c = s / (P * P);
-      const double dx = (ix0 + a) * g.h - px;
-      const double dy = (iy0 + b) * g.h - py;
-      const double dz = (iz0 + c) * g.h - pz;
-      const bool in = s < P3;
-      const double e = gauss_at(f1, a, b, c);
-      const double f = in ? kn3 * e : 0.0;
-      gw[it][0] = (T)(f * lx * (-2.0 * g.kcoef * dx - mx));
-      gw[it][1] = (T)(f * ly * (-2.0 * g.kcoef * dy - my));
-      gw[it][2] = (T)(f * lz * (-2.0 * g.kcoef * dz - mz));
-      w0[it] = (T)f;
-      gi[it] = in ? ((uint32_t)wrapi(iz0 + c, g.ng) * g.ng + wrapi(iy0 + b, g.ng)) * g.ng
-                        + wrapi(ix0 + a, g.ng)
-                  : 0;
-    }
-    T v[3][MAXIT];
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int it = 0; it < MAXIT; ++it) v[k][it] = vg[(size_t)k * ngrid + gi[it]];
-#pragma unroll
-    for (int it = 0; it < MAXIT; ++it)
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) acc[3 * k + j] += v[k][it] * gw[it][j];
-    if constexpr (HU) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        T u[MAXIT];
-#pragma unroll
-        for (int it = 0; it < MAXIT; ++it) u[it] = grids[(size_t)k * ngrid + gi[it]];
-#pragma unroll
-        for (int it = 0; it < MAXIT; ++it) acc[9 + k] += w0[it] * u[it];
-      }
-    }
-  }
-  // wavefront sums: the symmetric part always, the antisymmetric part for a
-  // rotation, the velocity with HU
-  T r[12];
-  r[0] = acc[0];                 // Gxx
-  r[1] = acc[4];                 // Gyy
-  r[2] = acc[8];                 // Gzz
-  r[3] = acc[1] + acc[3];        // Gxy + Gyx
-  r[4] = acc[2] + acc[6];        // Gxz + Gzx
-  r[5] = acc[5] + acc[7];        // Gyz + Gzy
-  r[6] = acc[7] - acc[5];        // Gzy - Gyz
-  r[7] = acc[2] - acc[6];        // Gxz - Gzx
-  r[8] = acc[3] - acc[1];        // Gyx - Gxy
-  r[9] = acc[9];
-  r[10] = acc[10];
-  r[11] = acc[11];
-  const int nr = HU ? 12 : (rot ? 9 : 6);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    if (k < nr) {
-      T w = r[k];
-      for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off, 64);
-      r[k] = w;
-    }
-  }
-  if (lane == 0) {
-    const double r2 = 0.70710678118654752440, r6 = 0.40824829046386301637;
-    for (int k = 0; k < cs.n; ++k) {
-      const int c = cs.idx[k];
-      double val;
-      if (c < 3) val = (double)r[9 + c];
-      else if (c < 6) val = -0.5 * (double)r[3 + c];   // rotation: -(G_ji - G_ij) / 2
-      else if (c < 9) val = -r2 * (double)r[c - 3];
-      else if (c == 9) val = -r2 * ((double)r[0] - (double)r[1]);
-      else val = -r6 * ((double)r[0] + (double)r[1] - 2.0 * (double)r[2]);
-      double *o = out + p * lo.stride + c - lo.off;
-      val *= scale;
-      *o = accumulate ? *o + val : val;
-    }
-  }
-}
-
-template <typename T> static const T *weights(const Handle &h) {
-  if constexpr (sizeof(T) == 8) return h.wt64;
-  else return h.wt32;
-}
-
 // Workgroups of the tile kernels: four wavefronts each, `parts` per tile.
 static dim3 tile_blocks(const Handle &h, int parts) {
   const size_t nb = (size_t)h.sbins.nc;
@@ -1518,35 +1241,12 @@ void spread(Handle &h, const double *x, const double *q, Layout lq, const CompSe
 }
 
 template <typename T>
-void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
-                 Layout lo, bool accumulate, double scale) {
-  const GridGeom g = geom(h);
-  const int acc = accumulate ? 1 : 0;
+void interp_deformed(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
+                     Layout lo, bool accumulate, double scale) {
   ProfScope ps(h, PK_INTERP, (double)cs.n * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
-  const int P3 = g.P * g.P * g.P;
-  const dim3 grid(nblocks(h.n, 4)), block(256);
-  const int *order = (const int *)h.cells.trav;
-  if (g.def)   // the Gaussian does not factorise over the lattice axes
-    hipLaunchKernelGGL((interp_kernel<T, 0>), grid, block, 0, h.stream, x, grids, h.ngrid, cs, g,
-                       order, h.n, out, lo, acc, scale);
-  else if (P3 <= 128)
-    hipLaunchKernelGGL((interp_kernel<T, 2>), grid, block, 0, h.stream, x, grids, h.ngrid, cs, g,
-                       order, h.n, out, lo, acc, scale);
-  else if (P3 <= 256)
-    hipLaunchKernelGGL((interp_kernel<T, 4>), grid, block, 0, h.stream, x, grids, h.ngrid, cs, g,
-                       order, h.n, out, lo, acc, scale);
-  else if (P3 <= 384)
-    hipLaunchKernelGGL((interp_kernel<T, 6>), grid, block, 0, h.stream, x, grids, h.ngrid, cs, g,
-                       order, h.n, out, lo, acc, scale);
-  else if (P3 <= 512)
-    hipLaunchKernelGGL((interp_kernel<T, 8>), grid, block, 0, h.stream, x, grids, h.ngrid, cs, g,
-                       order, h.n, out, lo, acc, scale);
-  else if (P3 <= 1024)
-    hipLaunchKernelGGL((interp_kernel<T, 16>), grid, block, 0, h.stream, x, grids, h.ngrid, cs,
-                       g, order, h.n, out, lo, acc, scale);
-  else
-    hipLaunchKernelGGL((interp_kernel<T, 0>), grid, block, 0, h.stream, x, grids, h.ngrid, cs, g,
-                       order, h.n, out, lo, acc, scale);
+  hipLaunchKernelGGL(interp_deformed_kernel<T>, dim3(nblocks(h.n, 4)), dim3(256), 0, h.stream, x,
+                     grids, h.ngrid, cs, geom(h), (const int *)h.cells.trav, h.n, out, lo,
+                     accumulate ? 1 : 0, scale);
   PSE_LAUNCH_CHECK();
 }
 
@@ -1576,36 +1276,6 @@ void spread_deriv(Handle &h, const double *q, Layout lq, bool hasL, bool hasS, T
   if (hasL && hasS) tile(std::true_type(), std::true_type());
   else if (hasL) tile(std::true_type(), std::false_type());
   else tile(std::false_type(), std::true_type());
-  PSE_LAUNCH_CHECK();
-}
-
-// Velocity (with hu), rotation and strain components cs of out in layout lo
-// from the grids of derivative gridding (see interp_deriv_kernel).
-template <typename T>
-void interp_deriv(Handle &h, const double *x, const T *grids, bool hu, const CompSet &cs,
-                  double *out, Layout lo, bool accumulate, double scale) {
-  const GridGeom g = geom(h);
-  const int acc = accumulate ? 1 : 0;
-  int rot = 0;
-  for (int k = 0; k < cs.n; ++k) rot |= cs.idx[k] >= 3 && cs.idx[k] < 6;
-  ProfScope ps(h, PK_INTERP, (hu ? 6.0 : 3.0) * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
-  const int P3 = g.P * g.P * g.P;
-  const dim3 grid(nblocks(h.n, 4)), block(256);
-  const int *order = (const int *)h.cells.trav;
-  const auto launch = [&](auto maxit) {
-    constexpr int MI = decltype(maxit)::value;
-    if (hu)
-      hipLaunchKernelGGL((interp_deriv_kernel<T, MI, true>), grid, block, 0, h.stream, x, grids,
-                         h.ngrid, cs, rot, g, order, h.n, h.dg_mu, out, lo, acc, scale);
-    else
-      hipLaunchKernelGGL((interp_deriv_kernel<T, MI, false>), grid, block, 0, h.stream, x, grids,
-                         h.ngrid, cs, rot, g, order, h.n, h.dg_mu, out, lo, acc, scale);
-  };
-  if (P3 <= 256) launch(std::integral_constant<int, 4>());
-  else if (P3 <= 384) launch(std::integral_constant<int, 6>());
-  else if (P3 <= 512) launch(std::integral_constant<int, 8>());
-  else if (P3 <= 1024) launch(std::integral_constant<int, 16>());
-  else throw Error{PSE_ERR_INVALID, "derivative gridding supports P <= 10"};
   PSE_LAUNCH_CHECK();
 }
 
@@ -1745,8 +1415,8 @@ template <typename T> void to_double(Handle &h, const T *src, size_t n, double *
 #define INST(T)                                                                 \
   template void spread<T>(Handle &, const double *, const double *, Layout,      \
                           const CompSet &, T *);                                 \
-  template void interpolate<T>(Handle &, const double *, const T *,              \
-                               const CompSet &, double *, Layout, bool, double); \
+  template void interp_deformed<T>(Handle &, const double *, const T *,          \
+                                   const CompSet &, double *, Layout, bool, double); \
   template void kspace_deformed<T>(Handle &, const cplx<T> *, const CompSet &,   \
                                    cplx<T> *, const CompSet &);                  \
   template void kspace_noise<T>(Handle &, const double *, uint64_t, uint64_t,    \
@@ -1757,8 +1427,6 @@ template <typename T> void to_double(Handle &h, const T *src, size_t n, double *
                                 cplx<T> *, const CompSet &, const cplx<T> *,     \
                                 bool);                                           \
   template void spread_deriv<T>(Handle &, const double *, Layout, bool, bool, T *); \
-  template void interp_deriv<T>(Handle &, const double *, const T *, bool,       \
-                                const CompSet &, double *, Layout, bool, double); \
   template void zero_grids<T>(Handle &, T *, int);                               \
   template void from_double<T>(Handle &, const double *, size_t, T *);           \
   template void to_double<T>(Handle &, const T *, size_t, double *);

@@ -677,19 +677,18 @@ __device__ __forceinline__ void tile_rows(unsigned blk, const double *__restrict
 // lambda_d (g_i - mu_d w_i), still separable, whose discrete sum is zero and
 // whose first moment is -sum_i w_i: the gradient of a constant field is
 // zero and that of a linear field exact, relative to the Gaussian's own
-// normalisation.  mu and lambda (three each per particle) are formed once
-// per position update.
+// normalisation.
 //
-// The one-dimensional Gaussian weights themselves are kept per particle and
-// axis for the spreading kernels: rows of rw = P + 2 (S - 1) entries, the P
-// weights with S - 1 zeros on either side, so that any tile that a stencil
-// meets reads its S weights as one window of the row; an entry is the weight,
-// or with derivative gridding the weight and the corrected gradient weight.
+// The one-dimensional weights are kept per particle and axis, formed once per
+// position update, for spreading and interpolation: rows of rw = P + 2 (S - 1)
+// entries, the P weights with S - 1 zeros on either side, so that any tile
+// that a stencil meets reads its S weights as one window of the row (grids
+// without tiles: no zeros); an entry is the weight, or with derivative
+// gridding the weight and the corrected gradient weight.
 struct WeightArgs {
   GridGeom g;
   int64_t n;
   int pad, rw;        // S - 1 zeros; entries of a row
-  double *mu;         // moment corrections (derivative gridding), or NULL
   double *w64;        // rows in each precision, or NULL
   float *w32;
 };
@@ -726,14 +725,10 @@ __device__ __forceinline__ void weight_rows(unsigned blk, const double *__restri
     if constexpr (DERIV) {
       // sum_i d_i (g_i - m w_i) = sd1 - m sd
       const double m = s1 / s0, lam = -s0 / (sd1 - m * sd);
-      const int64_t p = t / 3, ax = t % 3;
-      wa.mu[6 * p + ax] = m;
-      wa.mu[6 * p + 3 + ax] = lam;
       rowd[W_THREADS + tid] = m;
       rowd[2 * W_THREADS + tid] = lam;
     }
   }
-  if (!wa.w64 && !wa.w32) return;
   __syncthreads();
   const size_t o0 = (size_t)t0 * wa.rw;
   int row = tid / wa.rw, e = tid % wa.rw;
@@ -845,14 +840,16 @@ static void build_lists(Handle &h, const double *xw, bool spreading) {
   WeightArgs wa{};
   wa.g = ta.g;
   wa.n = h.n;
-  wa.pad = h.stile - 1;
+  wa.pad = weight_pad(h.stile);
   wa.rw = weight_row(h.d.support, h.stile);
-  wa.mu = h.dg_mu;
-  wa.w64 = tiles ? h.wt64 : nullptr;
-  wa.w32 = tiles ? h.wt32 : nullptr;
+  // (without spreading only the noise is interpolated, in a mixed handle from
+  // its FP32 grids)
+  h.rows64_current = !h.def.on && (spreading || !h.mixed);
+  wa.w64 = h.rows64_current ? h.wt64 : nullptr;
+  wa.w32 = h.wt32;
   // the coefficients' workgroups walk the list (its length is on the device)
   const unsigned nbc = std::min(nblocks(h.pl_cap, W_THREADS), (unsigned)h.num_cu * 32u);
-  const unsigned nbw = (tiles || h.deriv) ? nblocks(3 * (size_t)h.n, W_THREADS) : 0;
+  const unsigned nbw = h.def.on ? 0 : nblocks(3 * (size_t)h.n, W_THREADS);
   const size_t lds = nbw ? (size_t)W_THREADS * (h.d.support + 3) * sizeof(double) : 0;
   const auto launch = [&](auto *rec, auto *tab, auto deriv) {
     using R = std::remove_reference_t<decltype(*rec)>;

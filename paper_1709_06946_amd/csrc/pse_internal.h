@@ -177,6 +177,7 @@ struct Handle {
   Bins sbins;
   int stile;                 // grid points per spreading tile side (0: atomics)
   bool tiles_current = false; // tile lists built at the last cell build's positions
+  bool rows64_current = false; // and the weight rows in FP64
   int max_lds = 65536;       // dynamic LDS a workgroup may use on this device
   int num_cu = 256;          // compute units of the device
 
@@ -201,7 +202,6 @@ struct Handle {
   // arena's; lists_open lists of the running call are not yet verified
   int *info = nullptr;
   int lists_open = 0;
-  double *dg_mu = nullptr;   // derivative gridding: moment corrections, 6 per particle
   void *mpack = nullptr;     // pair sums: moments packed 12 per particle (FP64 size)
   // real-space pair list (CSR in cell order): start[N+1], neighbour index and
   // 10 numbers of pair data per entry (doubles in FP64 handles, floats in
@@ -216,7 +216,7 @@ struct Handle {
   TileRec *tl_rec = nullptr;
   size_t tl_cap = 0;
   // one-dimensional Gaussian weights per particle and axis, in the precisions
-  // the handle spreads in (see weight_rows)
+  // the handle works in (see weight_rows); not on deformed lattices
   double *wt64 = nullptr;
   float *wt32 = nullptr;
 
@@ -365,6 +365,10 @@ void rfft_z(Handle &h, T *grids, const cplx<T> *twiddle, int ncomp, int dir);
 template <typename T>
 void spread(Handle &h, const double *x, const double *q, Layout lq, const CompSet &cs,
             T *grids);
+// interpolation on a deformed lattice (interpolate comes here)
+template <typename T>
+void interp_deformed(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
+                     Layout lo, bool accumulate, double scale);
 template <typename T>
 void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
                  Layout lo, bool accumulate, double scale);
@@ -423,8 +427,10 @@ inline size_t tiles_per_particle(int P, int S) {
   const size_t k = (size_t)((P - 1 + S - 1) / S + 1);
   return k * k * k;
 }
-// Entries of a weight row (P weights with S - 1 zeros on either side).
-inline int weight_row(int P, int S) { return P + 2 * (S - 1); }
+// Entries of a weight row: P weights with S - 1 zeros on either side (S = 0,
+// no tiles: none).
+inline int weight_pad(int S) { return S ? S - 1 : 0; }
+inline int weight_row(int P, int S) { return P + 2 * weight_pad(S); }
 // Spreading tile side: the stencil may reach one tile beyond its particle's
 // bin, with one grid point of slack for rounding in the bin assignment.
 inline int spread_tile(int grid, int P) {

@@ -33,4 +33,15 @@ inline GridGeom geom(const Handle &h) {
   return g;
 }
 
+// The particles' weight rows in the kernels' precision.
+template <typename T> inline const T *weights(const Handle &h) {
+  if constexpr (sizeof(T) == 8) {
+    if (!h.rows64_current)
+      throw Error{PSE_ERR_INVALID, "FP64 weight rows not built for these positions"};
+    return h.wt64;
+  } else {
+    return h.wt32;
+  }
+}
+
 }  // namespace pse
