@@ -775,8 +775,6 @@ static void create(const pse_params &p, Handle &h) {
     handle_alloc(h, (void **)&h.tl_scan, ((ntile + 1023) / 1024 + 8) * sizeof(int));
     h.tl_cap = n * tiles_per_particle(h.d.support, h.stile);
     handle_alloc(h, (void **)&h.tl_rec, h.tl_cap * sizeof(TileRec));
-  }
-  if (!h.def.on) {
     const size_t entries = 3 * n * (size_t)weight_row(h.d.support, h.stile) * (h.deriv ? 2 : 1);
     handle_alloc(h, (void **)&h.wt64, entries * sizeof(double));
     if (h.mixed) handle_alloc(h, (void **)&h.wt32, entries * sizeof(float));
@@ -788,7 +786,7 @@ static void create(const pse_params &p, Handle &h) {
   // length): twice the capacity up front
   h.pl_cap = (h.async ? 2 : 1) * pair_capacity(h.p, h.d);
   pair_storage(h, h.pl_cap, true);
-  handle_alloc(h, (void **)&h.mpack, 12 * n * sizeof(double));
+  if (h.n >= PACK_MIN) handle_alloc(h, (void **)&h.mpack, 12 * n * sizeof(double));
   for (Bins *b : {&h.cells, &h.sbins}) {
     if (b->nc == 0) continue;
     const size_t ncells = (size_t)b->nc * b->nc * b->nc;

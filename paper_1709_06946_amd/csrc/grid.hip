@@ -290,11 +290,12 @@ spread_deriv_kernel(const double *__restrict__ q, Layout lq, int iL, int iS, int
 // --------------------------------------------------------- interpolation --
 
 // Deformed lattices, where the Gaussian does not factorise over the lattice
-// axes: one wavefront per particle, lane s covering stencil points s, s + 64,
-// ... (interp.hip has the cube's kernels).
+// axes, and grids without spreading tiles, whose handles keep no weight rows:
+// one wavefront per particle, lane s covering stencil points s, s + 64, ...
+// (interp.hip has the others' kernels).
 template <typename T>
 __global__ void __launch_bounds__(256)
-interp_deformed_kernel(const double *__restrict__ x, const T *__restrict__ grids,
+interp_generic_kernel(const double *__restrict__ x, const T *__restrict__ grids,
                        size_t ngrid, CompSet cs, GridGeom g, const int *__restrict__ order,
                        int64_t n, double *__restrict__ out, Layout lo, int accumulate,
                        double scale) {
@@ -316,7 +317,8 @@ interp_deformed_kernel(const double *__restrict__ x, const T *__restrict__ grids
     const double dx = (ix0 + a) * g.h - px;
     const double dy = (iy0 + b) * g.h - py;
     const double dz = (iz0 + c) * g.h - pz;
-    const T w = (T)(kn3 * exp(-g.kcoef * qform(g.G, dx, dy, dz)));
+    const double r2 = g.def ? qform(g.G, dx, dy, dz) : dx * dx + dy * dy + dz * dz;
+    const T w = (T)(kn3 * exp(-g.kcoef * r2));
     const size_t gi = ((size_t)wrapi(iz0 + c, g.ng) * g.ng + wrapi(iy0 + b, g.ng)) * g.ng
                       + wrapi(ix0 + a, g.ng);
 #pragma unroll
@@ -1241,10 +1243,10 @@ void spread(Handle &h, const double *x, const double *q, Layout lq, const CompSe
 }
 
 template <typename T>
-void interp_deformed(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
+void interp_generic(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
                      Layout lo, bool accumulate, double scale) {
   ProfScope ps(h, PK_INTERP, (double)cs.n * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
-  hipLaunchKernelGGL(interp_deformed_kernel<T>, dim3(nblocks(h.n, 4)), dim3(256), 0, h.stream, x,
+  hipLaunchKernelGGL(interp_generic_kernel<T>, dim3(nblocks(h.n, 4)), dim3(256), 0, h.stream, x,
                      grids, h.ngrid, cs, geom(h), (const int *)h.cells.trav, h.n, out, lo,
                      accumulate ? 1 : 0, scale);
   PSE_LAUNCH_CHECK();
@@ -1415,8 +1417,8 @@ template <typename T> void to_double(Handle &h, const T *src, size_t n, double *
 #define INST(T)                                                                 \
   template void spread<T>(Handle &, const double *, const double *, Layout,      \
                           const CompSet &, T *);                                 \
-  template void interp_deformed<T>(Handle &, const double *, const T *,          \
-                                   const CompSet &, double *, Layout, bool, double); \
+  template void interp_generic<T>(Handle &, const double *, const T *,           \
+                                  const CompSet &, double *, Layout, bool, double); \
   template void kspace_deformed<T>(Handle &, const cplx<T> *, const CompSet &,   \
                                    cplx<T> *, const CompSet &);                  \
   template void kspace_noise<T>(Handle &, const double *, uint64_t, uint64_t,    \

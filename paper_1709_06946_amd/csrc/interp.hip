@@ -1,4 +1,4 @@
-// Interpolation from the grids to the particles (cubic lattices): the values
+// Interpolation from the grids to the particles (handles with spreading tiles): the values
 // of the velocity grids, and with derivative gridding the gradients of
 // v = 3 f1(ka) u^'s grids, weighted with the particles' weight rows.
 //
@@ -293,7 +293,7 @@ InterpArgs interp_args(const Handle &h, Layout lo, bool accumulate, double scale
   ia.ng = g.ng;
   ia.P = g.P;
   ia.rw = weight_row(g.P, h.stile);
-  ia.pad = weight_pad(h.stile);
+  ia.pad = h.stile - 1;
   ia.h = g.h;
   ia.ngrid = h.ngrid;
   ia.lo = lo;
@@ -330,8 +330,8 @@ template <typename F> void with_count(int n, F f) {
 template <typename T>
 void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
                  Layout lo, bool accumulate, double scale) {
-  if (h.def.on) {
-    interp_deformed<T>(h, x, grids, cs, out, lo, accumulate, scale);
+  if (!h.stile) {
+    interp_generic<T>(h, x, grids, cs, out, lo, accumulate, scale);
     return;
   }
   if (cs.n < 1) return;

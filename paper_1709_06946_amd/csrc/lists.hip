@@ -682,9 +682,9 @@ __device__ __forceinline__ void tile_rows(unsigned blk, const double *__restrict
 // The one-dimensional weights are kept per particle and axis, formed once per
 // position update, for spreading and interpolation: rows of rw = P + 2 (S - 1)
 // entries, the P weights with S - 1 zeros on either side, so that any tile
-// that a stencil meets reads its S weights as one window of the row (grids
-// without tiles: no zeros); an entry is the weight, or with derivative
-// gridding the weight and the corrected gradient weight.
+// that a stencil meets reads its S weights as one window of the row; an entry
+// is the weight, or with derivative gridding the weight and the corrected
+// gradient weight.
 struct WeightArgs {
   GridGeom g;
   int64_t n;
@@ -840,16 +840,16 @@ static void build_lists(Handle &h, const double *xw, bool spreading) {
   WeightArgs wa{};
   wa.g = ta.g;
   wa.n = h.n;
-  wa.pad = weight_pad(h.stile);
+  wa.pad = h.stile - 1;
   wa.rw = weight_row(h.d.support, h.stile);
   // (without spreading only the noise is interpolated, in a mixed handle from
   // its FP32 grids)
-  h.rows64_current = !h.def.on && (spreading || !h.mixed);
+  h.rows64_current = h.stile && (spreading || !h.mixed);
   wa.w64 = h.rows64_current ? h.wt64 : nullptr;
   wa.w32 = h.wt32;
   // the coefficients' workgroups walk the list (its length is on the device)
   const unsigned nbc = std::min(nblocks(h.pl_cap, W_THREADS), (unsigned)h.num_cu * 32u);
-  const unsigned nbw = h.def.on ? 0 : nblocks(3 * (size_t)h.n, W_THREADS);
+  const unsigned nbw = !h.stile ? 0 : nblocks(3 * (size_t)h.n, W_THREADS);
   const size_t lds = nbw ? (size_t)W_THREADS * (h.d.support + 3) * sizeof(double) : 0;
   const auto launch = [&](auto *rec, auto *tab, auto deriv) {
     using R = std::remove_reference_t<decltype(*rec)>;

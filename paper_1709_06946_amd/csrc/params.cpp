@@ -230,21 +230,19 @@ size_t footprint(const pse_params &p, const pse_derived &d) {
   const int S = spread_tile(d.grid, d.support);
   const size_t tiles3 = S ? ng3 / ((size_t)S * S * S) : 0;
   if (S) {
-    // tile CSR, one record per (tile, particle) pair
+    // tile CSR, one record per (tile, particle) pair, and the particles'
+    // weight rows (gradient weights too with derivative gridding; both
+    // precisions in mixed handles)
     const size_t cap = n * tiles_per_particle(d.support, S);
     bytes += (2 * tiles3 + tiles3 / 1024 + 16) * sizeof(int) + cap * sizeof(TileRec);
-  }
-  if (!lattice_deformed(p)) {
-    // the particles' weight rows (gradient weights too with derivative
-    // gridding; both precisions in mixed handles)
     bytes += 3 * n * (size_t)weight_row(d.support, S) * (d.deriv_gridding == 2 ? 2 : 1) *
              (sizeof(double) + (mixed ? sizeof(float) : 0));
   }
   bytes += (2 * (ncell3 + tiles3) + 4 + (ncell3 + tiles3) / 1024 + 16) * sizeof(int)
-           + 8 * n * sizeof(int);
+           + (S ? 8 : 4) * n * sizeof(int);
   bytes += n * sizeof(int);   // the library's order of the particles
   bytes += (2 * 3 * n + 6 * NC * n + 5 * 5 * n) * sizeof(double);
-  bytes += 12 * n * sizeof(double);   // packed moments of the pair sums
+  if (p.n >= PACK_MIN) bytes += 12 * n * sizeof(double);   // packed moments of the pair sums
   bytes += (size_t)(d.lanczos_maxit + 1) * NC * n * sizeof(double);
   bytes += (size_t)(d.gmres_restart + 1) * 5 * n * sizeof(double);
   const size_t small = 4 * (size_t)(d.gmres_restart + 2) * (d.gmres_restart + 2)

@@ -56,6 +56,9 @@ struct Layout {
 };
 constexpr Layout FULL_LAYOUT{NC, 0};
 
+// Particles from which the pair sums pack their moments (see real.hip).
+constexpr int64_t PACK_MIN = 32768;
+
 struct CompSet {
   int n;          // number of components
   int idx[NC];    // component indices into the 11-vector
@@ -216,7 +219,7 @@ struct Handle {
   TileRec *tl_rec = nullptr;
   size_t tl_cap = 0;
   // one-dimensional Gaussian weights per particle and axis, in the precisions
-  // the handle works in (see weight_rows); not on deformed lattices
+  // the handle works in (see weight_rows); with spreading tiles only
   double *wt64 = nullptr;
   float *wt32 = nullptr;
 
@@ -365,9 +368,9 @@ void rfft_z(Handle &h, T *grids, const cplx<T> *twiddle, int ncomp, int dir);
 template <typename T>
 void spread(Handle &h, const double *x, const double *q, Layout lq, const CompSet &cs,
             T *grids);
-// interpolation on a deformed lattice (interpolate comes here)
+// interpolation without weight rows (interpolate comes here)
 template <typename T>
-void interp_deformed(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
+void interp_generic(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
                      Layout lo, bool accumulate, double scale);
 template <typename T>
 void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
@@ -427,10 +430,8 @@ inline size_t tiles_per_particle(int P, int S) {
   const size_t k = (size_t)((P - 1 + S - 1) / S + 1);
   return k * k * k;
 }
-// Entries of a weight row: P weights with S - 1 zeros on either side (S = 0,
-// no tiles: none).
-inline int weight_pad(int S) { return S ? S - 1 : 0; }
-inline int weight_row(int P, int S) { return P + 2 * weight_pad(S); }
+// Entries of a weight row (P weights with S - 1 zeros on either side).
+inline int weight_row(int P, int S) { return P + 2 * (S - 1); }
 // Spreading tile side: the stencil may reach one tile beyond its particle's
 // bin, with one grid point of slack for rounding in the bin assignment.
 inline int spread_tile(int grid, int P) {
