@@ -332,11 +332,18 @@ __device__ __forceinline__ void tw_store(C *twl, C first, const C *__restrict__ 
   for (int i = (int)(threadIdx.x + blockDim.x); i < N; i += blockDim.x) twl[i] = tw[i];
 }
 
-// Element counts per thread: line passes and the fused k-space kernel (which
-// also keeps three complex numbers per element in registers, so it takes few
-// elements: 4 for powers of two, 6 (radices 6, 3, 2) for 3 * 2^k lengths).
+// Element counts per thread: line passes; the fused k-space kernel, which
+// also keeps three complex numbers per element in registers (FP64: four
+// elements for powers of two, six, radices 6, 3, 2, for 3 * 2^k lengths; FP32
+// twice as many); the one with the three couplet grids in registers.
 constexpr int line_e(int n) { return n % 3 == 0 ? 12 : (n >= 128 ? 16 : 8); }
-constexpr int fused_e(int n) { return n % 3 == 0 ? 6 : 4; }
+template <typename T> constexpr int fused_e(int n) {
+  const int e = n % 3 == 0 ? 6 : 4;
+  return sizeof(T) == 4 && n >= 48 ? 2 * e : e;
+}
+template <typename T> constexpr int dg3_e(int n) {
+  return n % 3 == 0 ? (sizeof(T) == 4 ? 12 : 6) : (sizeof(T) == 4 && n >= 512 ? 16 : 8);
+}
 
 // Lines per workgroup: a power of two dividing `count`, at most max_threads
 // threads (about 256 by default), LDS of tl * line_bytes within 64 KiB.

@@ -11,6 +11,7 @@
 // Fourier transform is exp(-eta_s k^2 / 8 xi^2).  Spreading and
 // interpolation each contribute that factor once; the k-space scaling
 // divides both out again.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -453,6 +454,32 @@ __device__ __forceinline__ void p_column(int c, R kx, R ky, R kz, R j0, R f1, bo
   }
 }
 
+// P_c as a linear form, P_c(k) = B + A k without its radial factor: B = e_c for
+// forces (real), A for couplets (times i; the column of p_column with f1 = 1).
+template <typename R> struct ColumnForm {
+  R A[3][3], B[3];
+  __device__ __forceinline__ explicit ColumnForm(int c) {
+    const R r2 = (R)(-3.0 * 0.70710678118654752440), r6 = (R)(-3.0 * 0.40824829046386301637);
+    const R a = (R)1.5;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) B[m] = c == m ? (R)1 : (R)0;
+    A[0][0] = c == 9 ? r2 : (c == 10 ? r6 : (R)0);
+    A[1][1] = c == 9 ? -r2 : (c == 10 ? r6 : (R)0);
+    A[2][2] = c == 10 ? (R)-2 * r6 : (R)0;
+    A[0][1] = c == 6 ? r2 : (c == 5 ? a : (R)0);
+    A[1][0] = c == 6 ? r2 : (c == 5 ? -a : (R)0);
+    A[0][2] = c == 7 ? r2 : (c == 4 ? -a : (R)0);
+    A[2][0] = c == 7 ? r2 : (c == 4 ? a : (R)0);
+    A[1][2] = c == 8 ? r2 : (c == 3 ? a : (R)0);
+    A[2][1] = c == 8 ? r2 : (c == 3 ? -a : (R)0);
+  }
+  // the part of a column that kx and ky give
+  __device__ __forceinline__ void fixed(R kx, R ky, R *o) const {
+#pragma unroll
+    for (int m = 0; m < 3; ++m) o[m] = B[m] + A[m][0] * kx + A[m][1] * ky;
+  }
+};
+
 // rho += P_c(k) g
 template <typename C, typename R>
 __device__ __forceinline__ void add_P(int c, C gv, const R *kv, R j0, R f1, C *rho) {
@@ -515,13 +542,29 @@ __device__ __forceinline__ bool zero_mode(int ix, int iy, int iz, int n) {
 // Gaussian's gradient (factor -3 f1(ka)) on input, so rho = j0 F^ - 3 f1 D^;
 // on output 0-2 the velocity grids j0(ka) u^ and 3-5 the grids
 // v^ = 3 f1(ka) u^ whose gradient the interpolation takes.
+// The radial factors j0 and f1 come out of the sums over components of one
+// kind (forces, couplets): with one kind on a side its factor is applied with
+// the projection's scale, once per mode; with both, the inputs' couplets come
+// first, the accumulator takes f1, and the forces follow with j0 each, and the
+// outputs' forces come first (KOrder).  With the factors out of the inner
+// loops and the columns as linear forms an FP32 thread has registers for
+// twice the modes, and a line takes half the exchanges.  Bound by the memory
+// and the exchanges' barriers: five components each way at 384^3 in FP32 1.31
+// -> 0.82 ms (1.8 -> 2.8 TB/s), six in and five out 1.52 -> 1.3 ms; at 128^3
+// in FP64, six in and three out, 44 -> 35 us.
+struct KOrder {
+  int n, both;             // both kinds present
+  int kind;                // else the kind: 0 forces, 1 couplets
+  int slot[NC], comp[NC];  // grid slots and their components
+};
+
 template <typename T, int N, bool DG>
 __global__ void __launch_bounds__(512)
-kspace_fused_kernel(const cplx<T> *__restrict__ in, CompSet cin, cplx<T> *__restrict__ out,
-                    CompSet cout, KGeom kg, const typename TabT<T>::type *__restrict__ ktab,
+kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restrict__ out,
+                    KOrder cout, KGeom kg, const typename TabT<T>::type *__restrict__ ktab,
                     const cplx<T> *__restrict__ tw, int TL) {
   using C = cplx<T>;
-  constexpr int E = fused_e(N), M = N / 2;
+  constexpr int E = fused_e<T>(N), M = N / 2;
   using S = Shape<N, E>;
   constexpr int R0 = S::first(false), RL = S::last(false);
   extern __shared__ unsigned char smem_raw[];
@@ -544,173 +587,173 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, CompSet cin, cplx<T> *__rest
   for (int e = 0; e < E; ++e)
 #pragma unroll
     for (int m = 0; m < 3; ++m) rho[e][m] = C{(T)0, (T)0};
-  // radial factors of this thread's modes: j0 (x), f1 (y) and the
-  // projection's scale (z).  With four modes per thread they are read from
-  // the table once for all components; with six the registers they would
-  // hold cost more than the repeated (cached) table reads.
-  constexpr bool HOIST = E <= 4;
+  // table entry of the thread's mode e
   const auto entry = [&](int e) {
-    const int iz = reg_pos<N, E, RL>(t, e / RL, e % RL);
-    const int kz = kidx(iz, N);
+    const int kz = kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
     return ktab[ix * ix + ky * ky + kz * kz];
   };
-  T tj0[HOIST ? E : 1], tf1[HOIST ? E : 1], tsc[HOIST ? E : 1];
-  if constexpr (HOIST) {
+  // factors of both kinds: where registers allow, read once and kept; else j0
+  // is read for a side's forces and f1 on the spot
+  constexpr bool KEEP = N % 3 != 0;
+  const bool both = cin.both || cout.both;
+  T j0[E], f1[KEEP ? E : 1];
+  const auto read_j0 = [&] {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const auto tb = entry(e);
-      tj0[e] = (T)tb.x;
-      tf1[e] = (T)tb.y;
-      tsc[e] = (T)tb.z;
-    }
-  }
-  // Without hoisting, FP32 kernels up to 384 points (BATCH) load the factors
-  // where nothing else is in flight that their use would wait for (the
-  // vector-memory counter is in order): in each input step before the next
-  // component's prefetch, and for the fold and the output steps once, before
-  // the first store; the others (registers) read them at each use.
-  constexpr bool BATCH = !HOIST && sizeof(T) == 4 && N <= 384;
-  // the next component's z-line is loaded while the current one is
-  // transformed (the barriers of the exchanges wait on LDS traffic only)
-  const C tw0 = tw_fetch<C, N>(tw);
-  C v[E], vn[E];
-#pragma unroll
-  for (int b = 0; b < E / R0; ++b)
-#pragma unroll
-    for (int r = 0; r < R0; ++r) vn[b * R0 + r] = in[base + reg_pos<N, E, R0>(t, b, r) * plane];
-  C *twl = lds + (size_t)TL * N;
-  tw_store<C, N>(twl, tw0, tw);
-  for (int p = 0; p < cin.n; ++p) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = vn[e];
-    T pj0[BATCH ? E : 1], pf1[BATCH ? E : 1];
-    if constexpr (BATCH) {
+    for (int e = 0; e < E; ++e) j0[e] = (T)entry(e).x;
+  };
+  if constexpr (KEEP)
+    if (both)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const auto tb = entry(e);
-        pj0[e] = (T)tb.x;
-        pf1[e] = (T)tb.y;
+        j0[e] = (T)tb.x;
+        f1[e] = (T)tb.y;
       }
-    }
-    const auto j0_at = [&](int e) -> T {
-      if constexpr (HOIST) return tj0[e];
-      else if constexpr (BATCH) return pj0[e];
-      else return (T)entry(e).x;
-    };
-    const auto f1_at = [&](int e) -> T {
-      if constexpr (HOIST) return tf1[e];
-      else if constexpr (BATCH) return pf1[e];
-      else return (T)entry(e).y;
-    };
-    if (p + 1 < cin.n) {
-      const C *src = in + (size_t)(p + 1) * hsz + base;
-#pragma unroll
-      for (int b = 0; b < E / R0; ++b)
-#pragma unroll
-        for (int r = 0; r < R0; ++r) vn[b * R0 + r] = src[reg_pos<N, E, R0>(t, b, r) * plane];
-    }
-    reg_fft_forward<T, N, E>(v, t, lds, TL, line, twl);
-    const int c = cin.idx[p];
-#pragma unroll
-    for (int b = 0; b < E / RL; ++b)
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int iz = reg_pos<N, E, RL>(t, b, r);
-        if (zero_mode(ix, iy, iz, N)) continue;
-        if constexpr (DG) {
-          const T f = c < 3 ? j0_at(b * RL + r) : (T)-3 * f1_at(b * RL + r);
-          const C vv = v[b * RL + r];
-#pragma unroll
-          for (int m = 0; m < 3; ++m)
-            if (m == c % 3) {
-              rho[b * RL + r][m].x += f * vv.x;
-              rho[b * RL + r][m].y += f * vv.y;
-            }
-        } else {
-          const T kv[3] = {tp * ix, tp * ky, tp * kidx(iz, N)};
-          add_P<C, T>(c, v[b * RL + r], kv, j0_at(b * RL + r), f1_at(b * RL + r), rho[b * RL + r]);
-        }
-      }
-  }
-  T oj0[BATCH ? E : 1], of1[BATCH ? E : 1], osc[BATCH ? E : 1];
-  if constexpr (BATCH) {
+  const auto times_f1 = [&] {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const auto tb = entry(e);
-      oj0[e] = (T)tb.x;
-      of1[e] = (T)tb.y;
-      osc[e] = (T)tb.z;
+      T f;
+      if constexpr (KEEP) f = f1[e];
+      else f = (T)entry(e).y;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        rho[e][m].x *= f;
+        rho[e][m].y *= f;
+      }
+    }
+  };
+  // where registers allow, the next component's z-line is loaded while the
+  // current one is transformed (the barriers of the exchanges wait on LDS
+  // traffic only)
+  constexpr bool AHEAD = E <= 8;
+  const C tw0 = tw_fetch<C, N>(tw);
+  C v[E], vn[AHEAD ? E : 1];
+  const auto load = [&](C *dst, int p) {
+    const C *src = in + (size_t)cin.slot[p] * hsz + base;
+#pragma unroll
+    for (int b = 0; b < E / R0; ++b)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) dst[b * R0 + r] = src[reg_pos<N, E, R0>(t, b, r) * plane];
+  };
+  if constexpr (AHEAD) load(vn, 0);
+  C *twl = lds + (size_t)TL * N;
+  tw_store<C, N>(twl, tw0, tw);
+  for (int p = 0; p < cin.n; ++p) {
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = vn[e];
+      if (p + 1 < cin.n) load(vn, p + 1);
+    } else {
+      load(v, p);
+    }
+    reg_fft_forward<T, N, E>(v, t, lds, TL, line, twl);
+    const int c = cin.comp[p];
+    if (cin.both && c < 3) {
+      if (cin.comp[p - 1] >= 3) {
+        times_f1();
+        if constexpr (!KEEP) read_j0();
+      }
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        v[e].x *= j0[e];
+        v[e].y *= j0[e];
+      }
+    }
+    // (zeroed modes are zeroed at the fold)
+    if constexpr (DG) {
+      const T f = c < 3 ? (T)1 : (T)-3;
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        if (m == c % 3)
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            rho[e][m].x += f * v[e].x;
+            rho[e][m].y += f * v[e].y;
+          }
+    } else {
+      const ColumnForm<T> F(c);
+      T col0[3];
+      F.fixed(tp * ix, tp * ky, col0);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const T kz = tp * kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
+        const T gx = c < 3 ? v[e].x : -v[e].y, gy = c < 3 ? v[e].y : v[e].x;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          const T col = col0[m] + F.A[m][2] * kz;
+          rho[e][m].x += col * gx;
+          rho[e][m].y += col * gy;
+        }
+      }
     }
   }
-  const auto j0_at = [&](int e) -> T {
-    if constexpr (HOIST) return tj0[e];
-    else if constexpr (BATCH) return oj0[e];
-    else return (T)entry(e).x;
-  };
-  const auto f1_at = [&](int e) -> T {
-    if constexpr (HOIST) return tf1[e];
-    else if constexpr (BATCH) return of1[e];
-    else return (T)entry(e).y;
-  };
-  const auto sc_at = [&](int e) -> T {
-    if constexpr (HOIST) return tsc[e];
-    else if constexpr (BATCH) return osc[e];
-    else return (T)entry(e).z;
-  };
   // u = scale (I - k^k^) rho
 #pragma unroll
-  for (int b = 0; b < E / RL; ++b)
+  for (int e = 0; e < E; ++e) {
+    const int iz = reg_pos<N, E, RL>(t, e / RL, e % RL);
+    const int kz = kidx(iz, N);
+    const int n2 = ix * ix + ky * ky + kz * kz;
+    const auto tb = ktab[n2];
+    if (zero_mode(ix, iy, iz, N)) {
 #pragma unroll
-    for (int r = 0; r < RL; ++r) {
-      const int e = b * RL + r;
-      const int iz = reg_pos<N, E, RL>(t, b, r);
-      const int kz = kidx(iz, N);
-      const int n2 = ix * ix + ky * ky + kz * kz;
-      if (zero_mode(ix, iy, iz, N)) {
+      for (int m = 0; m < 3; ++m) rho[e][m] = C{(T)0, (T)0};
+      continue;
+    }
+    T scale = (T)tb.z;
+    if (!cin.both) scale *= cin.kind ? (T)tb.y : (T)tb.x;
+    if (!cout.both) scale *= cout.kind ? (T)tb.y : (T)tb.x;
+    const T kv[3] = {(T)ix, (T)ky, (T)kz};
+    const T inv = (T)1 / (T)n2;
+    T krx = 0, kry = 0;
 #pragma unroll
-        for (int m = 0; m < 3; ++m) rho[e][m] = C{(T)0, (T)0};
-        continue;
-      }
-      const T scale = sc_at(e);
-      const T kv[3] = {(T)ix, (T)ky, (T)kz};
-      const T inv = (T)1 / (T)n2;
-      T krx = 0, kry = 0;
+    for (int m = 0; m < 3; ++m) {
+      krx += kv[m] * rho[e][m].x;
+      kry += kv[m] * rho[e][m].y;
+    }
 #pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        krx += kv[m] * rho[e][m].x;
-        kry += kv[m] * rho[e][m].y;
-      }
+    for (int m = 0; m < 3; ++m) {
+      rho[e][m].x = scale * (rho[e][m].x - kv[m] * krx * inv);
+      rho[e][m].y = scale * (rho[e][m].y - kv[m] * kry * inv);
+    }
+  }
+  if constexpr (!KEEP)
+    if (cout.both) read_j0();
+  for (int q = 0; q < cout.n; ++q) {
+    const int c = cout.comp[q];
+    if (cout.both && c >= 3 && cout.comp[q - 1] < 3) times_f1();
+    if constexpr (DG) {
+      const T f = c < 3 ? (T)1 : (T)3;
 #pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        rho[e][m].x = scale * (rho[e][m].x - kv[m] * krx * inv);
-        rho[e][m].y = scale * (rho[e][m].y - kv[m] * kry * inv);
+      for (int m = 0; m < 3; ++m)
+        if (m == c % 3)
+#pragma unroll
+          for (int e = 0; e < E; ++e) v[e] = C{f * rho[e][m].x, f * rho[e][m].y};
+    } else {
+      const ColumnForm<T> F(c);
+      T col0[3];
+      F.fixed(tp * ix, tp * ky, col0);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const T kz = tp * kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
+        T re = (T)0, im = (T)0;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          const T col = col0[m] + F.A[m][2] * kz;
+          re += col * rho[e][m].x;
+          im += col * rho[e][m].y;
+        }
+        // conj(i) = -i on couplets
+        v[e] = c < 3 ? C{re, im} : C{im, -re};
       }
     }
-  for (int q = 0; q < cout.n; ++q) {
-    const int c = cout.idx[q];
+    if (cout.both && c < 3)
 #pragma unroll
-    for (int b = 0; b < E / RL; ++b)
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int e = b * RL + r;
-        const int iz = reg_pos<N, E, RL>(t, b, r);
-        if (zero_mode(ix, iy, iz, N)) {
-          v[e] = C{(T)0, (T)0};
-          continue;
-        }
-        if constexpr (DG) {
-          const T f = c < 3 ? j0_at(e) : (T)3 * f1_at(e);
-          v[e] = C{(T)0, (T)0};
-#pragma unroll
-          for (int m = 0; m < 3; ++m)
-            if (m == c % 3) v[e] = C{f * rho[e][m].x, f * rho[e][m].y};
-        } else {
-          const T kv[3] = {tp * ix, tp * ky, tp * kidx(iz, N)};
-          v[e] = apply_Pdag<C, T>(c, rho[e], kv, j0_at(e), f1_at(e));
-        }
+      for (int e = 0; e < E; ++e) {
+        v[e].x *= j0[e];
+        v[e].y *= j0[e];
       }
     reg_fft_inverse<T, N, E>(v, t, lds, TL, line, twl);
-    C *dst = out + (size_t)q * hsz + base;
+    C *dst = out + (size_t)cout.slot[q] * hsz + base;
 #pragma unroll
     for (int b = 0; b < E / R0; ++b)
 #pragma unroll
@@ -761,7 +804,8 @@ kspace_dg3_kernel(const cplx<T> *__restrict__ in, cplx<T> *__restrict__ out, KGe
   // the factors of the thread's modes are loaded in groups of KG before
   // their first use (every mode's |k|^2 is inside the table, the zeroed
   // modes' included) instead of one round trip per mode
-  constexpr int KG = sizeof(T) == 8 ? 2 : (E < 8 ? E : 8);
+  constexpr int KG = sizeof(T) == 8 ? 2 : (E % 8 == 0 ? 8 : 6);
+  static_assert(E % KG == 0, "whole groups");
 #pragma unroll
   for (int g0 = 0; g0 < E; g0 += KG) {
     T sk[KG];
@@ -1288,48 +1332,57 @@ void launch_fused(Handle &h, const cplx<T> *in, const CompSet &cin, cplx<T> *out
                   const CompSet &cout, const cplx<T> *tw, bool dg) {
   using Tab = typename TabT<T>::type;
   const Tab *tab = sizeof(T) == 8 ? (const Tab *)h.ktab : (const Tab *)h.ktab32;
-  // the constraint operator's derivative gridding at 512 (couplet grids
-  // each way): all three grids in registers, 128-byte row
-  // segments (measured 1.63 -> 1.32 ms per FP32 launch at 512^3, and 3.10 ->
-  // 2.65 ms in FP64, against the accumulating form below; at 256 the FP32
-  // form spills)
+  // the constraint operator's derivative gridding (couplet grids each way):
+  // all three grids in registers, row segments of up to 128 bytes (against
+  // the accumulating form: 512^3 1.63 -> 1.14 ms in FP32 and 3.10 -> 2.32 in
+  // FP64, 192^3 64 -> 46 us in FP32, 128^3 35 -> 22 us in FP64)
   const auto couplet3 = [](const CompSet &c) {
     return c.n == 3 && c.idx[0] == 3 && c.idx[1] == 4 && c.idx[2] == 5;
   };
-  if constexpr (N == 512) {
+  // exchange area of l lines and the twiddle table
+  const auto lds_of = [](int l) { return (size_t)(l + 1) * N * sizeof(cplx<T>); };
+  if constexpr (N >= 32) {
     if (dg && couplet3(cin) && couplet3(cout)) {
-      // the line passes' element count in FP32, half of it in FP64
-      constexpr int E = sizeof(T) == 4 ? line_e(N) : line_e(N) / 2;
-      constexpr int TPL = N / E;
+      constexpr int E = dg3_e<T>(N), TPL = N / E;
       int tl = (int)(128 / sizeof(cplx<T>));
-      // exchange area of tl lines and the twiddle table
-      const auto lds_of = [](int l) { return (size_t)(l + 1) * N * sizeof(cplx<T>); };
-      while (tl > 1 && (tl * TPL > 512 || lds_of(tl) > (size_t)h.max_lds)) tl /= 2;
-      const size_t lds = lds_of(tl);
+      while (tl > 1 && (N / 2 % tl || tl * TPL > 512 || lds_of(tl) > (size_t)h.max_lds)) tl /= 2;
       const unsigned nb = (unsigned)(N * (N / 2 / tl));
       const T *kdg = sizeof(T) == 8 ? (const T *)h.kdg : (const T *)h.kdg32;
       if (!kdg) throw Error{PSE_ERR_INVALID, "k-space factor of derivative gridding missing"};
-      hipLaunchKernelGGL((kspace_dg3_kernel<T, N, E>), dim3(nb), dim3(tl * TPL), lds, h.stream,
-                         in, out, kgeom(h), kdg, tw, tl);
+      hipLaunchKernelGGL((kspace_dg3_kernel<T, N, E>), dim3(nb), dim3(tl * TPL), lds_of(tl),
+                         h.stream, in, out, kgeom(h), kdg, tw, tl);
       PSE_LAUNCH_CHECK();
       return;
     }
   }
-  constexpr int TPL = N / fused_e(N);
-  // at least four z-lines (64-byte row segments) per workgroup on long lines
+  constexpr int TPL = N / fused_e<T>(N);
+  // at least 64-byte row segments per workgroup on long lines (FP32 at 512^3,
+  // six grids in and three out: 2.93 ms with 32 bytes, 2.13 with 64)
   const int tl = lines_per_block(N, TPL, N * sizeof(cplx<T>), (size_t)N / 2,
-                                 TPL >= 128 ? 512 : 256);
-  // exchange area and the twiddle table
-  const size_t lds = (size_t)(tl + 1) * N * sizeof(cplx<T>);
-  if (lds > (size_t)h.max_lds)
+                                 TPL >= 64 ? 512 : 256);
+  if (lds_of(tl) > (size_t)h.max_lds)
     throw Error{PSE_ERR_HIP, "k-space kernel: LDS beyond the device's per-workgroup limit"};
+  // the slots with couplets first (inputs) or last (outputs)
+  const auto order = [](const CompSet &c, bool couplets_first) {
+    KOrder o{};
+    for (int pass = 0; pass < 2; ++pass)
+      for (int k = 0; k < c.n; ++k)
+        if ((c.idx[k] >= 3) == (couplets_first == (pass == 0))) {
+          o.slot[o.n] = k;
+          o.comp[o.n++] = c.idx[k];
+        }
+    o.kind = o.n && o.comp[0] >= 3;
+    o.both = o.n && (o.comp[0] >= 3) != (o.comp[o.n - 1] >= 3);
+    return o;
+  };
+  const KOrder oin = order(cin, true), oout = order(cout, false);
   const unsigned nb = (unsigned)(N * (N / 2 / tl));
   if (dg)
-    hipLaunchKernelGGL((kspace_fused_kernel<T, N, true>), dim3(nb), dim3(tl * TPL), lds,
-                       h.stream, in, cin, out, cout, kgeom(h), tab, tw, tl);
+    hipLaunchKernelGGL((kspace_fused_kernel<T, N, true>), dim3(nb), dim3(tl * TPL), lds_of(tl),
+                       h.stream, in, oin, out, oout, kgeom(h), tab, tw, tl);
   else
-    hipLaunchKernelGGL((kspace_fused_kernel<T, N, false>), dim3(nb), dim3(tl * TPL), lds,
-                       h.stream, in, cin, out, cout, kgeom(h), tab, tw, tl);
+    hipLaunchKernelGGL((kspace_fused_kernel<T, N, false>), dim3(nb), dim3(tl * TPL), lds_of(tl),
+                       h.stream, in, oin, out, oout, kgeom(h), tab, tw, tl);
   PSE_LAUNCH_CHECK();
 }
 

@@ -249,9 +249,9 @@ __device__ __forceinline__ void pair_action(const T *co, const T *e, const T *F,
 // component c of particle j at v[j stride + c - off]), or (PACK) a packed copy
 // in the sum's precision, 12 numbers a particle (F, L, s1..s5, 0) read as
 // three 16-byte loads (FP32; FP64 six).  The copy costs a launch, which few
-// particles (below PACK_MIN) do not repay (N = 2*10^4, FP64: 29 + 5 us with it, 24 without).  A
-// copy by component instead, whose loads touch fewer cache lines, was slower
-// (N = 10^6, FP32, 11 components: 536 against 409 us).
+// particles (below PACK_MIN) do not repay (N = 2*10^4, FP64: 29 + 5 us with
+// it, 24 without).  A copy by component instead, whose loads touch fewer cache
+// lines, was slower (N = 10^6, FP32, 11 components: 536 against 409 us).
 template <typename T> struct Moments {
   const double *v;
   Layout l;
