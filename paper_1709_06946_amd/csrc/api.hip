@@ -717,10 +717,10 @@ static void create(const pse_params &p, Handle &h) {
   h.cells.nc = h.d.cells;
   // spreading tiles of stile^3 grid points gather from the 27 neighbouring
   // tiles, so a stencil (P points) must not reach beyond one tile.
-  // (deformed lattices spread with atomics: the Gaussian does not factorise
-  // over the lattice axes, which the tile records rely on)
+  // (on deformed lattices the Gaussian does not factorise over the lattice
+  // axes, which tile records and weight rows rely on: they have bins only)
   h.stile = h.def.on ? 0 : spread_tile(h.d.grid, h.d.support);
-  h.sbins.nc = h.stile ? h.d.grid / h.stile : 0;
+  h.sbins.nc = bin_tile(h.p, h.d) ? h.d.grid / bin_tile(h.p, h.d) : 0;
   h.deriv = h.d.deriv_gridding == 2;
   if (p.stream || h.arena) {
     // the caller's stream (an allocation-free handle creates none: NULL is

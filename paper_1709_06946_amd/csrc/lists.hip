@@ -787,7 +787,7 @@ list_data_kernel(const double *__restrict__ x, PairArgs pa, R *__restrict__ rec,
 // (verify_lists), before any result that depends on it is handed over.
 static void build_lists(Handle &h, const double *xw, bool spreading) {
   const bool tiles = h.stile && spreading;
-  h.tiles_current = tiles;
+  h.tiles_current = h.sbins.nc && spreading;
   PairArgs pa;
   pa.n = h.n;
   pa.nc = h.cells.nc;
@@ -927,7 +927,7 @@ void pair_storage(Handle &h, size_t cap, bool at_create) {
 }
 
 static double cells_bytes(const Handle &h, bool spreading) {
-  const bool tiles = h.stile && spreading;
+  const bool tiles = h.sbins.nc && spreading;
   const double nc3 = (double)h.cells.nc * h.cells.nc * h.cells.nc
                      + (tiles ? (double)h.sbins.nc * h.sbins.nc * h.sbins.nc : 0.0);
   return (double)h.n * (24 + 16) * (tiles ? 2 : 1) + 12.0 * nc3;
@@ -1010,13 +1010,13 @@ static void build_all_bins(Handle &h, const double *x, const double *xw, bool ti
 void prepare_positions(Handle &h, const double *x, bool spreading) {
   ProfScope ps(h, PK_CELLS, cells_bytes(h, spreading));
   begin_lists(h);
-  build_all_bins(h, x, nullptr, h.stile && spreading);
+  build_all_bins(h, x, nullptr, h.sbins.nc && spreading);
   build_lists(h, h.xw, spreading);
 }
 
 void build_cells(Handle &h, const double *xw, bool spreading) {
   ProfScope ps(h, PK_CELLS, cells_bytes(h, spreading));
-  build_all_bins(h, nullptr, xw, h.stile && spreading);
+  build_all_bins(h, nullptr, xw, h.sbins.nc && spreading);
   build_lists(h, xw, spreading);
 }
 

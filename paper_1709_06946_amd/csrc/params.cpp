@@ -45,7 +45,7 @@ static int next_supported(int n) {
 static void fail(const char *msg) { throw Error{PSE_ERR_INVALID, msg}; }
 
 // All zero (unset) or the identity: the cube.
-static bool lattice_deformed(const pse_params &p) {
+bool lattice_deformed(const pse_params &p) {
   bool any = false, ident = true;
   for (int i = 0; i < 9; ++i) {
     if (p.deform[i] != 0.0) any = true;
@@ -227,9 +227,9 @@ size_t footprint(const pse_params &p, const pse_derived &d) {
            + (2 * n + n / 1024 + 16) * sizeof(int);
   const size_t ntab = (size_t)(2048.0 * d.rcut / (2 * p.radius)) + 16;
   bytes += ntab * NCOEF * (sizeof(double) + sizeof(float));
-  const int S = spread_tile(d.grid, d.support);
+  const int S = bin_tile(p, d);
   const size_t tiles3 = S ? ng3 / ((size_t)S * S * S) : 0;
-  if (S) {
+  if (S && !lattice_deformed(p)) {
     // tile CSR, one record per (tile, particle) pair, and the particles'
     // weight rows (gradient weights too with derivative gridding; both
     // precisions in mixed handles)

@@ -442,6 +442,14 @@ inline int spread_tile(int grid, int P) {
   return 0;
 }
 
+bool lattice_deformed(const pse_params &p);
+// Side of the tiles that a handle bins its particles into for spreading; on
+// deformed lattices tiles of 8 points or none (spreading by atomics).
+inline int bin_tile(const pse_params &p, const pse_derived &d) {
+  const int S = spread_tile(d.grid, d.support);
+  return lattice_deformed(p) && S != 8 ? 0 : S;
+}
+
 // Workgroups are dispatched to the 8 XCDs in turn; this maps the dispatch
 // index to a logical block so that each XCD takes a contiguous range of
 // logical blocks (and its L2 sees neighbouring work).  A bijection of
