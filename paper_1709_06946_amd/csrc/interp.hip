@@ -22,8 +22,6 @@
 
 namespace pse {
 
-namespace {
-
 // Value of the same lane of the row rotated by R.
 template <int R> __device__ __forceinline__ float rotated(float v) {
   return __int_as_float(
@@ -285,7 +283,7 @@ interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids,
 }
 
 template <typename T>
-InterpArgs interp_args(const Handle &h, Layout lo, bool accumulate, double scale) {
+static InterpArgs interp_args(const Handle &h, Layout lo, bool accumulate, double scale) {
   const GridGeom g = geom(h);
   InterpArgs ia;
   ia.order = h.cells.trav;
@@ -305,7 +303,7 @@ InterpArgs interp_args(const Handle &h, Layout lo, bool accumulate, double scale
 // Instances by support: a wavefront's unrolled planes.  Supports that the
 // tolerances 1e-2 ... 1e-6 ask for have one each, the others go with the next
 // (planes beyond P read the last one once more).
-template <typename F> void with_planes(int P, F f) {
+template <typename F> static void with_planes(int P, F f) {
   if (P <= 4) f(std::integral_constant<int, 4>());
   else if (P == 5) f(std::integral_constant<int, 5>());
   else if (P == 6) f(std::integral_constant<int, 6>());
@@ -318,14 +316,12 @@ template <typename F> void with_planes(int P, F f) {
   else throw Error{PSE_ERR_INVALID, "interpolation: support beyond 16"};
 }
 
-template <typename F> void with_count(int n, F f) {
+template <typename F> static void with_count(int n, F f) {
   if (n <= 3) f(std::integral_constant<int, 3>());
   else if (n <= 5) f(std::integral_constant<int, 5>());
   else if (n <= 8) f(std::integral_constant<int, 8>());
   else f(std::integral_constant<int, NC>());
 }
-
-}  // namespace
 
 template <typename T>
 void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, double *out,
