@@ -169,8 +169,8 @@ STAGE_KERNELS = {
     'fft': 'fft_xy_plane_kernel (x-y transform of one z-plane, both directions)',
     'fft_large': 'fft_x_r2c/c2r_kernel and fft_lines_kernel (x and y passes)',
     'kspace': 'kspace_fused_kernel (z transform, k-space kernel, inverse z transform)',
-    'spread': 'spread_list_kernel and spread_deriv_kernel',
-    'interp': 'interp_kernel and interp_deriv_kernel', 'real': 'real_pair_kernel',
+    'spread': 'spread_tile_kernel and spread_deriv_kernel',
+    'interp': 'interp_kernel and interp_deriv_kernel', 'real': 'real_pair_kernel and es_pair_kernel',
 }
 
 

@@ -556,7 +556,7 @@ __device__ __forceinline__ void pair_rows(unsigned blk, const double *__restrict
         nbr[slot] = j;
         if (rec64 || rec32) {
           // the unit vector now, the distance in field d2 for
-          // pair_coef_kernel (the table interpolation runs there on every
+          // pair_coefficients (the table interpolation runs there on every
           // lane, not on the few lanes of a candidate batch that found a
           // neighbour)
           const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
