@@ -809,7 +809,8 @@ static void create(const pse_params &p, Handle &h) {
   double **vs[6] = {&h.v0, &h.v1, &h.v2, &h.v3, &h.v4, &h.v5};
   for (double **v : vs) handle_alloc(h, (void **)v, NC * n * sizeof(double));
   double **es[5] = {&h.es_b, &h.es_x, &h.es_r, &h.es_d, &h.es_p};
-  for (double **v : es) handle_alloc(h, (void **)v, 5 * n * sizeof(double));
+  if (!h.arena)   // (the allocation-free product runs no solve)
+    for (double **v : es) handle_alloc(h, (void **)v, 5 * n * sizeof(double));
   handle_alloc(h, (void **)&h.lz_V, (size_t)(h.d.lanczos_maxit + 1) * NC * n * sizeof(double));
   handle_alloc(h, (void **)&h.gm_V, (size_t)(h.d.gmres_restart + 1) * 5 * n * sizeof(double));
   const size_t M = h.d.lanczos_maxit, R = h.d.gmres_restart;
