@@ -28,7 +28,8 @@ template <typename T> __device__ __forceinline__ T &part(cplx<T> &z, int k) {
 
 // ------------------------------------------------------------- spreading --
 
-// One wavefront per particle; its lanes cover the P^3 stencil.
+// Grids without spreading tiles: one wavefront per particle, its lanes covering
+// the P^3 stencil, added to cleared grids.
 template <typename T>
 __global__ void __launch_bounds__(256)
 spread_kernel(const double *__restrict__ x, const double *__restrict__ q,
@@ -1325,8 +1326,6 @@ void build_ktable(Handle &h) {
     PSE_LAUNCH_CHECK();
   }
 }
-
-size_t tile_record_bytes(int S) { return sizeof(int) + (3 * (size_t)S + 3) * sizeof(double); }
 
 namespace {
 

@@ -178,7 +178,7 @@ struct Handle {
   // spreading tiles (stile^3 grid points each)
   Bins cells;
   Bins sbins;
-  int stile;                 // grid points per spreading tile side (0: atomics)
+  int stile;                 // grid points per tile side with weight rows (0: none)
   bool tiles_current = false; // tile lists built at the last cell build's positions
   bool rows64_current = false; // and the weight rows in FP64
   int max_lds = 65536;       // dynamic LDS a workgroup may use on this device
