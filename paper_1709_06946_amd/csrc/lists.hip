@@ -12,6 +12,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "listsum.h"
 #include "pairrec.h"
 #include "stencil.h"
 
@@ -56,6 +57,9 @@ __device__ __forceinline__ int bin_of(const double *__restrict__ xw, int64_t i, 
   return (c[2] * nc + c[1]) * nc + c[0];
 }
 
+// Prefix sums saturate (list_add): exclusive ones are the neighbour's
+// inclusive ones, never a difference.
+
 // Exclusive scan in chunks of 1024 (256 threads x 4).
 __global__ void scan_block_kernel(const int *__restrict__ in, int *__restrict__ out,
                                   int *__restrict__ block_sums, int n) {
@@ -64,20 +68,20 @@ __global__ void scan_block_kernel(const int *__restrict__ in, int *__restrict__ 
   int v[4], sum = 0;
   for (int j = 0; j < 4; ++j) {
     v[j] = base + j < n ? in[base + j] : 0;
-    sum += v[j];
+    sum = list_add(sum, v[j]);
   }
   s[threadIdx.x] = sum;
   __syncthreads();
   for (int off = 1; off < 256; off <<= 1) {
     const int t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
     __syncthreads();
-    s[threadIdx.x] += t;
+    s[threadIdx.x] = list_add(s[threadIdx.x], t);
     __syncthreads();
   }
-  int run = s[threadIdx.x] - sum;
+  int run = threadIdx.x > 0 ? s[threadIdx.x - 1] : 0;
   for (int j = 0; j < 4; ++j) {
     if (base + j < n) out[base + j] = run;
-    run += v[j];
+    run = list_add(run, v[j]);
   }
   if (threadIdx.x == 255) block_sums[blockIdx.x] = s[255];
 }
@@ -97,12 +101,12 @@ __global__ void scan_sums_kernel(int *__restrict__ sums, int nb, int *__restrict
     for (int off = 1; off < 256; off <<= 1) {
       const int t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
       __syncthreads();
-      s[threadIdx.x] += t;
+      s[threadIdx.x] = list_add(s[threadIdx.x], t);
       __syncthreads();
     }
-    if (i < nb) sums[i] = carry + s[threadIdx.x] - v;
+    if (i < nb) sums[i] = list_add(carry, threadIdx.x > 0 ? s[threadIdx.x - 1] : 0);
     __syncthreads();
-    if (threadIdx.x == 255) carry += s[255];
+    if (threadIdx.x == 255) carry = list_add(carry, s[255]);
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -115,7 +119,7 @@ __global__ void scan_add_kernel(int *__restrict__ out, const int *__restrict__ s
   const int i = blockIdx.x * 1024 + threadIdx.x * 4;
   const int add = sums[blockIdx.x];
   for (int j = 0; j < 4; ++j)
-    if (i + j < n) out[i + j] += add;
+    if (i + j < n) out[i + j] = list_add(out[i + j], add);
 }
 
 // Exclusive prefix sums of n ints by one workgroup of 1024: thread t takes a
@@ -127,32 +131,32 @@ __device__ __forceinline__ void scan_one(const int *in, int *out, int n, int *ws
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int per = (n + 1023) / 1024;
   const int lo = min(t * per, n), hi = min(lo + per, n);
-  int sum = 0;
-  for (int i = lo; i < hi; ++i) sum += in[i];
-  int incl = sum;
+  int incl = 0;
+  for (int i = lo; i < hi; ++i) incl = list_add(incl, in[i]);
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const int u = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += u;
+    if (lane >= off) incl = list_add(incl, u);
   }
+  const int below = __shfl_up(incl, 1, 64);
   if (lane == 63) wsum[wv] = incl;
   __syncthreads();
   if (wv == 0) {
-    const int w = lane < 16 ? wsum[lane] : 0;
-    int wi = w;
+    int wi = lane < 16 ? wsum[lane] : 0;
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       const int u = __shfl_up(wi, off, 64);
-      if (lane >= off) wi += u;
+      if (lane >= off) wi = list_add(wi, u);
     }
-    if (lane < 16) wsum[lane] = wi - w;
+    const int before = __shfl_up(wi, 1, 64);
+    if (lane < 16) wsum[lane] = lane > 0 ? before : 0;
   }
   __syncthreads();
-  int run = wsum[wv] + incl - sum;
+  int run = list_add(wsum[wv], lane > 0 ? below : 0);
   for (int i = lo; i < hi; ++i) {
     const int x = in[i];
     out[i] = run;
-    run += x;
+    run = list_add(run, x);
   }
   if (t == 1023) {
     if (total) *total = run;
@@ -478,7 +482,7 @@ struct PairArgs {
   double inv_cs, cs2;   // cells per unit length, squared cell side
   double inv_dr;
   int n2a, ntab;
-  int64_t cap;     // pair-list capacity: entries at or beyond it are not written
+  int limit;       // entries the pair list holds: those at or beyond are not written
   int *status;     // PSE_STATUS_PAIR_OVERFLOW is or-ed in when one is dropped
   int def;         // deformed lattice: positions are lattice coordinates and
   double A[9];     // separations are mapped back by A
@@ -531,7 +535,7 @@ __device__ __forceinline__ void pair_rows(unsigned blk, const double *__restrict
   }
   int first, pre, total;
   nbr27_setup(lane, cc[0], cc[1], cc[2], nc, cell_start, first, pre, total, skip);
-  int pos = FILL ? start[t] : 0;
+  const int row = FILL ? start[t] : 0;
   int count = 0;
   for (int base = 0; base < total; base += 64) {
     const int idx = base + lane;
@@ -547,12 +551,9 @@ __device__ __forceinline__ void pair_rows(unsigned blk, const double *__restrict
       count += ok ? 1 : 0;
     } else {
       const unsigned long long m = __ballot(ok);
-      const int slot = pos + __popcll(m & ((1ull << lane) - 1ull));
-      if (ok && slot >= pa.cap) {
-        atomicOr(pa.status, (int)PSE_STATUS_PAIR_OVERFLOW);
-        ok = false;
-      }
-      if (ok) {
+      const int slot =
+          list_slot(row, count + __popcll(m & ((1ull << lane) - 1ull)), pa.limit);
+      if (ok && slot >= 0) {
         nbr[slot] = j;
         if (rec64 || rec32) {
           // the unit vector now, the distance in field d2 for
@@ -574,7 +575,12 @@ __device__ __forceinline__ void pair_rows(unsigned blk, const double *__restrict
           }
         }
       }
-      pos += __popcll(m);
+      count += __popcll(m);
+      if (m && list_slot(row, count - 1, pa.limit) < 0) {
+        // the list is full: nothing more of this row fits
+        if (lane == 0) atomicOr(pa.status, (int)PSE_STATUS_PAIR_OVERFLOW);
+        return;
+      }
     }
   }
   if (!FILL) {
@@ -591,7 +597,7 @@ __device__ __forceinline__ void pair_rows(unsigned blk, const double *__restrict
 template <typename R>
 __device__ __forceinline__ void pair_coefficients(unsigned blk, unsigned nblk, R *__restrict__ rec,
                                                   const R *__restrict__ tab, const PairArgs &pa) {
-  const int64_t len = min((int64_t)pa.start[pa.n], pa.cap);
+  const int64_t len = list_row_end(pa.start[pa.n], pa.limit);
   constexpr int field[NCOEF] = {F_A, F_B, F_C1, F_C2, F_D2, F_D3, F_D4};
   for (int64_t s = (int64_t)blk * blockDim.x + threadIdx.x; s < len;
        s += (int64_t)nblk * blockDim.x) {
@@ -653,7 +659,7 @@ __device__ __forceinline__ void tile_rows(unsigned blk, const double *__restrict
       count += ok ? 1 : 0;
     } else {
       const unsigned long long m = __ballot(ok);
-      if (ok) ta.rec[pos + __popcll(m & ((1ull << lane) - 1ull))] = TileRec{p, win};
+      if (ok) ta.rec[(int64_t)pos + __popcll(m & ((1ull << lane) - 1ull))] = TileRec{p, win};
       pos += __popcll(m);
     }
   }
@@ -799,7 +805,7 @@ static void build_lists(Handle &h, const double *xw, bool spreading) {
   pa.inv_dr = 1.0 / h.dr;
   pa.n2a = h.n2a;
   pa.ntab = h.ntab;
-  pa.cap = (int64_t)h.pl_cap;
+  pa.limit = list_limit((int64_t)h.pl_cap);
   pa.status = h.dctl + CTL_STATUS;
   pa.def = h.def.on;
   for (int i = 0; i < 9; ++i) pa.A[i] = h.def.A[i];
@@ -882,6 +888,9 @@ void verify_lists(Handle &h) {
   for (int k = 0; k < h.lists_open; ++k) total = std::max(total, w[INFO_PAIRS + k]);
   h.lists_open = 0;
   if (w[INFO_BAD]) throw Error{PSE_ERR_NONFINITE, "non-finite particle position"};
+  if (total >= LIST_MAX)
+    throw Error{PSE_ERR_NOMEM, "real-space pair list beyond " + std::to_string(LIST_MAX) +
+                                   " pairs"};
   if ((size_t)total > h.pl_cap) {
     if (h.arena)
       throw Error{PSE_ERR_NOMEM, "real-space pair list beyond its capacity in the "

@@ -30,6 +30,7 @@
 // Both are tabulated once per handle on the GPU (FP64) on a uniform r grid
 // with a node at r = 2a, and interpolated with 4-point Lagrange stencils that
 // never straddle r = 2a.
+#include "listsum.h"
 #include "pairrec.h"
 
 namespace pse {
@@ -366,7 +367,7 @@ struct RealArgs {
   int in_mask;    // 1: F, 2: L, 4: S
   int out_mask;   // 1: U, 2: Omega, 4: E
   Layout lout;
-  int64_t cap;    // pair-list capacity (entries beyond it were never written)
+  int limit;      // entries the pair list holds (none beyond was written)
   double L;       // box; deformed lattice: separations mapped by A
   int def;
   double A[9];
@@ -417,7 +418,7 @@ real_pair_kernel(const double *__restrict__ xw, Moments<T> in,
     pair_action<T, UF, UC, OU, OD>(co, e0, F, C, U, D);
   }
   constexpr bool NEED_AB = UF && OU, NEED_C12 = (UF && OD) || (UC && OU), NEED_D = UC && OD;
-  const int s1 = (int)min((int64_t)start[t + 1], ra.cap);
+  const int s1 = list_row_end(start[t + 1], ra.limit);
   const auto record = [&](int s, T *co, T *e) {
     const Entry<const T> p(rec, (uint32_t)s);
     if constexpr (NEED_AB) {
@@ -546,7 +547,7 @@ es_pair_kernel(const double *__restrict__ xw, const double *__restrict__ in, Lay
   const int lane = threadIdx.x % GROUP;
   if (t >= ra.n) return;
   const int i = perm[t];
-  const int s1 = (int)min((int64_t)start[t + 1], ra.cap);
+  const int s1 = list_row_end(start[t + 1], ra.limit);
   T acc[5] = {}, m[5], e[3];
   const double *in6 = in + 6 - lin.off;
   const auto moments = [&](int j) {
@@ -617,7 +618,7 @@ static RealArgs real_args(const Handle &h, int in_mask, Layout lout, int out_mas
   ra.lout = lout;
   ra.in_mask = in_mask;
   ra.out_mask = out_mask;
-  ra.cap = (int64_t)h.pl_cap;
+  ra.limit = list_limit((int64_t)h.pl_cap);
   ra.L = h.p.box;
   ra.def = h.def.on;
   for (int k = 0; k < 9; ++k) ra.A[k] = h.def.A[k];
