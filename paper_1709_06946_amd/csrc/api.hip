@@ -862,8 +862,9 @@ static void release(Handle &h) {
 
 // Runs f, an entry point's work, and turns what it throws into a status.  A
 // pair list beyond its capacity (Regrow) grows and f starts over: results are
-// handed over only after the lists they depend on were verified, so a run that
-// stops there has left the caller's state as it was.
+// handed over only after the lists they depend on were verified, or by kernels
+// that look themselves (stopped_word), so a run that stops there has left the
+// caller's state as it was.
 template <typename F> static int guarded(pse_handle *hd, F &&f) {
   RelaxedCaptureScope relaxed;
   // an error left by the caller's own runtime calls is not this call's
@@ -1436,11 +1437,11 @@ int pse_spread(pse_handle *hd, const double *x, const double *q, int ncomp, doub
     if (h.mixed) {
       float *g = reinterpret_cast<float *>(h.g32.gin);
       spread<float>(h, h.xw, h.v4, Layout{ncomp, 0}, cs, g);
-      to_double<float>(h, g, cnt, out);
+      to_double<float>(h, g, cnt, out, stopped_word(h));
     } else {
       double *g = reinterpret_cast<double *>(h.g64.gin);
       spread<double>(h, h.xw, h.v4, Layout{ncomp, 0}, cs, g);
-      to_double<double>(h, g, cnt, out);
+      to_double<double>(h, g, cnt, out, stopped_word(h));
     }
     finish(h);
   });

@@ -1265,9 +1265,10 @@ __global__ void from_double_kernel(const double *src, size_t n, T *dst) {
 }
 
 template <typename T>
-__global__ void to_double_kernel(const T *src, size_t n, double *dst) {
+__global__ void to_double_kernel(const T *src, size_t n, double *dst, const int *stopped,
+                                 int call) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = (double)src[i];
+  if (i < n && !(stopped && *stopped == call)) dst[i] = (double)src[i];
 }
 
 // ----------------------------------------------------------- host side --
@@ -1583,9 +1584,10 @@ template <typename T> void from_double(Handle &h, const double *src, size_t n, T
   PSE_LAUNCH_CHECK();
 }
 
-template <typename T> void to_double(Handle &h, const T *src, size_t n, double *dst) {
+template <typename T>
+void to_double(Handle &h, const T *src, size_t n, double *dst, const int *stopped) {
   hipLaunchKernelGGL(to_double_kernel<T>, dim3(nblocks(n, 256)), dim3(256), 0, h.stream,
-                     src, n, dst);
+                     src, n, dst, stopped, h.call);
   PSE_LAUNCH_CHECK();
 }
 
@@ -1606,7 +1608,7 @@ template <typename T> void to_double(Handle &h, const T *src, size_t n, double *
   template void spread_deriv<T>(Handle &, const double *, Layout, bool, bool, T *); \
   template void zero_grids<T>(Handle &, T *, int);                               \
   template void from_double<T>(Handle &, const double *, size_t, T *);           \
-  template void to_double<T>(Handle &, const T *, size_t, double *);
+  template void to_double<T>(Handle &, const T *, size_t, double *, const int *);
 INST(double)
 INST(float)
 #undef INST

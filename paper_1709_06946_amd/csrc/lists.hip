@@ -21,20 +21,20 @@ namespace pse {
 // ---------------------------------------------------------- positions --
 
 // Position i wrapped into [0, L)^3 (a deformed lattice's in lattice
-// coordinates A^-1 x first).  Non-finite coordinates raise *bad and the status
-// bit and are replaced by 0, so that every later kernel stays in bounds until
-// the host reports the error.
+// coordinates A^-1 x first).  Non-finite coordinates are reported and replaced
+// by 0, so that every later kernel stays in bounds until the host reports the
+// error.
 __device__ __forceinline__ void wrapped_position(const double *__restrict__ x, int64_t i, double L,
-                                                 const Deform &df, int *bad, int *status,
-                                                 double *y) {
+                                                 const Deform &df, const Reports &rp, double *y) {
   const double p[3] = {x[3 * i], x[3 * i + 1], x[3 * i + 2]};
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     double v = df.on ? df.Ai[3 * d] * p[0] + df.Ai[3 * d + 1] * p[1] + df.Ai[3 * d + 2] * p[2]
                      : p[d];
     if (!isfinite(v)) {
-      *bad = 1;
-      atomicOr(status, (int)PSE_STATUS_NONFINITE_POS);
+      *rp.bad = 1;
+      *rp.stopped = rp.call;
+      atomicOr(rp.status, (int)PSE_STATUS_NONFINITE_POS);
       v = 0.0;
     }
     v -= L * floor(v / L);
@@ -228,12 +228,11 @@ struct BinSet {
 // x (may be NULL) wrapped into xu; counts cleared.
 __global__ void __launch_bounds__(256)
 bins_begin_kernel(const double *__restrict__ x, double *__restrict__ xu, int64_t n, double L,
-                  Deform df, int *__restrict__ bad, int *__restrict__ status, BinSet a,
-                  BinSet b) {
+                  Deform df, Reports rp, BinSet a, BinSet b) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (x && i < n) {
     double y[3];
-    wrapped_position(x, i, L, df, bad, status, y);
+    wrapped_position(x, i, L, df, rp, y);
 #pragma unroll
     for (int d = 0; d < 3; ++d) xu[3 * i + d] = y[d];
   }
@@ -377,14 +376,14 @@ __device__ __forceinline__ void bins_one(const BinJob &job, int n, int *lds, int
 // binned in that order.  Else workgroup 0 bins the cells, 1 the tiles.
 template <bool SORT>
 __global__ void __launch_bounds__(1024)
-bins_one_kernel(const double *__restrict__ x, double *xu, int n, double L, Deform df, int *bad,
-                int *status, BinJob cells, BinJob tiles, int *order, double *xs) {
+bins_one_kernel(const double *__restrict__ x, double *xu, int n, double L, Deform df, Reports rp,
+                BinJob cells, BinJob tiles, int *order, double *xs) {
   extern __shared__ int bin_lds[];
   __shared__ int wsum[16];
   if constexpr (SORT) {
     for (int i = threadIdx.x; i < n; i += 1024) {
       double y[3];
-      wrapped_position(x, i, L, df, bad, status, y);
+      wrapped_position(x, i, L, df, rp, y);
 #pragma unroll
       for (int d = 0; d < 3; ++d) xu[3 * i + d] = y[d];
     }
@@ -483,7 +482,7 @@ struct PairArgs {
   double inv_dr;
   int n2a, ntab;
   int limit;       // entries the pair list holds: those at or beyond are not written
-  int *status;     // PSE_STATUS_PAIR_OVERFLOW is or-ed in when one is dropped
+  Reports rp;
   int def;         // deformed lattice: positions are lattice coordinates and
   double A[9];     // separations are mapped back by A
   const int *perm, *cell_start, *cell_at;
@@ -578,7 +577,10 @@ __device__ __forceinline__ void pair_rows(unsigned blk, const double *__restrict
       count += __popcll(m);
       if (m && list_slot(row, count - 1, pa.limit) < 0) {
         // the list is full: nothing more of this row fits
-        if (lane == 0) atomicOr(pa.status, (int)PSE_STATUS_PAIR_OVERFLOW);
+        if (lane == 0) {
+          *pa.rp.stopped = pa.rp.call;
+          atomicOr(pa.rp.status, (int)PSE_STATUS_PAIR_OVERFLOW);
+        }
         return;
       }
     }
@@ -786,6 +788,10 @@ list_data_kernel(const double *__restrict__ x, PairArgs pa, R *__restrict__ rec,
   else weight_rows<DERIV>(blockIdx.x - nbc, x, wa, w_lds);
 }
 
+static Reports reports(const Handle &h) {
+  return Reports{h.info + INFO_BAD, h.dctl + CTL_STATUS, h.dctl + CTL_STOPPED, h.call};
+}
+
 // The pair list for the current cells and, with tiles, the tile lists and the
 // particles' weights.  No host read in between: the list keeps its capacity,
 // pairs beyond it are not written (and flagged in the device status), and a
@@ -806,7 +812,7 @@ static void build_lists(Handle &h, const double *xw, bool spreading) {
   pa.n2a = h.n2a;
   pa.ntab = h.ntab;
   pa.limit = list_limit((int64_t)h.pl_cap);
-  pa.status = h.dctl + CTL_STATUS;
+  pa.rp = reports(h);
   pa.def = h.def.on;
   for (int i = 0; i < 9; ++i) pa.A[i] = h.def.A[i];
   pa.perm = h.cells.perm;
@@ -903,6 +909,7 @@ void verify_lists(Handle &h) {
 
 void begin_lists(Handle &h) {
   h.lists_open = 0;
+  h.call = h.call < INT32_MAX ? h.call + 1 : 1;
   if (h.async) return;
   if (h.arena) fill_int(h, h.info, INFO_WORDS, 0);
   else
@@ -968,14 +975,13 @@ static void build_all_bins(Handle &h, const double *x, const double *xw, bool ti
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)ONE_WG_LDS);
     });
     PSE_HIP(attr);
-    int *bad = h.info + INFO_BAD, *status = h.dctl + CTL_STATUS;
     if (x)
       hipLaunchKernelGGL(bins_one_kernel<true>, dim3(1), dim3(1024), lds, h.stream, x, h.xh,
-                         (int)h.n, h.p.box, h.def, bad, status, bin_job(h, h.cells, h.xh),
+                         (int)h.n, h.p.box, h.def, reports(h), bin_job(h, h.cells, h.xh),
                          bin_job(h, tb, h.xw), h.order, h.xw);
     else
       hipLaunchKernelGGL(bins_one_kernel<false>, dim3(tiles ? 2 : 1), dim3(1024), lds, h.stream,
-                         nullptr, nullptr, (int)h.n, h.p.box, h.def, bad, status,
+                         nullptr, nullptr, (int)h.n, h.p.box, h.def, reports(h),
                          bin_job(h, h.cells, xw), bin_job(h, tb, xw), nullptr, nullptr);
     PSE_LAUNCH_CHECK();
     return;
@@ -986,7 +992,7 @@ static void build_all_bins(Handle &h, const double *x, const double *xw, bool ti
   const size_t most = std::max((size_t)std::max(cs.bins(), ts.bins()), x ? (size_t)h.n : 0);
   const unsigned jobs = tiles ? 2 : 1, np = nblocks(h.n, 256);
   hipLaunchKernelGGL(bins_begin_kernel, dim3(nblocks(most, 256)), dim3(256), 0, h.stream, x, xu,
-                     h.n, h.p.box, h.def, h.info + INFO_BAD, h.dctl + CTL_STATUS, cs, ts);
+                     h.n, h.p.box, h.def, reports(h), cs, ts);
   PSE_LAUNCH_CHECK();
   hipLaunchKernelGGL(bins_count_kernel, dim3(np, jobs), dim3(256), 0, h.stream, xb, h.n, cs, ts);
   PSE_LAUNCH_CHECK();
@@ -1039,13 +1045,15 @@ gather_rows_kernel(const double *__restrict__ src, const int *__restrict__ order
   dst[i] = src[(int64_t)order[t] * w + (i - t * w)];
 }
 
-// The components [lo, hi) of the rows; *bad is raised (bad not NULL) by a
-// non-finite number in any component of the rows as they are left.
+// The components [lo, hi) of the rows, unless the call has stopped
+// (stopped_word); *bad is raised (bad not NULL) by a non-finite number in any
+// component of the rows as they are left.
 __global__ void __launch_bounds__(256)
 scatter_rows_kernel(const double *__restrict__ src, const int *__restrict__ order, int w, int lo,
-                    int hi, int64_t nw, double *__restrict__ dst, int *__restrict__ bad) {
+                    int hi, int64_t nw, double *__restrict__ dst, int *__restrict__ bad,
+                    const int *__restrict__ stopped, int call) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nw) return;
+  if (i >= nw || (stopped && *stopped == call)) return;
   const int64_t t = i / w;
   const int c = (int)(i - t * w);
   double *o = dst + (int64_t)order[t] * w + c;
@@ -1064,7 +1072,8 @@ void gather_rows(Handle &h, const double *src, int w, double *dst) {
 
 void scatter_rows(Handle &h, const double *src, int w, int lo, int hi, double *dst, int *bad) {
   hipLaunchKernelGGL(scatter_rows_kernel, dim3(nblocks((size_t)h.n * w, 256)), dim3(256), 0,
-                     h.stream, src, (const int *)h.order, w, lo, hi, h.n * w, dst, bad);
+                     h.stream, src, (const int *)h.order, w, lo, hi, h.n * w, dst, bad,
+                     stopped_word(h), h.call);
   PSE_LAUNCH_CHECK();
 }
 

@@ -205,6 +205,7 @@ struct Handle {
   // arena's; lists_open lists of the running call are not yet verified
   int *info = nullptr;
   int lists_open = 0;
+  int call = 0;              // position updates so far (see CTL_STOPPED)
   void *mpack = nullptr;     // pair sums: moments packed 12 per particle (FP64 size)
   // real-space pair list (CSR in cell order): start[N+1], neighbour index and
   // 10 numbers of pair data per entry (doubles in FP64 handles, floats in
@@ -280,8 +281,18 @@ struct Regrow {
 
 // Device control words of a handle (ints at h.dctl): Lanczos and GMRES
 // selection state (found, count, not converged), the status bits
-// (PSE_STATUS_*) of asynchronous calls.
-enum { CTL_LZ = 0, CTL_GM = 4, CTL_STATUS = 8, CTL_WORDS = 16 };
+// (PSE_STATUS_*) of asynchronous calls, the number of the last call (h.call)
+// that met a non-finite position or a full pair list.
+enum { CTL_LZ = 0, CTL_GM = 4, CTL_STATUS = 8, CTL_STOPPED = 12, CTL_WORDS = 16 };
+
+// What the list builders' kernels report of a call: a non-finite position
+// (bad, status, stopped) and a pair list that is full (status, stopped).
+struct Reports {
+  int *bad;          // h.info's word
+  int *status;
+  int *stopped;      // takes `call`
+  int call;
+};
 
 // Device buffer of a handle: from its arena when it has one (throws
 // PSE_ERR_NOMEM when the arena is full), else from the runtime (dev_alloc).
@@ -408,7 +419,8 @@ template <typename T> void zero_grids(Handle &h, T *g, int ncomp);
 int ktable_len(int grid);                         // entries of the |k|^2 table
 void build_ktable(Handle &h);
 template <typename T> void from_double(Handle &h, const double *src, size_t n, T *dst);
-template <typename T> void to_double(Handle &h, const T *src, size_t n, double *dst);
+template <typename T>
+void to_double(Handle &h, const T *src, size_t n, double *dst, const int *stopped = nullptr);
 
 // Initial capacity of the real-space pair list: twice the pair count of a
 // uniform suspension (neighbours within rcut), plus slack.
@@ -514,6 +526,14 @@ void build_cells(Handle &h, const double *xw, bool spreading = true);
 // idle (throws on non-finite positions; Regrow on a list beyond its capacity).
 void verify_lists(Handle &h);
 void regrow_pairs(Handle &h, size_t total);
+// The word that the kernels handing results to the caller look at, or NULL
+// (asynchronous calls hand over what they have, with their status): they write
+// nothing when it holds h.call.  The host learns of a stopped call only after
+// them, when it waits, and the caller's arrays are then as they were, also for
+// a call that starts over (Regrow) with an input among its outputs.
+inline const int *stopped_word(const Handle &h) {
+  return h.async ? nullptr : h.dctl + CTL_STOPPED;
+}
 // dst[t] = src[order[t]], and dst[order[t]] = src[t] for the components
 // [lo, hi) of rows of w numbers (bad: see scatter_rows_kernel).
 void gather_rows(Handle &h, const double *src, int w, double *dst);
