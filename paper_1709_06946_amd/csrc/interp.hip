@@ -10,7 +10,10 @@
 // and the x and y weights come in once per column.  A point costs one load and
 // one or two multiply-adds; with weights and offsets formed per point the
 // arithmetic was as long as the loads (633 vector instructions per particle at
-// support 8, 2400 at support 10; now 195 and 270 in FP32).  Gradient
+// support 8, 2400 at support 10).  Weights, products and sums are FP64 on FP32
+// grids too: rounded one-dimensional weights share their errors over whole
+// rows and planes of the stencil (5.5e-8 of the value, rms, against 3.4e-8 with
+// each point's weight rounded once), and FP64 costs the step under 1 %.  Gradient
 // interpolation at 512^3, N = 10^6: 1.89 -> 1.45 ms, at 192^3, N = 2*10^5: 345
 // -> 207 us; five components at 384^3, N = 2*10^5, support 10: 1.17 -> 0.99
 // ms.  What bounds it now is the L1 cache: a load of 8 rows of 32 bytes takes
@@ -23,10 +26,6 @@
 namespace pse {
 
 // Value of the same lane of the row rotated by R.
-template <int R> __device__ __forceinline__ float rotated(float v) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + R, 0xf, 0xf, true));
-}
 template <int R> __device__ __forceinline__ double rotated(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + R, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + R, 0xf, 0xf, true);
@@ -35,16 +34,6 @@ template <int R> __device__ __forceinline__ double rotated(double v) {
 
 // a's upper and b's lower halves exchanged (rows of 16: a's odd with b's even
 // rows), then added: lane sums of a and b side by side in one register.
-__device__ __forceinline__ float fold32(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                  false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float fold16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                  false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 __device__ __forceinline__ double fold32(double a, double b) {
   const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a),
                                                   (unsigned)__double2loint(b), false, false);
@@ -62,8 +51,8 @@ __device__ __forceinline__ double fold16(double a, double b) {
 
 // Wavefront sums of four values: the sum of value SUM_OF[r] in every lane of
 // row r.
-template <typename T> __device__ __forceinline__ T wave_sum4(T a, T b, T c, T d) {
-  T v = fold16(fold32(a, b), fold32(c, d));
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d) {
+  double v = fold16(fold32(a, b), fold32(c, d));
   v += rotated<8>(v);
   v += rotated<4>(v);
   v += rotated<2>(v);
@@ -74,12 +63,12 @@ template <typename T> __device__ __forceinline__ T wave_sum4(T a, T b, T c, T d)
 __device__ __forceinline__ int sum_of(int row) { return row == 1 ? 2 : (row == 2 ? 1 : row); }
 
 // Wavefront sums of r[0..M), value k handed to store(k, sum) in one lane.
-template <int M, typename T, typename Store>
-__device__ __forceinline__ void wave_sums(int lane, const T (&r)[M], Store store) {
+template <int M, typename Store>
+__device__ __forceinline__ void wave_sums(int lane, const double (&r)[M], Store store) {
 #pragma unroll
   for (int k = 0; k < M; k += 4) {
-    const T v = wave_sum4(r[k], k + 1 < M ? r[k + 1] : (T)0, k + 2 < M ? r[k + 2] : (T)0,
-                          k + 3 < M ? r[k + 3] : (T)0);
+    const double v = wave_sum4(r[k], k + 1 < M ? r[k + 1] : 0.0, k + 2 < M ? r[k + 2] : 0.0,
+                               k + 3 < M ? r[k + 3] : 0.0);
     const int j = k + sum_of(lane / 16);
     if (lane % 16 == 0 && j < M) store(j, v);
   }
@@ -157,9 +146,7 @@ template <typename T, typename W, int PZ> struct Columns {
 };
 
 // the weight of a row's entry
-__device__ __forceinline__ float plain(float w) { return w; }
 __device__ __forceinline__ double plain(double w) { return w; }
-__device__ __forceinline__ float plain(const float2 &w) { return w.x; }
 __device__ __forceinline__ double plain(const double2 &w) { return w.x; }
 
 // Components cs of the particles' vectors from one grid each (M of them;
@@ -174,7 +161,7 @@ interp_kernel(const double *__restrict__ x, const T *__restrict__ grids,
   if (t >= ia.n) return;
   const Columns<T, W, PZ> C(ia, x, wt, t, lane);
   constexpr int NJ = Columns<T, W, PZ>::NJ;
-  T acc[M];
+  double acc[M];
 #pragma unroll
   for (int k = 0; k < M; ++k) {
     const T *g = grids + (size_t)min(k, cs.n - 1) * ia.ngrid;
@@ -183,19 +170,20 @@ interp_kernel(const double *__restrict__ x, const T *__restrict__ grids,
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int c = 0; c < PZ; ++c) v[j][c] = C.load(g, j, c);
-    acc[k] = (T)0;
+    double a = 0.0;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      T s = (T)0;
+      double s = 0.0;
 #pragma unroll
-      for (int c = 0; c < PZ; ++c) s += v[j][c] * plain(C.Z[c]);
-      acc[k] += s * (plain(C.X[j]) * plain(C.Y[j]));
+      for (int c = 0; c < PZ; ++c) s += (double)v[j][c] * plain(C.Z[c]);
+      a += s * (plain(C.X[j]) * plain(C.Y[j]));
     }
+    acc[k] = a;
   }
-  wave_sums<M>(lane, acc, [&](int k, T v) {
+  wave_sums<M>(lane, acc, [&](int k, double v) {
     if (k >= cs.n) return;
     double *o = out + (size_t)C.p * ia.lo.stride + cs.idx[k] - ia.lo.off;
-    const double r = ia.scale * (double)v;
+    const double r = ia.scale * v;
     *o = ia.accumulate ? *o + r : r;
   });
 }
@@ -212,16 +200,16 @@ interp_kernel(const double *__restrict__ x, const T *__restrict__ grids,
 template <typename T, int PZ, bool HU, bool ROT>
 __global__ void __launch_bounds__(256)
 interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids,
-                    const cplx<T> *__restrict__ wt, InterpArgs ia, int mask,
+                    const double2 *__restrict__ wt, InterpArgs ia, int mask,
                     double *__restrict__ out) {
-  using W = cplx<T>;   // (weight, gradient weight)
+  using W = double2;   // (weight, gradient weight)
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * 4 +
                     __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (t >= ia.n) return;
   const Columns<T, W, PZ> C(ia, x, wt, t, lane);
   constexpr int NJ = Columns<T, W, PZ>::NJ, NU = HU ? 3 : 0, NR = ROT ? 3 : 0;
-  T G[3][3], U[3];
+  double G[3][3], U[3];
 #pragma unroll
   for (int k = 0; k < 3 + NU; ++k) {
     const T *g = grids + (size_t)k * ia.ngrid;
@@ -230,15 +218,15 @@ interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids,
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int c = 0; c < PZ; ++c) v[j][c] = C.load(g, j, c);
-    T a[3] = {(T)0, (T)0, (T)0};
+    double a[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       // the column's sums with the weight and the gradient weight along z
-      T s = (T)0, z = (T)0;
+      double s = 0.0, z = 0.0;
 #pragma unroll
       for (int c = 0; c < PZ; ++c) {
-        s += v[j][c] * C.Z[c].x;
-        if (k >= NU) z += v[j][c] * C.Z[c].y;
+        s += (double)v[j][c] * C.Z[c].x;
+        if (k >= NU) z += (double)v[j][c] * C.Z[c].y;
       }
       const W X = C.X[j], Y = C.Y[j];
       if (k < NU) {
@@ -256,12 +244,12 @@ interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids,
       for (int i = 0; i < 3; ++i) G[k - NU][i] = a[i];
     }
   }
-  T r[5 + NR + NU];
+  double r[5 + NR + NU];
   r[0] = G[0][1] + G[1][0];
   r[1] = G[0][2] + G[2][0];
   r[2] = G[1][2] + G[2][1];
   r[3] = G[0][0] - G[1][1];
-  r[4] = G[0][0] + G[1][1] - (T)2 * G[2][2];
+  r[4] = G[0][0] + G[1][1] - 2.0 * G[2][2];
   if constexpr (ROT) {
     r[5] = G[2][1] - G[1][2];
     r[6] = G[0][2] - G[2][0];
@@ -270,14 +258,14 @@ interp_deriv_kernel(const double *__restrict__ x, const T *__restrict__ grids,
   if constexpr (HU)
 #pragma unroll
     for (int k = 0; k < 3; ++k) r[5 + NR + k] = U[k];
-  wave_sums<5 + NR + NU>(lane, r, [&](int k, T v) {
+  wave_sums<5 + NR + NU>(lane, r, [&](int k, double v) {
     const int c = k < 5 ? 6 + k : (k < 5 + NR ? k - 2 : k - 5 - NR);
     if (!((mask >> c) & 1)) return;
     const double f = c < 3 ? 1.0
                            : (c < 6 ? -0.5 : (c < 10 ? -0.70710678118654752440
                                                      : -0.40824829046386301637));
     double *o = out + (size_t)C.p * ia.lo.stride + c - ia.lo.off;
-    const double s = ia.scale * f * (double)v;
+    const double s = ia.scale * f * v;
     *o = ia.accumulate ? *o + s : s;
   });
 }
@@ -331,19 +319,18 @@ void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, 
     return;
   }
   if (cs.n < 1) return;
-  const T *wt = weights<T>(h);
   ProfScope ps(h, PK_INTERP, (double)cs.n * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
   const InterpArgs ia = interp_args<T>(h, lo, accumulate, scale);
   with_planes(ia.P, [&](auto planes) {
     with_count(cs.n, [&](auto count) {
       constexpr int PZ = decltype(planes)::value, M = decltype(count)::value;
       if (h.deriv)
-        hipLaunchKernelGGL((interp_kernel<T, cplx<T>, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256),
-                           0, h.stream, x, grids, reinterpret_cast<const cplx<T> *>(wt), ia, cs,
-                           out);
+        hipLaunchKernelGGL((interp_kernel<T, double2, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256),
+                           0, h.stream, x, grids, reinterpret_cast<const double2 *>(h.wt64), ia,
+                           cs, out);
       else
-        hipLaunchKernelGGL((interp_kernel<T, T, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256), 0,
-                           h.stream, x, grids, wt, ia, cs, out);
+        hipLaunchKernelGGL((interp_kernel<T, double, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256), 0,
+                           h.stream, x, grids, (const double *)h.wt64, ia, cs, out);
     });
   });
   PSE_LAUNCH_CHECK();
@@ -354,7 +341,7 @@ void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, 
 template <typename T>
 void interp_deriv(Handle &h, const double *x, const T *grids, bool hu, const CompSet &cs,
                   double *out, Layout lo, bool accumulate, double scale) {
-  const cplx<T> *wt = reinterpret_cast<const cplx<T> *>(weights<T>(h));
+  const double2 *wt = reinterpret_cast<const double2 *>(h.wt64);
   ProfScope ps(h, PK_INTERP, (hu ? 6.0 : 3.0) * h.ngrid * sizeof(T) + (double)h.n * (3 + cs.n) * 8);
   const InterpArgs ia = interp_args<T>(h, lo, accumulate, scale);
   int mask = 0;

@@ -697,8 +697,8 @@ struct WeightArgs {
   GridGeom g;
   int64_t n;
   int pad, rw;        // S - 1 zeros; entries of a row
-  double *w64;        // rows in each precision, or NULL
-  float *w32;
+  double *w64;
+  float *w32;         // or NULL
 };
 
 constexpr int W_THREADS = 192;
@@ -751,10 +751,10 @@ __device__ __forceinline__ void weight_rows(unsigned blk, const double *__restri
              (-2.0 * g.kcoef * (rowd[row] + a * g.h) - rowd[W_THREADS + row]) * w;
     }
     if constexpr (DERIV) {
-      if (wa.w64) reinterpret_cast<double2 *>(wa.w64)[o0 + k] = double2{w, gw};
+      reinterpret_cast<double2 *>(wa.w64)[o0 + k] = double2{w, gw};
       if (wa.w32) reinterpret_cast<float2 *>(wa.w32)[o0 + k] = float2{(float)w, (float)gw};
     } else {
-      if (wa.w64) wa.w64[o0 + k] = w;
+      wa.w64[o0 + k] = w;
       if (wa.w32) wa.w32[o0 + k] = (float)w;
     }
     row += drow;
@@ -854,11 +854,9 @@ static void build_lists(Handle &h, const double *xw, bool spreading) {
   wa.n = h.n;
   wa.pad = h.stile - 1;
   wa.rw = weight_row(h.d.support, h.stile);
-  // (without spreading only the noise is interpolated, in a mixed handle from
-  // its FP32 grids)
-  h.rows64_current = h.stile && (spreading || !h.mixed);
-  wa.w64 = h.rows64_current ? h.wt64 : nullptr;
-  wa.w32 = h.wt32;
+  // interpolation reads the FP64 rows, FP32 spreading the FP32 ones
+  wa.w64 = h.wt64;
+  wa.w32 = spreading ? h.wt32 : nullptr;
   // the coefficients' workgroups walk the list (its length is on the device)
   const unsigned nbc = std::min(nblocks(h.pl_cap, W_THREADS), (unsigned)h.num_cu * 32u);
   const unsigned nbw = !h.stile ? 0 : nblocks(3 * (size_t)h.n, W_THREADS);

@@ -180,7 +180,6 @@ struct Handle {
   Bins sbins;
   int stile;                 // grid points per tile side with weight rows (0: none)
   bool tiles_current = false; // tile lists built at the last cell build's positions
-  bool rows64_current = false; // and the weight rows in FP64
   int max_lds = 65536;       // dynamic LDS a workgroup may use on this device
   int num_cu = 256;          // compute units of the device
 
@@ -219,8 +218,9 @@ struct Handle {
   int *tl_cnt = nullptr, *tl_start = nullptr, *tl_scan = nullptr;
   TileRec *tl_rec = nullptr;
   size_t tl_cap = 0;
-  // one-dimensional Gaussian weights per particle and axis, in the precisions
-  // the handle works in (see weight_rows); with spreading tiles only
+  // one-dimensional Gaussian weights per particle and axis, in FP64 and, for
+  // spreading onto FP32 grids, in FP32 (see weight_rows); with spreading tiles
+  // only
   double *wt64 = nullptr;
   float *wt32 = nullptr;
 

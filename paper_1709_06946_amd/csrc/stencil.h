@@ -33,15 +33,10 @@ inline GridGeom geom(const Handle &h) {
   return g;
 }
 
-// The particles' weight rows in the kernels' precision.
+// The particles' weight rows that spreading onto grids of T reads.
 template <typename T> inline const T *weights(const Handle &h) {
-  if constexpr (sizeof(T) == 8) {
-    if (!h.rows64_current)
-      throw Error{PSE_ERR_INVALID, "FP64 weight rows not built for these positions"};
-    return h.wt64;
-  } else {
-    return h.wt32;
-  }
+  if constexpr (sizeof(T) == 8) return h.wt64;
+  else return h.wt32;
 }
 
 }  // namespace pse
