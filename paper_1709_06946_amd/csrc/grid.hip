@@ -565,13 +565,18 @@ __device__ __forceinline__ void p_column(int c, R kx, R ky, R kz, R j0, R f1, bo
   }
 }
 
-// P_c as a linear form, P_c(k) = B + A k without its radial factor: B = e_c for
-// forces (real), A for couplets (times i; the column of p_column with f1 = 1).
+// P_c as a linear form in the integer wave vector n, P_c(k) = B + (2 pi / L) CK
+// A n without its radial factor: B = e_c for forces (real), A for couplets
+// (times i; the column of p_column with f1 = 1).  With CK and 2 pi / L apart, n
+// and nearly all of A are exact in FP32 too; the constants join the radial
+// factors in FP64 before those are rounded (rounded into the columns they shift
+// every mode alike: -3 / sqrt 2 alone the stresslet-strain block by 9e-8).
+constexpr double CK = -3.0 * 0.70710678118654752440;
 template <typename R> struct ColumnForm {
   R A[3][3], B[3];
   __device__ __forceinline__ explicit ColumnForm(int c) {
-    const R r2 = (R)(-3.0 * 0.70710678118654752440), r6 = (R)(-3.0 * 0.40824829046386301637);
-    const R a = (R)1.5;
+    const R r2 = (R)1, r6 = (R)0.57735026918962576451;   // 1 / sqrt 3
+    const R a = (R)-0.70710678118654752440;              // 1.5 / CK
 #pragma unroll
     for (int m = 0; m < 3; ++m) B[m] = c == m ? (R)1 : (R)0;
     A[0][0] = c == 9 ? r2 : (c == 10 ? r6 : (R)0);
@@ -584,7 +589,7 @@ template <typename R> struct ColumnForm {
     A[1][2] = c == 8 ? r2 : (c == 3 ? a : (R)0);
     A[2][1] = c == 8 ? r2 : (c == 3 ? -a : (R)0);
   }
-  // the part of a column that kx and ky give
+  // the part of a column that n_x and n_y give
   __device__ __forceinline__ void fixed(R kx, R ky, R *o) const {
 #pragma unroll
     for (int m = 0; m < 3; ++m) o[m] = B[m] + A[m][0] * kx + A[m][1] * ky;
@@ -692,7 +697,7 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
   const int ky = kidx(iy, N);
   const size_t hsz = (size_t)M * N * N, plane = (size_t)N * M;
   const size_t base = (size_t)iy * M + ix;
-  const T tp = (T)kg.twopi_L;
+  const double ck = DG ? 1.0 : kg.twopi_L * CK;   // couplets' constant (ColumnForm)
   C rho[E][3];
 #pragma unroll
   for (int e = 0; e < E; ++e)
@@ -726,6 +731,7 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
       T f;
       if constexpr (KEEP) f = f1[e];
       else f = (T)entry(e).y;
+      if constexpr (!DG) f = (T)(ck * (double)f);
 #pragma unroll
       for (int m = 0; m < 3; ++m) {
         rho[e][m].x *= f;
@@ -784,10 +790,10 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
     } else {
       const ColumnForm<T> F(c);
       T col0[3];
-      F.fixed(tp * ix, tp * ky, col0);
+      F.fixed((T)ix, (T)ky, col0);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const T kz = tp * kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
+        const T kz = (T)kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
         const T gx = c < 3 ? v[e].x : -v[e].y, gy = c < 3 ? v[e].y : v[e].x;
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
@@ -810,9 +816,11 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
       for (int m = 0; m < 3; ++m) rho[e][m] = C{(T)0, (T)0};
       continue;
     }
-    T scale = (T)tb.z;
-    if (!cin.both) scale *= cin.kind ? (T)tb.y : (T)tb.x;
-    if (!cout.both) scale *= cout.kind ? (T)tb.y : (T)tb.x;
+    const double kind[2] = {(double)tb.x, ck * (double)tb.y};
+    double factor = (double)tb.z;
+    if (!cin.both) factor *= kind[cin.kind];
+    if (!cout.both) factor *= kind[cout.kind];
+    const T scale = (T)factor;
     const T kv[3] = {(T)ix, (T)ky, (T)kz};
     const T inv = (T)1 / (T)n2;
     T krx = 0, kry = 0;
@@ -842,10 +850,10 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
     } else {
       const ColumnForm<T> F(c);
       T col0[3];
-      F.fixed(tp * ix, tp * ky, col0);
+      F.fixed((T)ix, (T)ky, col0);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const T kz = tp * kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
+        const T kz = (T)kidx(reg_pos<N, E, RL>(t, e / RL, e % RL), N);
         T re = (T)0, im = (T)0;
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
