@@ -593,14 +593,15 @@ es_pair_kernel(const double *__restrict__ xw, const double *__restrict__ in, Lay
 #pragma unroll
   for (int k = 0; k < 5; ++k) acc[k] = group_sum(acc[k]);
   if (lane >= 5) return;
-  // lane k finishes component k; the self block is f s at r = 0
+  // lane k finishes component k in FP64; the self block is f s at r = 0 and the
+  // larger part of a dilute sum
   T a = acc[0];
 #pragma unroll
   for (int k = 1; k < 5; ++k) a = lane == k ? acc[k] : a;
   const double v = in[(size_t)i * lin.stride + 6 - lin.off + lane];
-  const T f = (T)-3 * tab[4] - tab[5];
+  const double f = -3.0 * (double)tab[4] - (double)tab[5];
   out[(size_t)i * ra.lout.stride + 6 - ra.lout.off + lane] =
-      alpha * v + beta * (double)((T)-9 * (a + f * (T)v));
+      alpha * v + beta * (-9.0 * ((double)a + f * v));
 }
 
 static int mask_of(const CompSet &cs) {
