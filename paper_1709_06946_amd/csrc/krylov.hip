@@ -917,9 +917,11 @@ static int first_look(const int *prev, size_t n) {
 // Lanczos approximation of y = A^(1/2) b (Chow & Saad): full
 // reorthogonalization, stop when the relative change of the iterate falls
 // below tol.  The iterate is y_m = |b| V_m f(T_m) e_1; with V_m orthonormal
-// its change is the change of the small coefficient vector.  Per-iteration
-// values are kept, so the first converged iteration (or a breakdown) is found
-// exactly whenever the host looks (first_look); later iterations are discarded.
+// its change is the change of the small coefficient vector.  The result does
+// not depend on when the host looks (first_look): later iterations than the one
+// that met the rule are discarded, and when the first look finds it met, the
+// changes of the iterations before are formed too (their scalars are kept) and
+// the first that met it is taken.
 KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n, double *y,
                           int maxit, double tol, int *prev_iters) {
   const int M = maxit, hcap = M + 1;
@@ -935,6 +937,7 @@ KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n, dou
   const int check_from = first_look(prev_iters, n);
   const volatile double *vh = h.kry + 1, *ch = host_change;
   int m = 0;
+  bool looked = false;
   for (int j = 0; j < M; ++j) {
     double *w = V + (size_t)(j + 1) * n;
     A(V + (size_t)j * n, w);
@@ -946,7 +949,7 @@ KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n, dou
     c.hcap = hcap;
     krylov_step(h, V, n, j + 1, w, z.h1, z.h2, c);
     // f(T) e_1 is needed from one iteration before the first look on (the
-    // change there is taken against it); a breakdown recomputes its own
+    // change there is taken against it)
     if (j + 2 >= check_from || j + 1 >= M)
       lanczos_coef(h, z, M, j + 1, host_change, nullptr, 0.0, false);
     m = j + 1;
@@ -958,25 +961,29 @@ KrylovResult lanczos_sqrt(Handle &h, const Op &A, const double *b, size_t n, dou
       vzero(h, y, n);
       return KrylovResult{0, 0.0, true, 0.0};
     }
-    int brk = -1;
-    for (int i = 0; i <= j; ++i)
-      if (vh[i] <= 1e-14 * res.bnorm) {
-        brk = i;
-        break;
+    // a breakdown: the Krylov space is exhausted after i + 1 vectors
+    const auto broke = [&](int i) { return vh[i] <= 1e-14 * res.bnorm; };
+    int stop = 0;
+    while (stop <= j && !broke(stop)) ++stop;
+    if (stop > j && j > 0 && ch[j] < tol) stop = j;
+    if (stop <= j) {
+      int formed = j;   // f(T) e_1's iteration
+      if (!looked && j > 0) {
+        for (formed = 0; formed < stop; ++formed)
+          lanczos_coef(h, z, M, formed + 1, host_change, nullptr, 0.0, false);
+        lanczos_coef(h, z, M, stop + 1, host_change, nullptr, 0.0, false);
+        host_scalars(h, hcap, j + 1);
+        for (int i = 1; i < stop; ++i)
+          if (ch[i] < tol) stop = i;
       }
-    if (brk >= 0) {
-      // breakdown: the Krylov space is exhausted after brk + 1 vectors
-      if (brk < j) lanczos_coef(h, z, M, brk + 1, nullptr, nullptr, 0.0, false);
-      m = brk + 1;
-      res.resid = ch[brk];
+      if (formed != stop) lanczos_coef(h, z, M, stop + 1, nullptr, nullptr, 0.0, false);
+      m = res.iters = stop + 1;
+      res.resid = ch[stop];
       res.converged = true;
       break;
     }
+    looked = true;
     res.resid = ch[j];
-    if (j > 0 && ch[j] < tol) {
-      res.converged = true;
-      break;
-    }
   }
   if (prev_iters) *prev_iters = res.iters;
   gemv_small(h, V, n, m, z.coef, y, n, 1.0, false, nullptr);
