@@ -1261,9 +1261,9 @@ __global__ void real_noise_kernel(uint64_t seed, uint64_t counter, int64_t n, in
 // --------------------------------------------------------- small kernels --
 
 template <typename T>
-__global__ void zero_kernel(T *g, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) g[i] = (T)0;
+__global__ void __launch_bounds__(256) zero_kernel(T *g, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
+    g[i] = (T)0;
 }
 
 template <typename T>
@@ -1357,8 +1357,6 @@ static dim3 tile_blocks(const Handle &h, int parts) {
 static void check_tiles(const Handle &h) {
   if (!h.tiles_current)
     throw Error{PSE_ERR_INVALID, "spreading tile lists not built for these positions"};
-  if (h.stile != 4 && h.stile != 8)
-    throw Error{PSE_ERR_INVALID, "unsupported spreading tile"};
 }
 
 template <typename T>
@@ -1582,7 +1580,9 @@ void real_noise(Handle &h, uint64_t seed, uint64_t counter, double *out, int nco
 template <typename T> void zero_grids(Handle &h, T *g, int ncomp) {
   const size_t n = (size_t)ncomp * h.ngrid;
   ProfScope ps(h, PK_ZERO, (double)n * sizeof(T));
-  hipLaunchKernelGGL(zero_kernel<T>, dim3(nblocks(n, 256)), dim3(256), 0, h.stream, g, n);
+  // (a launch has fewer than 2^32 threads; eleven grids of 768^3 points have more)
+  const unsigned nb = (unsigned)std::min<size_t>((n + 255) / 256, size_t(1) << 23);
+  hipLaunchKernelGGL(zero_kernel<T>, dim3(nb), dim3(256), 0, h.stream, g, n);
   PSE_LAUNCH_CHECK();
 }
 

@@ -300,8 +300,8 @@ template <typename F> static void with_planes(int P, F f) {
   else if (P == 9) f(std::integral_constant<int, 9>());
   else if (P == 10) f(std::integral_constant<int, 10>());
   else if (P <= 12) f(std::integral_constant<int, 12>());
-  else if (P <= 16) f(std::integral_constant<int, 16>());
-  else throw Error{PSE_ERR_INVALID, "interpolation: support beyond 16"};
+  else if (P <= 15) f(std::integral_constant<int, 15>());
+  else throw Error{PSE_ERR_INVALID, "interpolation: support beyond 15"};
 }
 
 template <typename F> static void with_count(int n, F f) {
@@ -324,13 +324,15 @@ void interpolate(Handle &h, const double *x, const T *grids, const CompSet &cs, 
   with_planes(ia.P, [&](auto planes) {
     with_count(cs.n, [&](auto count) {
       constexpr int PZ = decltype(planes)::value, M = decltype(count)::value;
-      if (h.deriv)
-        hipLaunchKernelGGL((interp_kernel<T, double2, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256),
-                           0, h.stream, x, grids, reinterpret_cast<const double2 *>(h.wt64), ia,
-                           cs, out);
-      else
-        hipLaunchKernelGGL((interp_kernel<T, double, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256), 0,
-                           h.stream, x, grids, (const double *)h.wt64, ia, cs, out);
+      if constexpr (PZ <= 10)   // derivative gridding's supports
+        if (h.deriv) {
+          hipLaunchKernelGGL((interp_kernel<T, double2, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256),
+                             0, h.stream, x, grids, reinterpret_cast<const double2 *>(h.wt64), ia,
+                             cs, out);
+          return;
+        }
+      hipLaunchKernelGGL((interp_kernel<T, double, PZ, M>), dim3(nblocks(h.n, 4)), dim3(256), 0,
+                         h.stream, x, grids, (const double *)h.wt64, ia, cs, out);
     });
   });
   PSE_LAUNCH_CHECK();

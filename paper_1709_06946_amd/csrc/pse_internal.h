@@ -445,9 +445,11 @@ inline size_t tiles_per_particle(int P, int S) {
 // Entries of a weight row (P weights with S - 1 zeros on either side).
 inline int weight_row(int P, int S) { return P + 2 * (S - 1); }
 // Spreading tile side: the stencil may reach one tile beyond its particle's
-// bin, with one grid point of slack for rounding in the bin assignment.
+// bin, with one grid point of slack for rounding in the bin assignment.  0:
+// no tiles (support 16, grids of fewer than three tiles a side), spreading by
+// atomics and interpolation without weight rows.
 inline int spread_tile(int grid, int P) {
-  for (int S : {8, 4, 16}) {
+  for (int S : {8, 4}) {
     const int need = (P & 1) ? P + 1 : P + 2;
     if (grid % S == 0 && grid / S >= 3 && need <= 2 * S) return S;
   }
