@@ -169,7 +169,7 @@ spread_tile_kernel(const double *__restrict__ q, Layout lq, CompSet cs, int ng, 
     if (lane < cnt)
 #pragma unroll
       for (int k = 0; k < NCM; ++k) mom[lane * NQ + k] = (T)qv[k];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     for (int c = 0; c < cnt; ++c) {
       const int wz = __builtin_amdgcn_readlane(r.win, c) >> 16;
       const T *w = items + c * NI;
@@ -187,7 +187,7 @@ spread_tile_kernel(const double *__restrict__ q, Layout lq, CompSet cs, int ng, 
         for (int k = 0; k < NCM; ++k) acc[z][k] += zw[z] * f[k];
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
   }
 #pragma unroll
   for (int z = 0; z < ZPT; ++z) {
@@ -260,7 +260,7 @@ spread_deformed_kernel(const double *__restrict__ x, const double *__restrict__ 
 #pragma unroll
       for (int k = 0; k < NCM; ++k) lds_q[wave][c][k] = k < cs.n ? (T)qp[cs.idx[k]] : (T)0;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     for (int c = 0; c < cnt; ++c) {
       const double *xc = lds_x[wave][c];
       const int *o = lds_o[wave][c];
@@ -282,7 +282,7 @@ spread_deformed_kernel(const double *__restrict__ x, const double *__restrict__ 
         for (int k = 0; k < NCM; ++k) acc[z][k] += w * mom[k];
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
   }
 #pragma unroll
   for (int z = 0; z < ZPT; ++z) {
@@ -348,7 +348,7 @@ spread_deriv_kernel(const double *__restrict__ q, Layout lq, int iL, int iS, int
       o[4] = xy + lz;    o[5] = b - a;    o[6] = yz - lx;
       o[8] = xz - ly;    o[9] = yz + lx;  o[10] = (T)-2 * b;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     for (int c = 0; c < cnt; ++c) {
       const int wz = __builtin_amdgcn_readlane(r.win, c) >> 16;
       const W *w = items + c * NI;
@@ -374,7 +374,7 @@ spread_deriv_kernel(const double *__restrict__ q, Layout lq, int iL, int iS, int
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
   }
 #pragma unroll
   for (int z = 0; z < ZPT; ++z) {

@@ -258,8 +258,7 @@ __device__ __forceinline__ void finish_column(const Column &c, int j, const doub
     cs_l[i] = c.cs[i];
     sn_l[i] = c.sn[i];
   }
-  // one wavefront: its LDS accesses are in order
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_sync();
   if (lane != 0) return;
   double *col = c.H + (size_t)j * c.ldh;
   double a = cl[0];
@@ -352,7 +351,7 @@ finish_kernel(double *w, const double *V, size_t ldv, int m, size_t n,
          (size_t)gridDim.x * 256);
   if (blockIdx.x != 0 || threadIdx.x >= 64) return;
   for (int j = threadIdx.x; j < m; j += 64) h1l[j] = h1[j];
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_sync();
   finish_column(c, m - 1, h1l, h, nn, cl, cs, sn);
 }
 
@@ -524,10 +523,10 @@ solve_gemv_kernel(const double *__restrict__ V, size_t ldv, int k, const double 
     for (int j = k - 1; j >= 0; --j) {
       const double *col = staged ? R + j * (j + 1) / 2 : H + (size_t)j * ldh;
       const double cj = c[j] / col[j];
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
       for (int i = threadIdx.x; i < j; i += 64) c[i] -= col[i] * cj;
       if (threadIdx.x == 0) c[j] = cj;
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
     }
   }
   __syncthreads();

@@ -473,6 +473,15 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
   return x * per + (x < rem ? x : rem) + i;
 }
 
+// What a wavefront's lanes have written to LDS is read by its other lanes after
+// this.  The hardware runs a wavefront's LDS accesses in order, so it emits
+// nothing; it keeps the compiler from moving them across.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---- neighbour-bin enumeration (device helpers shared by the list builders)
 
 // Lanes 0..26 of a wavefront take the 27 bins around (cx, cy, cz) of a
