@@ -651,12 +651,19 @@ template <typename T, typename F> static void with_records(const T *rec, F f) {
   }
 }
 
+// Pairs that the stage profiler counts a sum with: the last length the host
+// learned, or the list's capacity while it has learned none (asynchronous
+// calls never tell).
+static double profiled_pairs(const Handle &h) {
+  return (double)(h.pl_pairs ? h.pl_pairs : h.pl_cap);
+}
+
 template <typename T>
 void real_es(Handle &h, const double *xw, const double *in, Layout lin, double *out, Layout lout,
              double alpha, double beta) {
   const T *tab, *rec;
   real_data<T>(h, tab, rec);
-  ProfScope ps(h, PK_REAL, (double)h.pl_pairs * (4.0 + (rec ? 6 * sizeof(T) : 0)) +
+  ProfScope ps(h, PK_REAL, profiled_pairs(h) * (4.0 + (rec ? 6 * sizeof(T) : 0)) +
                                (double)h.n * (5 * 8 * 2 + 8));
   with_records<T>(rec, [&](auto R) {
     hipLaunchKernelGGL((es_pair_kernel<T, decltype(R)::value>),
@@ -677,7 +684,7 @@ void real_apply(Handle &h, const double *xw, const double *in, Layout lin, const
   }
   const T *tab, *rec;
   real_data<T>(h, tab, rec);
-  ProfScope ps(h, PK_REAL, (double)h.pl_pairs * (4.0 + (rec ? PAIR_REC * sizeof(T) : 0)) +
+  ProfScope ps(h, PK_REAL, profiled_pairs(h) * (4.0 + (rec ? PAIR_REC * sizeof(T) : 0)) +
                                (double)h.n * (NC * 8 * 2 + 8 + 24));
   const bool uf = ra.in_mask & 1, uc = (ra.in_mask & 6) != 0;
   const bool ou = ra.out_mask & 1, od = (ra.out_mask & 6) != 0;
