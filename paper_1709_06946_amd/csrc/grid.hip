@@ -12,19 +12,12 @@
 // interpolation each contribute that factor once; the k-space scaling
 // divides both out again.
 #include <algorithm>
-#include <mutex>
 #include <type_traits>
 
 #include "fftreg.h"
 #include "stencil.h"
 
 namespace pse {
-
-// ---------------------------------------------------------------- helpers --
-
-template <typename T> __device__ __forceinline__ T &part(cplx<T> &z, int k) {
-  return (k & 1) ? z.y : z.x;
-}
 
 // ------------------------------------------------------------- spreading --
 
@@ -502,15 +495,11 @@ __device__ __forceinline__ void deformed_k(const KGeom &kg, int i, int j, int l,
     kv[r] = kg.twopi_L * (kg.Ai[r] * i + kg.Ai[3 + r] * j + kg.Ai[6 + r] * l);
 }
 
-// Every stored wave vector is k = (2 pi / L) (i, j, l) with integers, so all
-// radial factors depend on |k|^2 only through the integer n2 = i^2 + j^2 + l^2
-// <= 3 (N/2)^2.  The table holds, per n2:
+// Radial factors of a wave number with square k2:
 //   x = j0(ka), y = f1(ka), z = h^6/(V eta) (1 + u) e^{-(1 - eta_s) u} / k^2,
 //   w = h^3/sqrt(V eta) sqrt(1 + u) e^{-(1 - eta_s) u / 2} / k,  u = k^2 / 4 xi^2
 // (the mobility scaling of Eq. WSops2 with both Gaussian factors divided out,
-// and the amplitude of Eq. FFTsqrt).  Entry 0 (k = 0) is zero.
-// Radial factors of one wave number k^2 (the entries of the |k|^2 table):
-// j0(ka), f1(ka), the mobility scale and the noise amplitude.
+// and the amplitude of Eq. FFTsqrt).
 __device__ __forceinline__ double4 radial_factors(const KGeom &kg, double k2) {
   const double k = sqrt(k2);
   double j0, f1;
@@ -521,22 +510,15 @@ __device__ __forceinline__ double4 radial_factors(const KGeom &kg, double k2) {
   return double4{j0, f1, mob, amp};
 }
 
+// Every stored wave vector of the cube is k = (2 pi / L) (i, j, l) with
+// integers, so its radial factors depend on the integer n2 = i^2 + j^2 + l^2 <=
+// 3 (N/2)^2 only: a table of them, entry 0 (k = 0) zero.
 __global__ void __launch_bounds__(256)
 ktable_kernel(KGeom kg, int len, double4 *__restrict__ tab) {
   const int n2 = blockIdx.x * blockDim.x + threadIdx.x;
   if (n2 >= len) return;
-  if (n2 == 0) {
-    tab[0] = double4{0, 0, 0, 0};
-    return;
-  }
-  const double k2 = kg.twopi_L * kg.twopi_L * (double)n2;
-  const double k = sqrt(k2);
-  double j0, f1;
-  shape_factors(k * kg.a, j0, f1);
-  const double u = k2 * kg.inv4xi2;
-  const double mob = kg.pref_m * (1.0 + u) * exp(-kg.one_m_etas * u) / k2;
-  const double amp = kg.pref_n * sqrt(1.0 + u) * exp(-0.5 * kg.one_m_etas * u) / k;
-  tab[n2] = double4{j0, f1, mob, amp};
+  tab[n2] = n2 == 0 ? double4{0, 0, 0, 0}
+                    : radial_factors(kg, kg.twopi_L * kg.twopi_L * (double)n2);
 }
 
 // Column of P(k) for moment component c (0..10), as (coef, col): the
@@ -1099,7 +1081,7 @@ kspace_noise_kernel(const double2 *__restrict__ psi, uint64_t seed, uint64_t cou
                     cplx<T> *__restrict__ out, CompSet cout, int dg, KGeom kg,
                     const double4 *__restrict__ ktab, const uint64_t *counter_dev) {
   using C = cplx<T>;
-  const int n = kg.ng, hx = n / 2, hp = n / 2 + 1;
+  const int n = kg.ng, hx = n / 2;
   const size_t hsz = (size_t)hx * n * n;
   const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (tid >= hsz) return;
