@@ -679,7 +679,10 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
   const int ky = kidx(iy, N);
   const size_t hsz = (size_t)M * N * N, plane = (size_t)N * M;
   const size_t base = (size_t)iy * M + ix;
-  const double ck = DG ? 1.0 : kg.twopi_L * CK;   // couplets' constant (ColumnForm)
+  // the couplets' constant (ColumnForm), and with that of the sides whose
+  // factor joins the projection's scale
+  const double ck = kg.twopi_L * CK;
+  const double cks = (!cin.both && cin.kind ? ck : 1.0) * (!cout.both && cout.kind ? ck : 1.0);
   C rho[E][3];
 #pragma unroll
   for (int e = 0; e < E; ++e)
@@ -798,11 +801,10 @@ kspace_fused_kernel(const cplx<T> *__restrict__ in, KOrder cin, cplx<T> *__restr
       for (int m = 0; m < 3; ++m) rho[e][m] = C{(T)0, (T)0};
       continue;
     }
-    const double kind[2] = {(double)tb.x, ck * (double)tb.y};
-    double factor = (double)tb.z;
-    if (!cin.both) factor *= kind[cin.kind];
-    if (!cout.both) factor *= kind[cout.kind];
-    const T scale = (T)factor;
+    T scale = (T)tb.z;
+    if (!cin.both) scale *= cin.kind ? (T)tb.y : (T)tb.x;
+    if (!cout.both) scale *= cout.kind ? (T)tb.y : (T)tb.x;
+    if constexpr (!DG) scale = (T)(cks * (double)scale);
     const T kv[3] = {(T)ix, (T)ky, (T)kz};
     const T inv = (T)1 / (T)n2;
     T krx = 0, kry = 0;
