@@ -33,9 +33,8 @@ PSE_LIST_FN int list_limit(int64_t cap) { return cap < LIST_MAX ? (int)cap : LIS
 
 // Slot of a row's entry `rank`, or -1 where the list (limit entries) ends
 // before it.
-PSE_LIST_FN int list_slot(int start, int64_t rank, int limit) {
-  const int64_t s = start + rank;
-  return s < limit ? (int)s : -1;
+PSE_LIST_FN int list_slot(int start, int rank, int limit) {
+  return rank < limit - start ? start + rank : -1;
 }
 
 // End of the row whose successor starts at `next`: no entry at or beyond the
