@@ -335,7 +335,10 @@ __device__ __forceinline__ void tw_store(C *twl, C first, const C *__restrict__ 
 // Element counts per thread: line passes; the fused k-space kernel, which
 // also keeps three complex numbers per element in registers (FP64: four
 // elements for powers of two, six, radices 6, 3, 2, for 3 * 2^k lengths; FP32
-// twice as many); the one with the three couplet grids in registers.
+// twice as many: 384^3 with five components each way 1307 -> 897 us; 512^3 with
+// six grids in and three out 2370 with four, 2150 with eight, and 2090 in the
+// kernel with four that read both radial factors for every component); the one
+// with the three couplet grids in registers.
 constexpr int line_e(int n) { return n % 3 == 0 ? 12 : (n >= 128 ? 16 : 8); }
 template <typename T> constexpr int fused_e(int n) {
   const int e = n % 3 == 0 ? 6 : 4;

@@ -649,7 +649,8 @@ __device__ __forceinline__ bool zero_mode(int ix, int iy, int iz, int n) {
 // twice the modes, and a line takes half the exchanges.  Bound by the memory
 // and the exchanges' barriers: five components each way at 384^3 in FP32 1.31
 // -> 0.82 ms (1.8 -> 2.8 TB/s), six in and five out 1.52 -> 1.3 ms; at 128^3
-// in FP64, six in and three out, 44 -> 35 us.
+// in FP64, six in and three out, 44 -> 35 us.  At 512^3 in FP32, six in and
+// three out, it is 3 % slower (2.09 -> 2.15 ms).
 struct KOrder {
   int n, both;             // both kinds present
   int kind;                // else the kind: 0 forces, 1 couplets

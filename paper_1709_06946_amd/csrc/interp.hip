@@ -1,6 +1,6 @@
-// Interpolation from the grids to the particles (handles with spreading tiles): the values
-// of the velocity grids, and with derivative gridding the gradients of
-// v = 3 f1(ka) u^'s grids, weighted with the particles' weight rows.
+// Interpolation from the grids to the particles (handles with spreading tiles):
+// the values of the velocity grids, and with derivative gridding the gradients
+// of v = 3 f1(ka) u^'s grids, weighted with the particles' weight rows.
 //
 // One wavefront per particle, particles in cell order, each XCD taking a
 // contiguous range of them so that neighbouring stencils share its L2.  Lane l
@@ -10,14 +10,17 @@
 // and the x and y weights come in once per column.  A point costs one load and
 // one or two multiply-adds; with weights and offsets formed per point the
 // arithmetic was as long as the loads (633 vector instructions per particle at
-// support 8, 2400 at support 10).  Weights, products and sums are FP64 on FP32
-// grids too: rounded one-dimensional weights share their errors over whole
-// rows and planes of the stencil (5.5e-8 of the value, rms, against 3.4e-8 with
-// each point's weight rounded once), and FP64 costs the step under 1 %.  Gradient
-// interpolation at 512^3, N = 10^6: 1.89 -> 1.45 ms, at 192^3, N = 2*10^5: 345
-// -> 207 us; five components at 384^3, N = 2*10^5, support 10: 1.17 -> 0.99
-// ms.  What bounds it now is the L1 cache: a load of 8 rows of 32 bytes takes
-// it some 35 cycles.
+// support 8, 2400 at support 10; now 240 and 390 with three and five components
+// from FP32 grids).  Weights, products and sums are FP64 on FP32 grids too:
+// rounded one-dimensional weights share their errors over whole rows and planes
+// of the stencil (5.5e-8 of the value, rms, against 3.4e-8 with each point's
+// weight rounded once).  FP64 takes 1 to 6 % of these kernels' time.  Against
+// weights formed per point, gradient interpolation at 512^3, N = 10^6: 1.89 ->
+// 1.47 ms, at 192^3, N = 2*10^5: 345 -> 221 us; five components at 384^3, N =
+// 2*10^5, support 10: 1.17 -> 1.03 ms; six grids at 512^3 in one launch 2.92 ->
+// 3.02 ms.  What bounds it now is the L1's misses: of 295 accesses a particle at
+// 512^3 216 go on to the L2, and the L1 stalls on them for 70 % of the kernel's
+// cycles (at 192^3 175 of 310 and 56 %).
 #include <type_traits>
 
 #include "fftreg.h"
